@@ -4,9 +4,10 @@
 // executor.
 //
 // SHJ: fill table -> build -> count -> scan -> write (or build -> one-pass write).
-// PHJ: per pass: hist -> scan -> scatter (R and S in the same launches); then
-// plan the partition pairs -> HBM tables for oversized R partitions -> count ->
-// scan -> write (or one-pass write).
+// PHJ: hist -> starts -> scatter (R and S in the same launches; with more than
+// kFuseBits radix bits a second scatter, the partition pairs planned beside the
+// last one; small joins without the starts launch) -> HBM tables for oversized R partitions -> count -> scan -> write
+// (or one-pass write).
 // Everything is enqueued on one stream; no host synchronisation, no
 // host<->device copy and no allocation happen here.
 #include "engine.h"
@@ -178,19 +179,13 @@ hj_status check_params(const hj_params* p, uint64_t n_r, uint64_t n_s, Plan* pl)
 // Workspace layout; with base == nullptr only the size is computed.
 struct PhjWs {
     uint64_t* err;
-    hj::PartSeg* segs1;
-    uint32_t* tb1;
-    uint32_t* hist1;
-    int32_t *keyA, *ridA;
-    hj::PartSeg* segs2;
+    hj::Tuple* A;        // partitioned R, then S: of pass 1, or of a plan's only scatter
+    hj::Tuple* B;        //   of pass 2
+    hj::PartSeg* segs2;  // two scatters
     uint32_t* tb2;
     uint32_t* tseg2;
-    uint32_t* hist2;     // pass-2 histogram (not counted)
-    uint8_t* rows;       // pass-1 count rows (counted pass 2)
-    uint32_t* esc;       //   and their escapes
-    uint32_t* tot2;      // counted pass 2: final partition totals (zeroed block)
-    uint32_t* cur2;      //   and reservation cursors (zeroed block)
-    int32_t *keyB, *ridB;
+    uint32_t* start1;    // pass-1 partition starts (two scatters)
+    uint32_t* start;     // final partition starts
     hj::PartPair* pairs;
     uint32_t* item_begin;
     uint32_t* ovf_begin;
@@ -199,15 +194,24 @@ struct PhjWs {
     uint64_t* wave_cnt;
     uint64_t* ovf_table;
     uint32_t* ovf_next;
-    hj::HeavyQueue* heavy;  // one-pass heavy-tuple queue (cleared with the scan states)
-    hj::HotKeys* hot;       // hot keys of the HBM-table build (cleared with the scan states)
-    uint64_t* st1;     // scan states (cleared by the first kernel): pass-1 histogram,
-    uint64_t* st2;     //   pass-2 histogram,
-    uint64_t* stw;     //   per-wave match counts,
-    uint64_t* stp;     //   join plan
-    uint64_t* zero;    // the queue and the scan states, cleared by the first kernel
-    uint64_t nzero;    // words from `zero` on to clear
+    uint32_t tile1, tile2;  // tuples per scatter workgroup
     uint64_t tiles1, tiles2_ub, items_ub, ovf_ub;
+    bool self;              // self_starts
+    bool clears;            // the last scatter clears the HBM tables
+    hj::HistRows h;
+    uint32_t* rows;         // the histogram's count rows, and the pass-1 ones (fine counts)
+    uint32_t* rows1;
+    uint32_t* cur1;         // first scatter's cursors
+    uint32_t* cnt2;         // second scatter's counts
+    // the block the histogram clears, `nzero` words from `zero` on:
+    uint64_t* zero;
+    uint64_t nzero;
+    hj::HeavyQueue* heavy;  // one-pass heavy-tuple queue
+    hj::HotKeys* hot;       // hot keys of the HBM-table build
+    uint32_t* words;        // [0]: an R partition is oversized
+    uint64_t *st1, *st2;    // scan states: partition starts (pass 1, final),
+    uint64_t* stw;          //   per-wave match counts,
+    uint64_t* stp;          //   join plan
     size_t bytes;
 };
 
@@ -218,27 +222,25 @@ PhjWs phj_layout(const Plan& pl, uint64_t n_r, uint64_t n_s, uint64_t n_r_tab, v
     PhjWs w{};
     Carver c(base);
     const uint64_t n = n_r + n_s;
-    w.tiles1 = cdiv(n_r, pl.tile) + cdiv(n_s, pl.tile);
+    const bool one = hj::one_scatter(pl.passes, pl.b1, pl.b2);
+    const bool hist2 = !hj::counts_final(pl.passes, pl.b1, pl.b2, n);
+    w.clears = n_r_tab && hj::scatter_clears(pl.passes, pl.b1, pl.b2, n);
+    const uint64_t Pc = one ? pl.P : pl.P1;  // partitions of the first scatter
+    w.tile1 = hj::scatter_tile(pl.tile, one ? pl.B : pl.b1, n);
+    w.tiles1 = cdiv(n_r, w.tile1) + cdiv(n_s, w.tile1);
+    const uint32_t bits1 = one ? pl.B : pl.b1, cbits = hist2 ? pl.b1 : pl.B;
+    w.self = one && hj::self_starts(w.tiles1, pl.B);
+    w.h = hj::hist_rows(w.tiles1, hj::cursor_replicas(w.tiles1), cbits);
     w.err = c.take<uint64_t>(1);
-    w.segs1 = c.take<hj::PartSeg>(2);
-    w.tb1 = c.take<uint32_t>(3);
-    w.hist1 = c.take<uint32_t>(w.tiles1 * pl.P1);
-    w.keyA = c.take<int32_t>(n);
-    w.ridA = c.take<int32_t>(n);
-    const bool counted = hj::counted_pass2(pl.passes, pl.b1, pl.b2);
-    if (pl.passes == 2) {
-        w.tiles2_ub = cdiv(n, pl.tile) + 2ull * pl.P1;
+    w.A = c.take<hj::Tuple>(n);
+    if (pl.passes == 2) w.B = c.take<hj::Tuple>(n);  // (two passes that run as one scatter leave it unused)
+    if (!one) {
+        w.tile2 = hj::scatter_tile(pl.tile, pl.b2, n);
+        w.tiles2_ub = cdiv(n, w.tile2) + 2ull * pl.P1;
         w.segs2 = c.take<hj::PartSeg>(2ull * pl.P1);
         w.tb2 = c.take<uint32_t>(2ull * pl.P1 + 1);
         w.tseg2 = c.take<uint32_t>(w.tiles2_ub);
-        if (counted) {
-            w.rows = c.take<uint8_t>(w.tiles1 * pl.P);
-            w.esc = c.take<uint32_t>(w.tiles1 * hj::kCountEsc);
-        } else {
-            w.hist2 = c.take<uint32_t>(w.tiles2_ub * pl.P2);
-        }
-        w.keyB = c.take<int32_t>(n);
-        w.ridB = c.take<int32_t>(n);
+        w.start1 = c.take<uint32_t>(2 * Pc + 1);
     }
     w.pairs = c.take<hj::PartPair>(pl.P);
     w.item_begin = c.take<uint32_t>(pl.P + 1ull);
@@ -248,31 +250,51 @@ PhjWs phj_layout(const Plan& pl, uint64_t n_r, uint64_t n_s, uint64_t n_r_tab, v
     w.item_rec = c.take<hj::ItemRec>(w.items_ub);
     w.ovf_part = c.take<uint32_t>(w.ovf_ub);
     w.wave_cnt = c.take<uint64_t>(w.items_ub * hj::kJoinWaves);
+    // the partition starts (2 P + 1 words of 32 bits) are last read by the
+    // launch before the first that writes wave counts (at least 8 P words of 64)
+    w.start = reinterpret_cast<uint32_t*>(w.wave_cnt);
     w.ovf_table = c.take<uint64_t>(2 * n_r_tab);
     w.ovf_next = c.take<uint32_t>(n_r_tab);
-    const uint64_t n1 = hj::scan_state_words(w.tiles1 * pl.P1);
-    const uint64_t n2 = pl.passes == 2 && !counted ? hj::scan_state_words(w.tiles2_ub * pl.P2) : 0;
+    static_assert(sizeof(hj::HotKeys) % sizeof(uint64_t) == 0, "hot keys in whole words");
+    constexpr uint64_t kHeavyWords = sizeof(hj::HeavyQueue) / sizeof(uint64_t);
+    constexpr uint64_t kHotWords = sizeof(hj::HotKeys) / sizeof(uint64_t);
+    if (w.self) {
+        w.rows = c.take<uint32_t>(w.tiles1 << cbits);
+    } else {
+        // the rows are read by the last launch before the one that first writes
+        // a copy: they lie where copy A will
+        const uint64_t fine = !one && !hist2 ? (uint64_t)w.h.rows() << bits1 : 0;
+        const uint64_t words = ((uint64_t)w.h.rows() << cbits) + fine;
+        w.rows = 4 * words <= 8 * n ? reinterpret_cast<uint32_t*>(w.A) : c.take<uint32_t>(words);
+        if (fine) w.rows1 = w.rows ? w.rows + ((uint64_t)w.h.rows() << cbits) : nullptr;
+    }
+    if (!w.self) w.cur1 = c.take<uint32_t>(2ull * w.h.nx() * Pc);
+    if (!one && !hist2) w.cnt2 = c.take<uint32_t>(2ull * pl.P);
+    const uint64_t c2 = hist2 ? pl.P : 0;  // 64-bit words of a pass-2 histogram's counts
+    const uint64_t n1 = w.self ? 0 : hj::start_state_words(Pc);
+    const uint64_t n2 = one ? 0 : hist2 ? hj::scan_state_words(2ull * pl.P) : hj::start_state_words(pl.P);
     const uint64_t nw = hj::scan_state_words(w.items_ub * hj::kJoinWaves);
     const uint64_t np = hj::plan_state_words(pl.P);
-    static_assert(sizeof(hj::HotKeys) % sizeof(uint64_t) == 0, "hot keys in whole words");
-    const uint64_t nq = sizeof(hj::HeavyQueue) / sizeof(uint64_t) + sizeof(hj::HotKeys) / sizeof(uint64_t);
-    const uint64_t nc = counted ? 2ull * pl.P : 0;  // totals and cursors: 2 P words of 32 bits each
-    uint64_t* zero = c.take<uint64_t>(nq + nc + n1 + n2 + nw + np);
-    w.heavy = reinterpret_cast<hj::HeavyQueue*>(zero);
-    w.hot = zero ? reinterpret_cast<hj::HotKeys*>(zero + sizeof(hj::HeavyQueue) / sizeof(uint64_t)) : nullptr;
-    if (zero) {  // (sizing only when there is no base: no arithmetic on a null pointer)
-        if (counted) {
-            w.tot2 = reinterpret_cast<uint32_t*>(zero + nq);
-            w.cur2 = w.tot2 + 2ull * pl.P;
-        }
-        w.st1 = zero + nq + nc;
-        w.st2 = w.st1 + n1;
-        w.stw = w.st2 + n2;
-        w.stp = w.stw + nw;
-    }
-    w.zero = zero;
-    w.nzero = nq + nc + n1 + n2 + nw + np;
+    w.nzero = kHeavyWords + kHotWords + 1 + c2 + n1 + n2 + nw + np;
+    w.zero = c.take<uint64_t>(w.nzero);
     w.bytes = c.off;
+    if (w.zero) {  // (sizing only when there is no base: no arithmetic on a null pointer)
+        uint64_t* z = w.zero;
+        auto part = [&](uint64_t words) {
+            uint64_t* p = z;
+            z += words;
+            return p;
+        };
+        w.heavy = reinterpret_cast<hj::HeavyQueue*>(part(kHeavyWords));
+        w.hot = reinterpret_cast<hj::HotKeys*>(part(kHotWords));
+        w.words = reinterpret_cast<uint32_t*>(part(1));
+        uint64_t* c2p = part(c2);
+        if (hist2) w.cnt2 = reinterpret_cast<uint32_t*>(c2p);
+        w.st1 = part(n1);
+        w.st2 = part(n2);
+        w.stw = part(nw);
+        w.stp = part(np);
+    }
     return w;
 }
 
@@ -430,98 +452,76 @@ void run_shj(const Plan& pl, const hj_rel& R, const hj_rel& S, const hj_out& out
 // PHJ partitioning (Algorithm 2, n1-n3) of R and S (either may be empty) into
 // w, with the join plan of the partition pairs riding on the last scatter.
 // r_pairs: R's partition ranges from a built table (R is then empty here).
-// The partitioned arrays are returned in *fk / *fr (R first, S from n_r on).
-// *tables_cleared (optional): set when the last scatter cleared the join's HBM tables.
-void phj_partition(const Plan& pl, const hj_rel& R, const hj_rel& S, const PhjWs& w, const hj::PartPair* r_pairs,
-                   uint64_t* zero_total, int32_t** fk, int32_t** fr, hj::Recorder& rec,
-                   bool* tables_cleared = nullptr) {
-    if (tables_cleared) *tables_cleared = false;
+// n_r_tab: tuples of the R that is joined (0: a table build, nothing joined yet).
+// Returns the partitioned tuples (R first, S from n_r on).
+hj::Tuple* phj_partition(const Plan& pl, const hj_rel& R, const hj_rel& S, const PhjWs& w, uint64_t n_r_tab,
+                         const hj::PartPair* r_pairs, uint64_t* zero_total, hj::Recorder& rec) {
     const uint32_t n_r = (uint32_t)R.n, n_s = (uint32_t)S.n;
-    const bool two = pl.passes == 2;
-    const bool counted = two && w.rows;  // (w.rows is set exactly for a counted pass 2 with a workspace)
-    hj::Pass1 p1 = hj::make_pass1(R.key, R.rid, n_r, S.key, S.rid, n_s, pl.tile, pl.b1, w.segs1, w.tb1,
-                                  w.zero, w.nzero, rec.err_clear);
-    if (counted) {
-        p1.rows = w.rows;
-        p1.esc = w.esc;
-        p1.bits_all = pl.B;
-    }
-    // the join plan rides on the last pass's scatter, the pass-2 setup on the first
-    // The plan's records are written at offsets from its chained scan; its wait
-    // keeps the full bound and no injected stall (every consumer of the other
-    // scans clamps what it reads and writes, the item records have no clamp).
-    const hj::ScanCtl plan_ctl{rec.ctl.err, hj::kMaxStatusPolls, 0};
-    hj::SideJob plan{};
+    const bool one = hj::one_scatter(pl.passes, pl.b1, pl.b2);
+    const bool fine = !one && hj::counts_final(pl.passes, pl.b1, pl.b2, R.n + S.n);
+    const hj::PassCfg c1{one ? 0u : pl.b2, one ? pl.B : pl.b1, pl.hash, w.tile1, pl.nt_part};
+    const hj::PassCfg c2{0, pl.b2, pl.hash, w.tile2, pl.nt_part};
+    hj::Pass1 p1 = hj::make_pass1(R.key, R.rid, n_r, S.key, S.rid, n_s, w.tile1);
+    p1.self = w.self;
+    p1.fine_bits = fine ? pl.b2 : 0;
+    p1.h = w.h;
+    p1.rows = w.rows;
+    p1.rows1 = w.rows1;
+    p1.zero = w.zero;
+    p1.nzero = w.nzero;
+    p1.err_clear = rec.err_clear;
+    const hj::StartArgs starts{w.cur1, one ? w.start : w.start1, fine ? w.cnt2 : nullptr, w.start, w.st1, w.st2,
+                               w.words, r_pairs, pl.lds_cap, one || fine ? pl.P : 0, rec.ctl};
+    hj::SideJob plan;
     plan.kind = hj::kSidePlan;
-    plan.blocks = hj::plan_blocks(pl.P, hj::part_block(pl.tile));
-    plan.plan = hj::PlanArgs{two ? w.segs2 : w.segs1, two ? w.tb2 : w.tb1, two ? w.hist2 : w.hist1,
-                             two ? 2 * pl.P1 : 2u, two ? pl.b2 : pl.b1, n_r, n_s, pl.B, pl.lds_cap,
-                             w.pairs, w.item_begin, w.ovf_begin, w.item_rec, w.ovf_part, zero_total, w.stp,
-                             r_pairs, plan_ctl, counted ? w.tot2 : nullptr, (uint32_t)w.items_ub};
-    hj::SideJob setup2{};
-    if (two) {
-        setup2.kind = hj::kSideSetup2;
-        setup2.blocks = 1;
-        setup2.setup2 = hj::Setup2Args{w.hist1, w.tb1, pl.b1, n_r, n_s, pl.tile, pl.b2, 0u, w.keyA, w.ridA,
-                                       w.segs2, w.tb2, w.tseg2};
+    plan.blocks = hj::plan_blocks(pl.P, hj::scatter_block(one ? w.tile1 : w.tile2));
+    plan.plan = hj::PlanArgs{w.start, n_r, n_s, pl.B, pl.lds_cap, w.pairs, w.item_begin, w.ovf_begin, w.item_rec,
+                             w.ovf_part, zero_total, w.stp, r_pairs, rec.ctl, (uint32_t)w.items_ub};
+    const hj::ClearTables clr{w.clears ? w.ovf_table : nullptr, w.words, w.start, r_pairs, pl.P, (uint32_t)n_r_tab,
+                              pl.lds_cap};
+    hj::part_hist(p1, c1, rec);
+    hj::part_starts(p1, c1, starts, rec);
+    if (one) {
+        hj::part_scatter(p1, c1, w.cur1, w.A, nullptr, nullptr, clr, plan, rec);
+        return w.A;
     }
-    hj::PassCfg c1{pl.b2, pl.b1, pl.hash, pl.tile, pl.nt_part};
-    if (counted) {  // the count rows are summed beside the pass-1 scatter's tiles
-        setup2.sums = hj::make_count_sums(w.rows, w.esc, w.tot2, p1.nt_r, p1.ntiles - p1.nt_r, pl.B,
-                                          hj::part_block(pl.tile));
-        setup2.front = hj::count_sum_blocks(setup2.sums, hj::part_block(pl.tile));
+    hj::SideJob setup2;
+    setup2.kind = hj::kSideSetup2;
+    setup2.blocks = 1;
+    setup2.setup2 = hj::Setup2Args{w.start1, pl.b1, w.tile2, n_r, n_s, (uint32_t)w.tiles2_ub, w.segs2, w.tb2, w.tseg2};
+    hj::part_scatter(p1, c1, w.cur1, w.A, nullptr, nullptr, hj::ClearTables{}, setup2, rec);
+    if (!fine) {
+        hj::part_hist2(w.A, w.segs2, w.tb2, w.tseg2, 2 * pl.P1, (uint32_t)w.tiles2_ub, c2, w.cnt2, rec);
+        // R's counters come first, so the sums are positions; the total is the end
+        hj::scan_u32(w.cnt2, w.start, 2ull * pl.P, w.st2, w.start + 2ull * pl.P, rec);
     }
-    hj::part_hist_pass1(p1, c1, w.hist1, rec);  // also writes segs1/tb1 and clears the scan states
-    hj::scan_u32(w.hist1, w.hist1, w.tiles1 * pl.P1, w.st1, nullptr, rec);
-    hj::part_scatter(w.segs1, w.tb1, nullptr, 2, (uint32_t)w.tiles1, c1, w.hist1, w.keyA, w.ridA,
-                     two ? setup2 : plan, rec);
-    *fk = w.keyA;
-    *fr = w.ridA;
-    if (two) {
-        hj::PassCfg c2{0, pl.b2, pl.hash, pl.tile, pl.nt_part};
-        if (counted) {
-            // with R scattered here (not a probe of a built table), its HBM tables are cleared by the scatter
-            const bool clears = tables_cleared && !r_pairs && hj::counted_clears_tables(pl.b2);
-            const hj::Reserve rsv{w.tot2, w.cur2, clears ? w.ovf_table : nullptr, pl.lds_cap, 0u};
-            hj::part_scatter(w.segs2, w.tb2, w.tseg2, 2 * pl.P1, (uint32_t)w.tiles2_ub, c2, nullptr, w.keyB,
-                             w.ridB, plan, rec, &rsv);
-            if (clears) *tables_cleared = true;
-        } else {
-            hj::part_hist(w.segs2, w.tb2, w.tseg2, 2 * pl.P1, (uint32_t)w.tiles2_ub, c2, w.hist2, rec);
-            hj::scan_u32(w.hist2, w.hist2, w.tiles2_ub * pl.P2, w.st2, nullptr, rec);
-            hj::part_scatter(w.segs2, w.tb2, w.tseg2, 2 * pl.P1, (uint32_t)w.tiles2_ub, c2, w.hist2, w.keyB,
-                             w.ridB, plan, rec);
-        }
-        *fk = w.keyB;
-        *fr = w.ridB;
-    }
+    hj::part_scatter2(w.A, w.segs2, w.tb2, w.tseg2, 2 * pl.P1, (uint32_t)w.tiles2_ub, c2, w.start, w.cnt2, w.B, clr,
+                      plan, rec);
+    return w.B;
 }
 
 // PHJ join of the planned partition pairs (Algorithm 1 per pair): HBM tables
 // for oversized R partitions, then count -> scan -> write (or one-pass write).
-// rk/rr: partitioned R, sk/sr: partitioned S.
-void phj_join_pairs(const Plan& pl, const PhjWs& w, const int32_t* rk, const int32_t* rr, const int32_t* sk,
-                    const int32_t* sr, const hj_out& out, uint64_t* d_count, hj::Recorder& rec,
-                    bool tables_cleared = false) {
-    hj::join_ovf_build(w.pairs, w.ovf_begin, w.ovf_part, pl.P, (uint32_t)w.ovf_ub, rk, w.ovf_table, w.ovf_next,
-                       w.hot, pl.one_pass ? w.heavy : nullptr, rec, !tables_cleared);
+// rt: partitioned R, st: partitioned S.
+void phj_join_pairs(const Plan& pl, const PhjWs& w, const hj::Tuple* rt, const hj::Tuple* st, const hj_out& out,
+                    uint64_t* d_count, hj::Recorder& rec) {
+    hj::join_ovf_build(w.pairs, w.ovf_begin, w.ovf_part, pl.P, (uint32_t)w.ovf_ub, rt, w.ovf_table, w.ovf_next,
+                       w.hot, pl.one_pass ? w.heavy : nullptr, rec, !w.clears);
     if (!pl.one_pass) {
-        hj::join_count(w.pairs, w.item_begin, w.item_rec, pl.P, (uint32_t)w.items_ub, rk, sk, pl.lds_cap,
-                       w.ovf_table, w.ovf_next, w.hot, w.wave_cnt, pl.nt_s, rec);
+        hj::join_count(w.item_rec, (uint32_t)w.items_ub, rt, st, pl.lds_cap, w.ovf_table, w.ovf_next, w.hot,
+                       w.wave_cnt, pl.nt_s, rec);
         hj::scan_u64(w.wave_cnt, w.wave_cnt, w.items_ub * hj::kJoinWaves, w.stw, d_count, rec);
     }
-    hj::join_write(w.pairs, w.item_begin, w.item_rec, pl.P, (uint32_t)w.items_ub, rk, rr, sk, sr, pl.lds_cap,
-                   w.ovf_table, w.ovf_next, pl.one_pass ? nullptr : w.wave_cnt, d_count, out.rid_r, out.rid_s,
-                   w.hot, out.capacity, pl.one_pass ? w.heavy : nullptr, pl.nt_s, rec);
+    hj::join_write(w.item_rec, (uint32_t)w.items_ub, rt, st, pl.lds_cap, w.ovf_table, w.ovf_next, w.hot,
+                   pl.one_pass ? nullptr : w.wave_cnt, d_count, out.rid_r, out.rid_s, out.capacity,
+                   pl.one_pass ? w.heavy : nullptr, pl.nt_s, rec);
 }
 
 void run_phj(const Plan& pl, const hj_rel& R, const hj_rel& S, const hj_out& out, void* ws,
              uint64_t* d_count, hj::Recorder& rec) {
     const PhjWs w = phj_layout(pl, R.n, S.n, R.n, ws);
-    int32_t *fk, *fr;
-    bool cleared = false;
-    phj_partition(pl, R, S, w, nullptr, pl.one_pass ? d_count : nullptr, &fk, &fr, rec, &cleared);
-    phj_join_pairs(pl, w, fk, fr, fk + R.n, fr + R.n, out, d_count, rec, cleared);
+    const hj::Tuple* t = phj_partition(pl, R, S, w, R.n, nullptr, pl.one_pass ? d_count : nullptr, rec);
+    phj_join_pairs(pl, w, t, t + R.n, out, d_count, rec);
 }
 
 void run_join(const Plan& pl, const hj_rel& R, const hj_rel& S, const hj_out& out, void* ws,
@@ -548,8 +548,7 @@ void run_build(const Plan& pl, const hj_rel& R, void* ws, hj::Recorder& rec) {
     }
     const PhjWs w = phj_layout(pl, R.n, 0, 0, ws);
     const hj_rel none{nullptr, nullptr, 0};
-    int32_t *fk, *fr;
-    phj_partition(pl, R, none, w, nullptr, nullptr, &fk, &fr, rec);
+    phj_partition(pl, R, none, w, 0, nullptr, nullptr, rec);
 }
 
 void run_probe(const Plan& pl, const hj_table& t, const hj_rel& S, const hj_out& out, void* ws,
@@ -568,10 +567,8 @@ void run_probe(const Plan& pl, const hj_table& t, const hj_rel& S, const hj_out&
         const PhjWs tw = phj_layout(pl, t.n_r, 0, 0, t.ws);
         const PhjWs w = phj_layout(pl, 0, S.n, t.n_r, ws);
         const hj_rel none{nullptr, nullptr, 0};
-        int32_t *fk, *fr;
-        phj_partition(pl, none, S, w, tw.pairs, pl.one_pass ? d_count : nullptr, &fk, &fr, rec);
-        const bool two = pl.passes == 2;
-        phj_join_pairs(pl, w, two ? tw.keyB : tw.keyA, two ? tw.ridB : tw.ridA, fk, fr, out, d_count, rec);
+        const hj::Tuple* s = phj_partition(pl, none, S, w, t.n_r, tw.pairs, pl.one_pass ? d_count : nullptr, rec);
+        phj_join_pairs(pl, w, hj::one_scatter(pl.passes, pl.b1, pl.b2) ? tw.A : tw.B, s, out, d_count, rec);
     }
 }
 

@@ -6,8 +6,8 @@
 //
 //  1. Partition pass: R, then S, streams through the device in chunks; every
 //     chunk is split into 2^k partitions on the k high bits of the key's
-//     MurmurHash 2.0 with the radix kernels of Algorithm 2 (histogram, scan,
-//     scatter: phj_partition.hip), and the partitioned chunk goes back to a
+//     MurmurHash 2.0 with the radix kernels of Algorithm 2 (histogram, scatter:
+//     phj_partition.hip), and the partitioned chunk goes back to a
 //     pinned host buffer together with its partition boundaries.  Two device
 //     slots on two streams alternate, so one chunk's copies overlap the other
 //     chunk's kernels and copies (host->device and device->host run together).
@@ -57,32 +57,30 @@ struct Carve {
 };
 
 // One device slot of the partition pass: a chunk of up to c tuples, its
-// partitioned copy, histogram, scan state and partition boundaries.
+// partitioned copy, count rows, cursors and partition boundaries.
 struct Slot {
-    hj::PartSeg* segs;
-    uint32_t* tb;
-    uint32_t* hist;
     int32_t *kin, *rin, *kout, *rout;
-    uint64_t* st;
+    uint32_t *rows, *cur;  // the histogram's count rows, the scatter's cursors
+    uint64_t* st;          // scan state of the partition starts (cleared by the histogram)
     uint64_t nst;
-    uint32_t* starts;
+    uint32_t* starts;      // [2^k + 1] boundaries (then those of an empty second relation)
     size_t bytes;
 };
 
 Slot slot_layout(uint64_t c, uint32_t k, char* base) {
     Slot s{};
     Carve cv{base};
-    const uint64_t tiles = cdiv(c, kExtTile);
-    s.segs = cv.take<hj::PartSeg>(2);
-    s.tb = cv.take<uint32_t>(3);
-    s.hist = cv.take<uint32_t>(tiles << k);
     s.kin = cv.take<int32_t>(c);
     s.rin = cv.take<int32_t>(c);
     s.kout = cv.take<int32_t>(c);
     s.rout = cv.take<int32_t>(c);
-    s.nst = hj::scan_state_words(tiles << k);
+    const uint64_t tiles = cdiv(c, kExtTile);
+    const uint32_t nx = hj::cursor_replicas(tiles);
+    s.rows = cv.take<uint32_t>((uint64_t)hj::hist_rows(tiles, nx, k).rows() << k);
+    s.cur = cv.take<uint32_t>((2ull * nx) << k);
+    s.nst = hj::start_state_words(1ull << k);
     s.st = cv.take<uint64_t>(s.nst);
-    s.starts = cv.take<uint32_t>((1ull << k) + 1);
+    s.starts = cv.take<uint32_t>((2ull << k) + 1);
     s.bytes = cv.off;
     return s;
 }
@@ -240,15 +238,16 @@ hj_status partition_relation(const hj_rel& X, uint32_t k, uint64_t chunk, Slot* 
         *h2d += 8ull * len;
         hj::Recorder rec;
         init_recorder(rec, s, err, false);
-        const hj::Pass1 p1 = hj::make_pass1(sl.kin, sl.rin, len, nullptr, nullptr, 0, kExtTile, k, sl.segs, sl.tb,
-                                            sl.st, sl.nst, nullptr);
+        hj::Pass1 p1 = hj::make_pass1(sl.kin, sl.rin, len, nullptr, nullptr, 0, kExtTile);
+        p1.h = hj::hist_rows(p1.ntiles, hj::cursor_replicas(p1.ntiles), k);  // (no more rows than the slot's)
+        p1.rows = sl.rows;
+        p1.zero = sl.st;
+        p1.nzero = sl.nst;
         const hj::PassCfg cfg{32 - k, k, HJ_HASH_MURMUR2, kExtTile, len >= hj::kNtMinTuples};
-        const uint32_t tiles = (uint32_t)cdiv(len, kExtTile);
-        hj::part_hist_pass1(p1, cfg, sl.hist, rec);
-        hj::scan_u32(sl.hist, sl.hist, (uint64_t)tiles << k, sl.st, nullptr, rec);
-        hj::SideJob none{};
-        hj::part_scatter(sl.segs, sl.tb, nullptr, 2, tiles, cfg, sl.hist, sl.kout, sl.rout, none, rec);
-        hj::part_starts(sl.hist, tiles, k, len, sl.starts, rec);
+        const hj::StartArgs sa{sl.cur, sl.starts, nullptr, nullptr, sl.st, nullptr, nullptr, nullptr, 0, 0, rec.ctl};
+        hj::part_hist(p1, cfg, rec);
+        hj::part_starts(p1, cfg, sa, rec);
+        hj::part_scatter(p1, cfg, sl.cur, nullptr, sl.kout, sl.rout, hj::ClearTables{}, hj::SideJob(), rec);
         if (rec.err != hipSuccess) return hip_fail("partition launch", rec.err);
         e = hipMemcpyAsync(hk + off, sl.kout, 4ull * len, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipMemcpyAsync(hr + off, sl.rout, 4ull * len, hipMemcpyDeviceToHost, s);

@@ -31,6 +31,20 @@ __device__ __forceinline__ uint32_t radix_hash(int32_t key, uint32_t kind) {
     return kind ? murmur2((uint32_t)key) : (uint32_t)key;
 }
 
+__device__ __forceinline__ int32_t key_of(Tuple t) { return (int32_t)(uint32_t)t; }
+__device__ __forceinline__ int32_t rid_of(Tuple t) { return (int32_t)(uint32_t)(t >> 32); }
+
+// A column of 32-bit values, every kStride-th word from p on: a relation's key
+// or rid array (1), or the keys or rids of partitioned tuples (2).
+template <uint32_t kStride>
+struct Column {
+    const int32_t* __restrict__ p;
+    template <typename Index>
+    __device__ __forceinline__ int32_t operator[](Index i) const {
+        return p[(uint64_t)i * kStride];
+    }
+};
+
 // Full-avalanche 32-bit mixer (the MurmurHash3 finaliser) used to place keys in
 // hash tables; independent of the radix bits so a partition's table is uniform.
 __device__ __forceinline__ uint32_t slot_hash(int32_t key) {
@@ -265,6 +279,9 @@ __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 // counter again wherever the register is reused, and such a wait also waits
 // for every store in flight, which serializes a store loop.
 __device__ __forceinline__ void settle(uint32_t v) { __asm__ volatile("" ::"v"(v)); }
+
+// Waits until this wave's loads, stores and atomics so far are performed.
+__device__ __forceinline__ void await_memory() { __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 __device__ __forceinline__ uint64_t lanemask_lt() {
     const uint32_t l = lane_id();

@@ -80,8 +80,8 @@ __device__ __forceinline__ uint32_t heavy_or_len(const uint32_t* __restrict__ ne
 // key, kV keys per thread per step (Len: an index type that holds r_len).
 // kQueued: entries marked in hs->queued are skipped (count 0).  All threads of
 // the block call it, after the registrations.
-template <uint32_t kBlock, uint32_t kV, bool kQueued = false, typename Len>
-__device__ __forceinline__ void heavy_counts(const int32_t* __restrict__ rk, Len r_len, HeavySet* hs) {
+template <uint32_t kBlock, uint32_t kV, bool kQueued = false, typename Col, typename Len>
+__device__ __forceinline__ void heavy_counts(Col rk, Len r_len, HeavySet* hs) {
     constexpr uint32_t kWaves = kBlock / kWave;
     static_assert(kWaves <= kHeavyMaxWaves, "block too large for the heavy set");
     __syncthreads();  // registrations done
@@ -136,9 +136,8 @@ __device__ __forceinline__ void heavy_counts(const int32_t* __restrict__ rk, Len
 // past `capacity` are not written.  All threads of the block call it, after
 // the positions are set.  kRids: the step's rids are loaded with its keys
 // (more registers, no dependent load per hit).
-template <uint32_t kBlock, uint32_t kV, bool kRids = false, typename Len>
-__device__ __forceinline__ void heavy_writes(const int32_t* __restrict__ rk, const int32_t* __restrict__ rr,
-                                             Len r_len, HeavySet* hs, uint64_t capacity,
+template <uint32_t kBlock, uint32_t kV, bool kRids = false, typename Col, typename Len>
+__device__ __forceinline__ void heavy_writes(Col rk, Col rr, Len r_len, HeavySet* hs, uint64_t capacity,
                                              int32_t* __restrict__ out_r, int32_t* __restrict__ out_s) {
     constexpr Len kStep = (Len)kV * kBlock;
     static_assert(kV <= 32 && kMaxHeavy <= sizeof(hs->wsum) / sizeof(uint32_t), "fill counters fit wsum");
@@ -238,9 +237,8 @@ __device__ __forceinline__ uint32_t claim_chunk(uint32_t* counter, uint32_t* sh)
 
 // rk, rr: the columns the queued tuples' R rows index (job rows r_off ..
 // r_off + r_len - 1).  sh: LDS scratch of 9 + kHeavyV * kBlock / 64 words.
-template <uint32_t kBlock>
-__device__ __forceinline__ void help_heavy(HeavyQueue* Q, const int32_t* __restrict__ rk,
-                                           const int32_t* __restrict__ rr,
+template <uint32_t kBlock, typename Col>
+__device__ __forceinline__ void help_heavy(HeavyQueue* Q, Col rk, Col rr,
                                            unsigned long long* __restrict__ total, uint64_t capacity,
                                            int32_t* __restrict__ out_r, int32_t* __restrict__ out_s, uint32_t* sh) {
     constexpr uint32_t kWaves = kBlock / kWave;

@@ -7,16 +7,18 @@
 
 namespace hj {
 
-// One input segment of a partitioning pass.  A pass partitions every segment
-// independently: the tuples of segment s land in [out_base, out_base + n) of
-// the output arrays, grouped by partition number.
+// Partitioned tuples are 64-bit words: the key in the low 32 bits, the rid in
+// the high 32, so that a run of a partition is one stream of 8-byte stores and
+// a join reads key and rid of a tuple with one load.  Measured on MI355X
+// (2^25 tuples, 8192-tuple tiles): the scatter takes 92 us at 64 partitions
+// and 105 us at 1024 with such words, 99 and 120 us with two columns.
+typedef uint64_t Tuple;
+
+// One segment of a second partitioning pass (a pass-1 partition of R or of S):
+// tuples [base, base + n) of the first copy, which become the same positions
+// of the second one, grouped by partition number.
 struct PartSeg {
-    const int32_t* key_in;
-    const int32_t* rid_in;
-    uint64_t out_base;   // first output position of this segment
-    uint64_t hist_base;  // first histogram entry of this segment (ntiles * P entries)
-    uint32_t n;          // tuples
-    uint32_t pad;
+    uint32_t base, n;
 };
 
 // One join work item: an R partition and a chunk of its S partition
@@ -141,12 +143,7 @@ void shj_write(const int32_t* s_key, const int32_t* s_rid, uint64_t n_s, const u
                Recorder& rec);  // wave_base == nullptr: one-pass output into *total
 
 // ---- phj_partition.hip ----
-// Threads of a partitioning workgroup for a given tile: 512 from 4096 tuples on
-// (twice the waves per CU of 256-thread workgroups at the same LDS per tile;
-// measured on MI355X: the 8192-tuple scatter 1.3x faster, the 16M x 16M join
-// 4% faster), 256 below (the vector tile loads need >= 4 tuples per thread).
 constexpr uint32_t kMinPartBlock = 256;
-inline uint32_t part_block(uint32_t tile) { return tile >= 4096 ? 512u : kMinPartBlock; }
 // Default partitioning tile: 8192 tuples when the join has enough tuples to
 // fill the chip several times over with such tiles and needs the longer
 // partition runs they give (2^25 tuples or more, or 2^24 or more in one pass of
@@ -159,8 +156,8 @@ struct PassCfg {
     uint32_t shift;      // radix bits taken from (hash >> shift)
     uint32_t bits;       // partitions = 1 << bits
     uint32_t hash_kind;  // hj_hash
-    uint32_t tile;       // tuples per tile
-    uint32_t nt;         // tiles read with non-temporal loads
+    uint32_t tile;       // tuples per workgroup of the pass (scatter_tile)
+    uint32_t nt;         // input read with non-temporal loads
 };
 // Non-temporal loads of data a launch reads once pay only once a join's
 // relations outgrow the caches; below that, plain loads leave lines that a
@@ -173,113 +170,159 @@ struct PassCfg {
 constexpr uint64_t kNtMinTuples = 1ull << 24;
 constexpr uint64_t kNtMinBuild = 1ull << 23;
 // Two passes whose final partitions number 2^4..2^kCountedMaxBits are
-// "counted": pass 1 also counts every tile's tuples per final partition (one
-// row of 2^bits 8-bit counts per tile; a count of 255 or more is 0 in the row
-// and goes to the tile's list of kCountEsc escapes instead: a tile of at most
-// 8192 tuples has no more than 32 of them), workgroups at the front of the
-// pass-1 scatter sum the rows into per-relation totals, and pass 2 has no
-// histogram of its own: each pass-2 tile places its runs at the scanned
-// totals of its segment plus what it reserves on a cursor per final
-// partition (the order of tiles inside a partition is then the order of
-// their reservations).  More bits would make the rows larger than the pass-2
-// histogram read they replace.
+// "counted": the histogram of the input counts the final partitions and no
+// later pass has a histogram of its own.
 constexpr uint32_t kCountedMaxBits = 13;
-constexpr uint32_t kCountEsc = 32;       // escapes per tile: (partition << 14) | count, 0 unused
-constexpr uint32_t kCountEscMin = 255;   // counts from here on are escaped
 inline bool counted_pass2(uint32_t passes, uint32_t b1, uint32_t b2) {
     return passes == 2 && b1 + b2 >= 4 && b1 + b2 <= kCountedMaxBits;
 }
-// A counted pass 2's totals and cursors, each 2^(b1 + b2) entries for R then
-// as many for S (index = segment * 2^b2 + partition in the segment).
-struct Reserve {
-    const uint32_t* tot;
-    uint32_t* cur;  // zero before the pass
-    // Optional (nullptr: not done here): the HBM tables of R's partitions of more
-    // than lds_cap tuples (2 slots per tuple at twice its position in R) are
-    // cleared by the tiles that write the partitions' runs, in place of the
-    // clearing launch.  Only with at most 64 partitions per segment.
-    uint64_t* ovf_table;
-    uint32_t lds_cap, pad;
-};
-// Whether a counted pass 2 clears the HBM tables (Reserve::ovf_table).
+// How the partitions of a plan are made.  Up to kFuseBits radix bits in all,
+// two passes run as one scatter straight into the final partitions: a
+// workgroup's runs stay long enough (4 tuples of 16384 at 4096 partitions,
+// the lines of one XCD's runs fit its L2) that one scatter beats two.
+// Measured on MI355X, 2^25 tuples: one scatter into 2^12 partitions 151 us,
+// two of 2^6 each 92 us; 2^13 partitions at once would need runs of 2.
+constexpr uint32_t kFuseBits = 12;
+inline bool one_scatter(uint32_t passes, uint32_t b1, uint32_t b2) { return passes == 1 || b1 + b2 <= kFuseBits; }
+// Whether the histogram of the input counts the final partitions (up to 2^15
+// counters of a workgroup in LDS, 128 KiB); else pass 2 has its own.  Plans of
+// two scatters do so while the workgroups' rows fit the first copy, where they
+// lie until it is written.
+constexpr uint32_t kWideCountBits = 15;
+inline bool counts_final(uint32_t passes, uint32_t b1, uint32_t b2, uint64_t n) {
+    return one_scatter(passes, b1, b2) ||
+           ((counted_pass2(passes, b1, b2) || b1 + b2 <= kWideCountBits) && n >= 160ull << (b1 + b2));
+}
+// Whether the last scatter clears the HBM tables of oversized partitions (it
+// needs the final partitions' sizes before it starts), else a launch of its own.
 inline bool counted_clears_tables(uint32_t b2) { return b2 <= 6; }
-// The sums of a counted pass 2's count rows (Pass1::rows and ::esc: nt_r
-// rows of R, then nt_s of S) into tot[rel * 2^bits + i] (zero before), by
-// workgroups at the front of the pass-1 scatter's grid: the totals are needed
-// only by pass 2, so the sums run beside the scatter's tiles.  Each workgroup
-// takes `rows_per` rows of one relation and a group of 16-count columns
-// (spread over its threads in phases when the group is narrower than it).
-struct CountSums {
-    const uint8_t* rows;
-    const uint32_t* esc;
-    uint32_t* tot;
-    uint32_t nt_r, nt_s, bits, rows_per;
+inline bool scatter_clears(uint32_t passes, uint32_t b1, uint32_t b2, uint64_t n) {
+    return one_scatter(passes, b1, b2) || (counts_final(passes, b1, b2, n) && counted_clears_tables(b2));
+}
+// Tuples per workgroup of a pass into 2^bits partitions: the plan's tile, or
+// more at a high fan-out, where a 4096-tuple tile's runs would be too short, as
+// long as every CU still has a workgroup.  Measured, 2^25 tuples: 2^10
+// partitions 117 / 105 / 122 us with 4096 / 8192 / 16384 tuples, 2^11 149 / 123
+// / 132 us, 2^12 186 / 190 / 151 us.  Tiles below 4096 are the caller's wish.
+constexpr uint32_t kMaxScatterTile = 16384;
+inline uint32_t scatter_tile(uint32_t tile, uint32_t bits, uint64_t n) {
+    const uint32_t want = bits == 12 ? kMaxScatterTile : bits >= 10 ? 8192u : tile;
+    return tile < 4096 || want <= tile || n < 256ull * want ? tile : want;
+}
+// Threads of a partitioning workgroup that takes `tile` tuples.
+inline uint32_t scatter_block(uint32_t tile) { return tile >= 8192 ? 1024u : tile >= 4096 ? 512u : kMinPartBlock; }
+// Replicas of a pass-1 partition's cursor: one for each of the 8 XCDs (tile t
+// reserves in replica t mod 8, and workgroups go to the XCDs round-robin), so that the tuples that one XCD writes to a partition
+// are contiguous and lines are written by one L2.  Measured on MI355X, 2^25
+// tuples, 8192-tuple tiles: 92 against 113 us at 2^6 partitions with one
+// cursor for all, 105 against 146 us at 2^10.  Small joins keep one.
+inline uint32_t cursor_replicas(uint64_t tiles) { return tiles >= 64 ? 8u : 1u; }
+
+// The histogram's workgroups and their count rows.  Workgroup (x, q) = x + q nx
+// counts a contiguous share of the tiles x, x + nx, ... of replica x and writes
+// its counts as row x + q nx; a workgroup that meets both relations writes R's
+// there and S's to row grid + x (only one of a replica does).
+struct HistRows {
+    uint32_t log_nx, log_groups;  // log2 of the replicas, of the workgroups per replica
+    __host__ __device__ uint32_t nx() const { return 1u << log_nx; }
+    __host__ __device__ uint32_t groups() const { return 1u << log_groups; }
+    __host__ __device__ uint32_t grid() const { return 1u << (log_nx + log_groups); }
+    __host__ __device__ uint32_t rows() const { return grid() + nx(); }
+    // tiles of replica x below tile t
+    __host__ __device__ uint32_t tiles_of(uint32_t x, uint32_t t) const {
+        return t > x ? (t - x + nx() - 1) >> log_nx : 0u;
+    }
+    // first tile (in the replica's count) of workgroup q of a replica of `of` tiles
+    __host__ __device__ uint32_t first(uint32_t of, uint32_t q) const {
+        return (uint32_t)(((uint64_t)of * q) >> log_groups);
+    }
 };
-// Column groups of 16-count columns per row for workgroups of `block` threads.
-__host__ __device__ inline uint32_t count_sum_groups(uint32_t bits, uint32_t block) {
-    const uint32_t cols = (1u << bits) / 16;
-    return cols > block ? cols / block : 1u;
+// At most one workgroup per tile; fewer at many counters, whose rows the next
+// launch sums.
+inline HistRows hist_rows(uint64_t tiles, uint32_t nx, uint32_t count_bits) {
+    const uint32_t cap = count_bits > 13 ? 256u : count_bits > 10 ? 512u : 1024u;
+    HistRows h{nx == 8 ? 3u : 0u, 0};
+    while (2ull * h.grid() <= cap && 2ull * h.grid() <= tiles) ++h.log_groups;
+    return h;
 }
-// About 32 workgroups in all: each adds its sums with atomics, and the pass-1
-// scatter they run beside leaves them time for many rows; 8 rows at least.
-inline CountSums make_count_sums(const uint8_t* rows, const uint32_t* esc, uint32_t* tot, uint32_t nt_r,
-                                 uint32_t nt_s, uint32_t bits, uint32_t block) {
-    const uint64_t want = ((uint64_t)(nt_r + nt_s) * count_sum_groups(bits, block) + 31) / 32;
-    return CountSums{rows, esc, tot, nt_r, nt_s, bits, want > 8 ? (uint32_t)want : 8u};
+// Small joins: the histogram writes one row per tile and every workgroup of the
+// scatter sums the rows itself, which saves the launch that makes the starts.
+// The rows (kSelfWords words at most) are read by every scatter workgroup.
+constexpr uint32_t kSelfBits = 8;
+constexpr uint32_t kSelfWords = 16384;
+inline bool self_starts(uint64_t tiles, uint32_t bits) {
+    return bits <= kSelfBits && (tiles << bits) <= kSelfWords;
 }
-// Workgroups of the sums, rounded up to a multiple of 8 (the scatter's tiles
-// keep their XCD mapping behind them; the extra ones have no rows).
-inline uint32_t count_sum_blocks(const CountSums& c, uint32_t block) {
-    const uint32_t b = count_sum_groups(c.bits, block) *
-                       ((c.nt_r + c.rows_per - 1) / c.rows_per + (c.nt_s + c.rows_per - 1) / c.rows_per);
-    return (b + 7) / 8 * 8;
-}
-// Pass 1 of a join: R and S are its two segments (tiles numbered R first).
-// The pass-1 histogram takes them from here, as plain launch arguments, and
-// its first workgroup writes what later launches read from memory: the two
-// segment descriptors (segs[0..1]), tile_begin[0..2] = {0, nt_r, nt_r + nt_s},
-// and zero[0..nzero) cleared (the join's scan states).
+
+// The input of a join's first pass and what its histogram leaves for later
+// launches.  R's tiles are numbered first; all positions are those of the
+// partitioned copies (R's tuples, then S's).
 struct Pass1 {
     const int32_t* rk;
     const int32_t* rr;
     const int32_t* sk;
     const int32_t* sr;
     uint32_t n_r, n_s;
-    uint32_t nt_r, ntiles;
-    uint64_t hist_s;  // first histogram entry of S: nt_r << bits
-    PartSeg* segs;
-    uint32_t* tile_begin;
-    uint64_t* zero;
+    uint32_t nt_r, ntiles;  // tiles of R, of both
+    uint32_t self;          // self_starts: rows per tile
+    uint32_t fine_bits;     // bits of pass 2 when pass 1 counts its partitions too, else 0
+    HistRows h;
+    uint32_t* rows;         // [h.rows() (self: ntiles)][2^(bits + fine_bits)] counts
+    uint32_t* rows1;        // fine_bits: [h.rows()][2^bits] the same per pass-1 partition
+    uint64_t* zero;         // words the histogram clears for later launches
     uint64_t nzero;
-    uint64_t* err_clear;  // the call's error word, cleared with the scan states (or nullptr)
-    // counted pass 2: rows[tile * 2^bits_all + i] = tuples of the tile in final
-    // partition i = hash & (2^bits_all - 1), esc[tile * kCountEsc + k] its
-    // escapes (rows == nullptr: no counting)
-    uint8_t* rows;
-    uint32_t* esc;
-    uint32_t bits_all;
-    uint32_t pad;
+    uint64_t* err_clear;    // the call's error word, cleared too (or nullptr)
 };
+// What the starts launch makes of the rows.
+struct StartArgs {
+    uint32_t* cur1;         // [rel][x][p]: first free position of replica x in pass-1 partition p
+    uint32_t* start1;       // [2 << bits, + 1] partition starts of pass 1
+    uint32_t* cnt2;         // fine_bits: tuples per final partition,
+    uint32_t* start2;       //   and their starts
+    uint64_t* state1;       // scan states (start_state_words; cleared by the histogram)
+    uint64_t* state2;
+    uint32_t* big;          // set when an R partition has more than lds_cap tuples (cleared by the histogram)
+    const PartPair* r_pairs;  // R's partitions come from a built table (then n_r == 0 here)
+    uint32_t lds_cap;       // (npart == 0: the final partitions are not known yet)
+    uint32_t npart;
+    ScanCtl ctl;
+};
+constexpr uint32_t kStartCols = 64;  // partitions per workgroup of the starts launch
+inline size_t start_state_words(uint64_t partitions) { return 1 + (2 * partitions + kStartCols - 1) / kStartCols; }
+
 Pass1 make_pass1(const int32_t* rk, const int32_t* rr, uint32_t n_r, const int32_t* sk, const int32_t* sr,
-                 uint32_t n_s, uint32_t tile, uint32_t bits, PartSeg* segs, uint32_t* tile_begin, uint64_t* zero,
-                 uint64_t nzero, uint64_t* err_clear);
-// Pass-1 histogram (and the pass's set-up, see Pass1).
-void part_hist_pass1(const Pass1& p1, const PassCfg& cfg, uint32_t* hist, Recorder& rec);
-// Histogram of a later pass over the segments in memory; tile_seg: segment of
-// every tile (nullptr: binary search over tile_begin).
-void part_hist(const PartSeg* segs, const uint32_t* tile_begin, const uint32_t* tile_seg, uint32_t nseg,
-               uint32_t grid, const PassCfg& cfg, uint32_t* hist, Recorder& rec);
-// Partition boundaries of a one-segment pass (R only, segment at position 0):
-// starts[p] for p < 2^bits from the pass's histogram scan, starts[2^bits] = n.
-void part_starts(const uint32_t* hist_scan, uint32_t ntiles, uint32_t bits, uint32_t n, uint32_t* starts,
-                 Recorder& rec);
+                 uint32_t n_s, uint32_t tile);
+// Histogram of the input into rows.
+void part_hist(const Pass1& p1, const PassCfg& cfg, Recorder& rec);
+// Partition starts and cursors from the rows.
+void part_starts(const Pass1& p1, const PassCfg& cfg, const StartArgs& st, Recorder& rec);
+// Histogram of a second pass over the tuples `in` of the segments, into
+// cnt2[seg << bits | p] (zero before).
+void part_hist2(const Tuple* in, const PartSeg* segs, const uint32_t* tile_begin, const uint32_t* tile_seg,
+                uint32_t nseg, uint32_t grid, const PassCfg& cfg, uint32_t* cnt2, Recorder& rec);
+// HBM tables a scatter clears (two slots per R tuple at twice its position):
+// those of R's partitions of more than lds_cap tuples, when *big is set
+// (self_starts: the scatter's workgroups see for themselves).
+struct ClearTables {
+    uint64_t* table;          // nullptr: nothing to clear
+    const uint32_t* big;
+    const uint32_t* start;    // starts of R's npart partitions (positions in R), [npart] = n_r
+    const PartPair* r_pairs;  // instead of start, for a built table
+    uint32_t npart, n_r, lds_cap;
+};
 // `side`: extra workgroups appended to the grid that run the next step's setup
 // (hj_side.h: the pass-2 segment table or the join plan).
 struct SideJob;
-// rsv (counted pass 2): offsets from the totals and cursors instead of hist_scan.
-void part_scatter(const PartSeg* segs, const uint32_t* tile_begin, const uint32_t* tile_seg, uint32_t nseg,
-                  uint32_t grid, const PassCfg& cfg, const uint32_t* hist_scan, int32_t* key_out,
-                  int32_t* rid_out, const SideJob& side, Recorder& rec, const Reserve* rsv = nullptr);
+// First pass: the input's tuples to `out`, or to two columns (key_out, rid_out)
+// when out is nullptr.
+// cur1: the starts launch's cursors (self_starts: unused).
+void part_scatter(const Pass1& p1, const PassCfg& cfg, uint32_t* cur1, Tuple* out, int32_t* key_out,
+                  int32_t* rid_out, const ClearTables& clr, const SideJob& side, Recorder& rec);
+// Second pass over segments of `in`: partition p of segment s starts at
+// start2[s << bits | p], cnt2 holds its tuples and is counted down.
+void part_scatter2(const Tuple* in, const PartSeg* segs, const uint32_t* tile_begin, const uint32_t* tile_seg,
+                   uint32_t nseg, uint32_t grid, const PassCfg& cfg, const uint32_t* start2, uint32_t* cnt2,
+                   Tuple* out, const ClearTables& clr, const SideJob& side, Recorder& rec);
 
 // ---- phj_join.hip ----
 constexpr uint32_t kJoinBlock = 512;
@@ -303,13 +346,6 @@ constexpr uint32_t kRptSmall = 4, kRptMid = 9, kRptLarge = kMaxLdsCap / kJoinBlo
 inline uint32_t join_rpt(uint32_t lds_cap) {
     return lds_cap <= kRptSmall * kJoinBlock ? kRptSmall : (lds_cap <= kRptMid * kJoinBlock ? kRptMid : kRptLarge);
 }
-struct JoinPlanOut {
-    PartPair* pairs;       // [P]
-    uint32_t* item_begin;  // [P + 1] exclusive scan of work items per partition
-    uint32_t* ovf_begin;   // [P + 1] exclusive scan of HBM-table build chunks per partition
-    ItemRec* item_rec;     // [join_grid] every work item's R range and S chunk
-    uint32_t* ovf_part;    // [ovf_grid] partition of every HBM-table build chunk
-};
 // The join plan (final partition table, work-item and overflow-chunk scans and
 // maps) runs as a side job of the last scatter (hj_side.h); its state needs
 // plan_state_words(2^total_bits) words that are zero when it starts.
@@ -320,24 +356,21 @@ uint32_t join_grid(uint32_t P, uint64_t n_s);  // (a multiple of 8 kItemGroup)
 constexpr uint32_t kItemGroup = 16;  // consecutive join items dealt to one XCD
 // Dynamic LDS bytes of the join kernels for a given lds_cap.
 size_t join_lds_bytes(uint32_t lds_cap, bool write);
-size_t part_scatter_lds_bytes(uint32_t bits, uint32_t tile);
+// rt, st: partitioned R and S.
 // hot: where the build records its hot keys (zeroed before); heavy: the
 // one-pass queue (nullptr for count -> scan -> write), whose `wait` it sets.
-// clear == false: the tables were cleared by the last scatter (Reserve::ovf_table).
+// clear == false: the tables were cleared by the last scatter (ClearTables).
 void join_ovf_build(const PartPair* pairs, const uint32_t* ovf_begin, const uint32_t* ovf_part, uint32_t P,
-                    uint32_t grid, const int32_t* rk, uint64_t* ovf_table, uint32_t* ovf_next, HotKeys* hot,
-                    HeavyQueue* heavy, Recorder& rec, bool clear = true);
-// item_begin/item_rec come from the join plan (JoinPlanOut).
-void join_count(const PartPair* pairs, const uint32_t* item_begin, const ItemRec* item_rec, uint32_t P,
-                uint32_t grid,
-                const int32_t* rk, const int32_t* sk, uint32_t lds_cap, const uint64_t* ovf_table,
-                const uint32_t* ovf_next, const HotKeys* hot, uint64_t* wave_cnt, bool nt_s, Recorder& rec);
-void join_write(const PartPair* pairs, const uint32_t* item_begin, const ItemRec* item_rec, uint32_t P,
-                uint32_t grid,
-                const int32_t* rk, const int32_t* rr, const int32_t* sk, const int32_t* sr,
-                uint32_t lds_cap, const uint64_t* ovf_table, const uint32_t* ovf_next,
-                const uint64_t* wave_base, uint64_t* total, int32_t* out_r, int32_t* out_s,
-                const HotKeys* hot, uint64_t capacity, HeavyQueue* heavy, bool nt_s, Recorder& rec);
+                    uint32_t grid, const Tuple* rt, uint64_t* ovf_table, uint32_t* ovf_next, HotKeys* hot,
+                    HeavyQueue* heavy, Recorder& rec, bool clear);
+// item_rec comes from the join plan; grid: join_grid.
+void join_count(const ItemRec* item_rec, uint32_t grid, const Tuple* rt, const Tuple* st, uint32_t lds_cap,
+                const uint64_t* ovf_table, const uint32_t* ovf_next, const HotKeys* hot, uint64_t* wave_cnt, bool nt_s,
+                Recorder& rec);
+void join_write(const ItemRec* item_rec, uint32_t grid, const Tuple* rt, const Tuple* st, uint32_t lds_cap,
+                const uint64_t* ovf_table, const uint32_t* ovf_next, const HotKeys* hot, const uint64_t* wave_base,
+                uint64_t* total, int32_t* out_r, int32_t* out_s, uint64_t capacity, HeavyQueue* heavy, bool nt_s,
+                Recorder& rec);
 // nt_s: S chunks read with non-temporal loads (LDS-table items).
 // wave_base == nullptr selects the one-pass write: `total` must be zero on entry
 // and ends as the number of pairs; `heavy` (one-pass only, zeroed before the

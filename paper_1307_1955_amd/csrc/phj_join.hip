@@ -64,7 +64,7 @@ struct RegionStep {
 __global__ void __launch_bounds__(256) k_ovf_build(const PartPair* __restrict__ pairs,
                                                   const uint32_t* __restrict__ ovf_begin,
                                                   const uint32_t* __restrict__ ovf_part, uint32_t P,
-                                                  const int32_t* __restrict__ rk,
+                                                  const Tuple* __restrict__ rt,
                                                   uint64_t* __restrict__ ovf_table,
                                                   uint32_t* __restrict__ ovf_next, HotKeys* hot,
                                                   HeavyQueue* heavy) {
@@ -93,7 +93,7 @@ __global__ void __launch_bounds__(256) k_ovf_build(const PartPair* __restrict__ 
             int32_t k = 0;
             uint64_t s = kClaimed;
             if (j < end) {
-                k = rk[pp.r_off + j];
+                k = key_of(rt[pp.r_off + j]);
                 s = push.hot(k) ? push.hot_slot : chain_claim(region, region_slot(k, step.H), k, j, step);
             }
             push.add(region, next, s, k, j);
@@ -113,8 +113,23 @@ __device__ __forceinline__ uint32_t table_log2H(uint32_t n) {
     return 31u - (uint32_t)__clz(v);
 }
 
+// Strided columns of the heavy-key scans (hj_heavy.h) over partitioned tuples.
+typedef Column<2> TupleColumn;
+__device__ __forceinline__ TupleColumn key_column(const Tuple* t) { return TupleColumn{reinterpret_cast<const int32_t*>(t)}; }
+__device__ __forceinline__ TupleColumn rid_column(const Tuple* t) { return TupleColumn{reinterpret_cast<const int32_t*>(t) + 1}; }
+
 // R_i's keys of this thread, n <= RPT * kJoinBlock.  Plain loads: every S
-// chunk (work item) of a partition reads R_i again.
+// chunk (work item) of a partition reads R_i again, and the rids of its
+// matches come from the same lines.
+template <uint32_t RPT>
+__device__ __forceinline__ void load_r(const Tuple* __restrict__ rt, uint32_t n, int32_t* k) {
+#pragma unroll
+    for (uint32_t u = 0; u < RPT; ++u) {
+        const uint32_t j = u * kJoinBlock + threadIdx.x;
+        k[u] = j < n ? key_of(rt[j]) : 0;
+    }
+}
+// The same from a key column (direct joins).
 template <uint32_t RPT>
 __device__ __forceinline__ void load_r(const int32_t* __restrict__ rk, uint32_t n, int32_t* k) {
 #pragma unroll
@@ -202,16 +217,27 @@ __device__ __forceinline__ ItemLoc locate_item(const ItemRec* __restrict__ item_
     return L;
 }
 
-// S keys (and rids) of this lane for the wave's range [wb, we) of the item
+// S keys and rids of this lane for the wave's range [wb, we) of the item
 // (kNt: non-temporal loads, for large joins; see kNtMinTuples).
-template <bool kRids, bool kNt = false>
-__device__ __forceinline__ void load_s(const int32_t* __restrict__ skp, const int32_t* __restrict__ srp,
-                                       uint32_t wb, uint32_t we, int32_t* q, int32_t* qr) {
+template <bool kNt>
+__device__ __forceinline__ void load_s(const Tuple* __restrict__ st, uint32_t wb, uint32_t we, int32_t* q,
+                                       int32_t* qr) {
 #pragma unroll
     for (uint32_t u = 0; u < kSU; ++u) {
         const uint32_t j = wb + u * kWave + lane_id();
-        q[u] = j < we ? (kNt ? __builtin_nontemporal_load(skp + j) : skp[j]) : 0;
-        if (kRids) qr[u] = j < we ? (kNt ? __builtin_nontemporal_load(srp + j) : srp[j]) : 0;
+        const uint64_t t = j < we ? (kNt ? __builtin_nontemporal_load(st + j) : st[j]) : 0ull;
+        q[u] = key_of(t);
+        qr[u] = rid_of(t);
+    }
+}
+// The same from two columns (direct joins).
+__device__ __forceinline__ void load_s(const int32_t* __restrict__ skp, const int32_t* __restrict__ srp, uint32_t wb,
+                                       uint32_t we, int32_t* q, int32_t* qr) {
+#pragma unroll
+    for (uint32_t u = 0; u < kSU; ++u) {
+        const uint32_t j = wb + u * kWave + lane_id();
+        q[u] = j < we ? skp[j] : 0;
+        qr[u] = j < we ? srp[j] : 0;
     }
 }
 
@@ -291,7 +317,8 @@ __device__ __forceinline__ void probe_hbm(const uint64_t* __restrict__ region, c
 // and the capacity left there).  The first match is at row `first` and its
 // rid, rid0, was fetched already; further matches follow the chain and read
 // their rids from R_i's rid column `rrp`.
-__device__ __forceinline__ void write_lds_matches(const LdsView& v, const int32_t* __restrict__ rrp, int32_t key,
+template <typename Rids>
+__device__ __forceinline__ void write_lds_matches(const LdsView& v, Rids rrp, int32_t key,
                                                   int32_t rs, uint32_t first, int32_t rid0, uint32_t c, uint32_t p,
                                                   uint32_t room, int32_t* __restrict__ o_r,
                                                   int32_t* __restrict__ o_s) {
@@ -356,7 +383,8 @@ __device__ __forceinline__ uint32_t lane_pairs_lds(const uint32_t* cf) {
 // by match counts); returns the slot after the wave's last pair.  LDS table.
 // A round of a wave has fewer than 2^32 pairs (kSubJ keys x kMaxLdsCap
 // matches), so slots are 32-bit offsets from the wave's uniform base.
-__device__ __forceinline__ uint64_t write_round_lds(const LdsView& v, const int32_t* __restrict__ rrp,
+template <typename Rids>
+__device__ __forceinline__ uint64_t write_round_lds(const LdsView& v, Rids rrp,
                                                     const int32_t* q, const int32_t* qr, const uint32_t* cf,
                                                     const int32_t* rid0, uint64_t pos0, uint64_t capacity,
                                                     int32_t* __restrict__ out_r, int32_t* __restrict__ out_s) {
@@ -379,7 +407,8 @@ __device__ __forceinline__ uint64_t write_round_lds(const LdsView& v, const int3
 
 // Rids of the first matches (issued right after the probe, so the loads are in
 // flight during the output reservation).
-__device__ __forceinline__ void fetch_first_rids(const int32_t* __restrict__ rrp, const uint32_t* cf, int32_t* rid0) {
+template <typename Rids>
+__device__ __forceinline__ void fetch_first_rids(Rids rrp, const uint32_t* cf, int32_t* rid0) {
 #pragma unroll
     for (uint32_t u = 0; u < kSU; ++u) rid0[u] = (cf[u] & 0xFFFFu) ? rrp[cf[u] >> 16] : 0;
 }
@@ -389,7 +418,7 @@ __device__ __forceinline__ void fetch_first_rids(const int32_t* __restrict__ rrp
 // Heavy entries (is_heavy(c[u])) take their count from hs and only publish
 // their first slot in hs->pos; heavy_writes writes them.
 __device__ __forceinline__ uint64_t write_round_hbm(const uint32_t* __restrict__ next,
-                                                    const int32_t* __restrict__ rrp, const int32_t* qr,
+                                                    TupleColumn rrp, const int32_t* qr,
                                                     const uint32_t* c, const uint32_t* at,
                                                     HeavySet* hs, uint64_t pos0, uint64_t capacity,
                                                     int32_t* __restrict__ out_r, int32_t* __restrict__ out_s) {
@@ -424,24 +453,24 @@ __device__ __forceinline__ uint64_t write_round_hbm(const uint32_t* __restrict__
 // partition-local HBM table and returns this lane's pair count.  hs takes the
 // LDS the table would have used.  Inlined: a call would give the kernel a
 // stack, and the LDS path measured a few percent slower with one.
-__device__ __forceinline__ uint64_t join_count_hbm(const ItemLoc L, uint32_t w, const int32_t* __restrict__ rk,
-                                                   const int32_t* __restrict__ skp,
+__device__ __forceinline__ uint64_t join_count_hbm(const ItemLoc L, uint32_t w, const Tuple* __restrict__ rt,
+                                                   const Tuple* __restrict__ stp,
                                                    const uint64_t* __restrict__ ovf_table,
                                                    const uint32_t* __restrict__ ovf_next, const HotKeys* hot,
                                                    HbmLds* sh) {
     HeavySet* hs = &sh->hs;
     uint64_t cnt = 0;
-    int32_t q[kSU];
+    int32_t q[kSU], qr[kSU];
     load_hot(hot, sh->hk, sh->hr, &sh->nhk);  // read after the round's barrier
     for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
         const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-        load_s<false>(skp, nullptr, wb, we, q, nullptr);
+        load_s<false>(stp, wb, we, q, qr);
         if (threadIdx.x == 0) hs->n = 0;
         __syncthreads();
         uint32_t c[kSU], at[kSU];
         probe_hbm(ovf_table + 2ull * L.r_off, ovf_next + L.r_off, 2u * L.r_len, heavy_limit(L.r_len), q, nullptr, wb,
                   we, c, at, sh);
-        heavy_counts<kJoinBlock, kHeavyV>(rk + L.r_off, L.r_len, hs);
+        heavy_counts<kJoinBlock, kHeavyV>(key_column(rt + L.r_off), L.r_len, hs);
 #pragma unroll
         for (uint32_t u = 0; u < kSU; ++u) cnt += is_heavy(c[u]) ? hs->cnt[c[u] & ~kHeavyBit] : c[u];
         __syncthreads();  // the set is reused by the next round
@@ -450,11 +479,9 @@ __device__ __forceinline__ uint64_t join_count_hbm(const ItemLoc L, uint32_t w, 
 }
 
 template <uint32_t RPT, bool kNt>
-__global__ void __launch_bounds__(kJoinBlock) k_join_count(const PartPair* __restrict__ pairs,
-                                                          const uint32_t* __restrict__ item_begin,
-                                                          const ItemRec* __restrict__ item_rec,
-                                                          uint32_t P, const int32_t* __restrict__ rk,
-                                                          const int32_t* __restrict__ sk, uint32_t lds_cap,
+__global__ void __launch_bounds__(kJoinBlock) k_join_count(const ItemRec* __restrict__ item_rec,
+                                                          const Tuple* __restrict__ rt,
+                                                          const Tuple* __restrict__ st, uint32_t lds_cap,
                                                           const uint64_t* __restrict__ ovf_table,
                                                           const uint32_t* __restrict__ ovf_next,
                                                           const HotKeys* __restrict__ hot,
@@ -467,25 +494,25 @@ __global__ void __launch_bounds__(kJoinBlock) k_join_count(const PartPair* __res
         if (lane == 0) wave_cnt[(uint64_t)L.item * kJoinWaves + w] = 0;
         return;
     }
-    const int32_t* __restrict__ skp = sk + L.s_begin;
+    const Tuple* __restrict__ stp = st + L.s_begin;
     uint64_t cnt = 0;
-    int32_t q[kSU];
+    int32_t q[kSU], qr[kSU];
     if (L.r_len <= lds_cap) {
         int32_t k[RPT];
-        load_r<RPT>(rk + L.r_off, L.r_len, k);
-        load_s<false, kNt>(skp, nullptr, w * kSubJ, min(w * kSubJ + kSubJ, L.s_n), q, nullptr);
+        load_r<RPT>(rt + L.r_off, L.r_len, k);
+        load_s<kNt>(stp, w * kSubJ, min(w * kSubJ + kSubJ, L.s_n), q, qr);
         const LdsView v = lds_view(lds, lds_cap);
         const uint32_t log2H = table_log2H(L.r_len);
         build_lds<RPT>(k, L.r_len, log2H, v);
         for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
             const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-            if (sb) load_s<false, kNt>(skp, nullptr, wb, we, q, nullptr);
+            if (sb) load_s<kNt>(stp, wb, we, q, qr);
             uint32_t cf[kSU];
             probe_lds(v, log2H, q, wb, we, cf);
             cnt += lane_pairs_lds(cf);
         }
     } else {
-        cnt = join_count_hbm(L, w, rk, skp, ovf_table, ovf_next, hot, reinterpret_cast<HbmLds*>(lds));
+        cnt = join_count_hbm(L, w, rt, stp, ovf_table, ovf_next, hot, reinterpret_cast<HbmLds*>(lds));
     }
     cnt = wave_sum(cnt);
     if (lane == 0) wave_cnt[(uint64_t)L.item * kJoinWaves + w] = cnt;
@@ -500,33 +527,34 @@ __global__ void __launch_bounds__(kJoinBlock) k_join_count(const PartPair* __res
 // workgroup's own scans.
 template <bool kOnePass>
 __device__ __forceinline__ void join_write_hbm(
-    const ItemLoc L, uint32_t w, const int32_t* __restrict__ rk, const int32_t* __restrict__ rrp,
-    const int32_t* __restrict__ skp, const int32_t* __restrict__ srp, const uint64_t* __restrict__ ovf_table,
+    const ItemLoc L, uint32_t w, const Tuple* __restrict__ rt, const Tuple* __restrict__ stp,
+    const uint64_t* __restrict__ ovf_table,
     const uint32_t* __restrict__ ovf_next, const HotKeys* hot, uint64_t base, unsigned long long* __restrict__ total,
     uint64_t* wtot, int32_t* __restrict__ out_r, int32_t* __restrict__ out_s, uint64_t capacity, HbmLds* sh,
     HeavyQueue* heavy) {
     HeavySet* hs = &sh->hs;
     const uint64_t* __restrict__ region = ovf_table + 2ull * L.r_off;
     const uint32_t* __restrict__ next = ovf_next + L.r_off;
+    const TupleColumn rkp = key_column(rt + L.r_off), rrp = rid_column(rt + L.r_off);
     const bool queue = kOnePass && heavy && L.r_len > kHelpChunk;  // uniform
     const uint32_t lim = queue ? min(heavy_limit(L.r_len), kQueueWalk) : heavy_limit(L.r_len);
     int32_t q[kSU], qr[kSU];
     load_hot(hot, sh->hk, sh->hr, &sh->nhk);  // read after the round's barrier
     for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
         const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-        load_s<true>(skp, srp, wb, we, q, qr);
+        load_s<false>(stp, wb, we, q, qr);
         if (threadIdx.x == 0) hs->n = hs->queued = 0;
         __syncthreads();
         uint32_t c[kSU], at[kSU];
         probe_hbm(region, next, 2u * L.r_len, lim, q, qr, wb, we, c, at, sh);
         if (queue) hand_off(heavy, hs, L.r_off, L.r_len);
-        heavy_counts<kJoinBlock, kHeavyV, kOnePass>(rk + L.r_off, L.r_len, hs);
+        heavy_counts<kJoinBlock, kHeavyV, kOnePass>(rkp, L.r_len, hs);
         uint64_t mine = 0;
 #pragma unroll
         for (uint32_t u = 0; u < kSU; ++u) mine += is_heavy(c[u]) ? hs->cnt[c[u] & ~kHeavyBit] : c[u];
         const uint64_t pos0 = kOnePass ? block_reserve(mine, total, wtot, sb != 0) : base;
         base = write_round_hbm(next, rrp, qr, c, at, hs, pos0, capacity, out_r, out_s);
-        heavy_writes<kJoinBlock, kHeavyV>(rk + L.r_off, rrp, L.r_len, hs, capacity, out_r, out_s);
+        heavy_writes<kJoinBlock, kHeavyV>(rkp, rrp, L.r_len, hs, capacity, out_r, out_s);
         __syncthreads();  // the set is reused by the next round
     }
 }
@@ -534,27 +562,25 @@ __device__ __forceinline__ void join_write_hbm(
 // The pairs of one work item (R_i in an LDS table, or its HBM table).
 template <bool kOnePass, uint32_t RPT, bool kNt>
 __device__ __forceinline__ void write_item(const ItemLoc L, uint32_t w, uint32_t* lds, uint64_t* wtot,
-                                           const int32_t* __restrict__ rk, const int32_t* __restrict__ rr,
-                                           const int32_t* __restrict__ sk, const int32_t* __restrict__ sr,
+                                           const Tuple* __restrict__ rt, const Tuple* __restrict__ st,
                                            uint32_t lds_cap, const uint64_t* __restrict__ ovf_table,
                                            const uint32_t* __restrict__ ovf_next, const HotKeys* hot,
                                            uint64_t base, unsigned long long* __restrict__ total,
                                            int32_t* __restrict__ out_r, int32_t* __restrict__ out_s,
                                            uint64_t capacity, HeavyQueue* heavy) {
-    const int32_t* __restrict__ rrp = rr + L.r_off;
-    const int32_t* __restrict__ skp = sk + L.s_begin;
-    const int32_t* __restrict__ srp = sr + L.s_begin;
+    const Tuple* __restrict__ stp = st + L.s_begin;
     int32_t q[kSU], qr[kSU];
     if (L.r_len <= lds_cap) {
+        const TupleColumn rrp = rid_column(rt + L.r_off);
         int32_t k[RPT];
-        load_r<RPT>(rk + L.r_off, L.r_len, k);
-        load_s<true, kNt>(skp, srp, w * kSubJ, min(w * kSubJ + kSubJ, L.s_n), q, qr);
+        load_r<RPT>(rt + L.r_off, L.r_len, k);
+        load_s<kNt>(stp, w * kSubJ, min(w * kSubJ + kSubJ, L.s_n), q, qr);
         const LdsView v = lds_view(lds, lds_cap);
         const uint32_t log2H = table_log2H(L.r_len);
         build_lds<RPT>(k, L.r_len, log2H, v);
         for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
             const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-            if (sb) load_s<true, kNt>(skp, srp, wb, we, q, qr);
+            if (sb) load_s<kNt>(stp, wb, we, q, qr);
             uint32_t cf[kSU];
             int32_t rid0[kSU];
             probe_lds(v, log2H, q, wb, we, cf);
@@ -563,8 +589,8 @@ __device__ __forceinline__ void write_item(const ItemLoc L, uint32_t w, uint32_t
             base = write_round_lds(v, rrp, q, qr, cf, rid0, pos0, capacity, out_r, out_s);
         }
     } else {
-        join_write_hbm<kOnePass>(L, w, rk, rrp, skp, srp, ovf_table, ovf_next, hot, base, total, wtot, out_r,
-                                 out_s, capacity, reinterpret_cast<HbmLds*>(lds), heavy);
+        join_write_hbm<kOnePass>(L, w, rt, stp, ovf_table, ovf_next, hot, base, total, wtot, out_r, out_s, capacity,
+                                 reinterpret_cast<HbmLds*>(lds), heavy);
     }
 }
 
@@ -577,7 +603,7 @@ constexpr uint32_t kMaxHelpers = 256;
 // A helper's loop: help with the queued tuples until the items the build
 // counted are done.  Not inlined: inside the write kernel its registers cost
 // the item path 6-10 us at 16M x 16M (measured), while as a call they do not.
-__device__ __attribute__((noinline)) void help_until_done(HeavyQueue* heavy, const int32_t* rk, const int32_t* rr,
+__device__ __attribute__((noinline)) void help_until_done(HeavyQueue* heavy, const Tuple* rt,
                                                          unsigned long long* total, uint64_t capacity, int32_t* out_r,
                                                          int32_t* out_s, uint32_t* lds, uint32_t* s_word) {
     const uint32_t expected = heavy->items_expected;
@@ -587,7 +613,7 @@ __device__ __attribute__((noinline)) void help_until_done(HeavyQueue* heavy, con
             *s_word = __hip_atomic_load(&heavy->items_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         const bool all_done = *s_word >= expected;
-        help_heavy<kJoinBlock>(heavy, rk, rr, total, capacity, out_r, out_s, lds);
+        help_heavy<kJoinBlock>(heavy, key_column(rt), rid_column(rt), total, capacity, out_r, out_s, lds);
         if (all_done || polls >= kHelpWaitPolls) break;
         __builtin_amdgcn_s_sleep(32);
     }
@@ -608,10 +634,7 @@ __device__ __attribute__((noinline)) void help_until_done(HeavyQueue* heavy, con
 template <bool kOnePass, uint32_t RPT, bool kNt>
 __global__ void __launch_bounds__(kJoinBlock) __attribute__((amdgpu_waves_per_eu(RPT > kRptMid ? 4 : 6)))
 k_join_write(
-    const PartPair* __restrict__ pairs, const uint32_t* __restrict__ item_begin,
-    const ItemRec* __restrict__ item_rec, uint32_t P, const int32_t* __restrict__ rk,
-    const int32_t* __restrict__ rr, const int32_t* __restrict__ sk, const int32_t* __restrict__ sr,
-    uint32_t lds_cap, const uint64_t* __restrict__ ovf_table,
+    const ItemRec* __restrict__ item_rec, const Tuple* __restrict__ rt, const Tuple* __restrict__ st, uint32_t lds_cap, const uint64_t* __restrict__ ovf_table,
     const uint32_t* __restrict__ ovf_next, const HotKeys* __restrict__ hot, const uint64_t* __restrict__ wave_base,
     unsigned long long* __restrict__ total, int32_t* __restrict__ out_r, int32_t* __restrict__ out_s,
     uint64_t capacity, HeavyQueue* heavy, uint32_t item_grid) {
@@ -621,15 +644,15 @@ k_join_write(
     const uint32_t w = threadIdx.x / kWave;
     if (kOnePass && heavy && blockIdx.x >= item_grid) {  // a helper
         if (!heavy->wait) return;  // written by an earlier launch: uniform
-        help_until_done(heavy, rk, rr, total, capacity, out_r, out_s, lds, &s_word);
+        help_until_done(heavy, rt, total, capacity, out_r, out_s, lds, &s_word);
         return;
     }
     const ItemLoc L = locate_item(item_rec);
     if (!L.live) return;
     const uint32_t item = L.item;
     const uint64_t base = kOnePass ? 0ull : wave_base[(uint64_t)item * kJoinWaves + w];
-    write_item<kOnePass, RPT, kNt>(L, w, lds, wtot, rk, rr, sk, sr, lds_cap, ovf_table, ovf_next, hot, base, total,
-                              out_r, out_s, capacity, heavy);
+    write_item<kOnePass, RPT, kNt>(L, w, lds, wtot, rt, st, lds_cap, ovf_table, ovf_next, hot, base, total, out_r, out_s,
+                                   capacity, heavy);
     // one-pass: help with the heavy tuples any workgroup queued (the LDS
     // tables are free now and give the scratch)
     if (kOnePass && heavy) {
@@ -637,7 +660,7 @@ k_join_write(
             __syncthreads();  // the item's hand-offs are made
             if (threadIdx.x == 0) atomicAdd(&heavy->items_done, 1u);
         }
-        help_heavy<kJoinBlock>(heavy, rk, rr, total, capacity, out_r, out_s, lds);
+        help_heavy<kJoinBlock>(heavy, key_column(rt), rid_column(rt), total, capacity, out_r, out_s, lds);
     }
 }
 
@@ -660,22 +683,23 @@ k_direct_join(const DirectJob* __restrict__ jobs,
     const uint32_t r_len = min(J.n_r, lds_cap);  // the planner guarantees n_r <= lds_cap
     const int32_t* __restrict__ skp = J.sk + s_begin;
     const int32_t* __restrict__ srp = J.sr + s_begin;
+    const Column<1> rids{J.rr};
     int32_t k[RPT];
     load_r<RPT>(J.rk, r_len, k);
     int32_t q[kSU], qr[kSU];
-    load_s<true>(skp, srp, w * kSubJ, min(w * kSubJ + kSubJ, s_n), q, qr);
+    load_s(skp, srp, w * kSubJ, min(w * kSubJ + kSubJ, s_n), q, qr);
     const LdsView v = lds_view(lds, lds_cap);
     const uint32_t log2H = table_log2H(r_len);
     build_lds<RPT>(k, r_len, log2H, v);
     for (uint32_t sb = 0; sb < s_n; sb += kJoinSub) {
         const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, s_n);
-        if (sb) load_s<true>(skp, srp, wb, we, q, qr);
+        if (sb) load_s(skp, srp, wb, we, q, qr);
         uint32_t cf[kSU];
         int32_t rid0[kSU];
         probe_lds(v, log2H, q, wb, we, cf);
-        fetch_first_rids(J.rr, cf, rid0);
+        fetch_first_rids(rids, cf, rid0);
         const uint64_t pos0 = block_reserve(lane_pairs_lds(cf), (unsigned long long*)J.count, wtot, sb != 0);
-        write_round_lds(v, J.rr, q, qr, cf, rid0, pos0, J.capacity, J.out_r, J.out_s);
+        write_round_lds(v, rids, q, qr, cf, rid0, pos0, J.capacity, J.out_r, J.out_s);
     }
 }
 
@@ -768,7 +792,7 @@ uint32_t join_grid(uint32_t P, uint64_t n_s) {
 }
 
 void join_ovf_build(const PartPair* pairs, const uint32_t* ovf_begin, const uint32_t* ovf_part, uint32_t P,
-                    uint32_t grid, const int32_t* rk, uint64_t* ovf_table, uint32_t* ovf_next, HotKeys* hot,
+                    uint32_t grid, const Tuple* rt, uint64_t* ovf_table, uint32_t* ovf_next, HotKeys* hot,
                     HeavyQueue* heavy, Recorder& rec, bool clear) {
     if (grid == 0) return;
     grid = grid < kOvfGrid ? grid : kOvfGrid;  // grid-stride: few chunks in the common case
@@ -779,67 +803,45 @@ void join_ovf_build(const PartPair* pairs, const uint32_t* ovf_begin, const uint
         rec.after();
     }
     rec.before("ovf_build");
-    hipLaunchKernelGGL(k_ovf_build, dim3(grid), dim3(256), 0, rec.stream, pairs, ovf_begin, ovf_part, P, rk,
+    hipLaunchKernelGGL(k_ovf_build, dim3(grid), dim3(256), 0, rec.stream, pairs, ovf_begin, ovf_part, P, rt,
                        ovf_table, ovf_next, hot, heavy);
     rec.after();
 }
 
+namespace {
+
+struct JoinArgs {
+    const ItemRec* item_rec;
+    uint32_t grid;
+    const Tuple *rt, *st;
+    uint32_t lds_cap;
+    const uint64_t* ovf_table;
+    const uint32_t* ovf_next;
+    const HotKeys* hot;
+    uint64_t* wave;   // per-wave counts (count), or their scan (write; nullptr: one-pass)
+    uint64_t* total;
+    int32_t *out_r, *out_s;
+    uint64_t capacity;
+    HeavyQueue* heavy;
+};
+
 template <uint32_t RPT, bool kNt>
-void join_count_t(const PartPair* pairs, const uint32_t* item_begin, const ItemRec* item_rec, uint32_t P,
-                  uint32_t grid, const int32_t* rk, const int32_t* sk, uint32_t lds_cap, const uint64_t* ovf_table,
-                  const uint32_t* ovf_next, const HotKeys* hot, uint64_t* wave_cnt, Recorder& rec) {
-    const size_t lds = join_lds_bytes(lds_cap, false);
+void join_count_t(const JoinArgs& a, Recorder& rec) {
+    const size_t lds = join_lds_bytes(a.lds_cap, false);
     allow_lds((const void*)k_join_count<RPT, kNt>, lds);
     rec.before("join_count");
-    hipLaunchKernelGGL((k_join_count<RPT, kNt>), dim3(grid), dim3(kJoinBlock), lds, rec.stream, pairs, item_begin,
-                       item_rec, P, rk, sk, lds_cap, ovf_table, ovf_next, hot, wave_cnt);
+    hipLaunchKernelGGL((k_join_count<RPT, kNt>), dim3(a.grid), dim3(kJoinBlock), lds, rec.stream, a.item_rec, a.rt,
+                       a.st, a.lds_cap, a.ovf_table, a.ovf_next, a.hot, a.wave);
     rec.after();
 }
 
-template <bool kNt>
-void join_count_n(const PartPair* pairs, const uint32_t* item_begin, const ItemRec* item_rec, uint32_t P,
-                  uint32_t grid, const int32_t* rk, const int32_t* sk, uint32_t lds_cap, const uint64_t* ovf_table,
-                  const uint32_t* ovf_next, const HotKeys* hot, uint64_t* wave_cnt, Recorder& rec) {
-    switch (join_rpt(lds_cap)) {
-        case kRptSmall:
-            join_count_t<kRptSmall, kNt>(pairs, item_begin, item_rec, P, grid, rk, sk, lds_cap, ovf_table, ovf_next,
-                                         hot, wave_cnt, rec);
-            break;
-        case kRptMid:
-            join_count_t<kRptMid, kNt>(pairs, item_begin, item_rec, P, grid, rk, sk, lds_cap, ovf_table, ovf_next,
-                                       hot, wave_cnt, rec);
-            break;
-        default:
-            join_count_t<kRptLarge, kNt>(pairs, item_begin, item_rec, P, grid, rk, sk, lds_cap, ovf_table, ovf_next,
-                                         hot, wave_cnt, rec);
-            break;
-    }
-}
-
-void join_count(const PartPair* pairs, const uint32_t* item_begin, const ItemRec* item_rec, uint32_t P,
-                uint32_t grid,
-                const int32_t* rk, const int32_t* sk, uint32_t lds_cap, const uint64_t* ovf_table,
-                const uint32_t* ovf_next, const HotKeys* hot, uint64_t* wave_cnt, bool nt_s, Recorder& rec) {
-    if (grid == 0) return;
-    if (nt_s)
-        join_count_n<true>(pairs, item_begin, item_rec, P, grid, rk, sk, lds_cap, ovf_table, ovf_next, hot,
-                           wave_cnt, rec);
-    else
-        join_count_n<false>(pairs, item_begin, item_rec, P, grid, rk, sk, lds_cap, ovf_table, ovf_next, hot,
-                            wave_cnt, rec);
-}
-
 template <bool kOnePass, uint32_t RPT, bool kNt>
-void join_write_t(const PartPair* pairs, const uint32_t* item_begin, const ItemRec* item_rec, uint32_t P,
-                  uint32_t grid, const int32_t* rk, const int32_t* rr, const int32_t* sk, const int32_t* sr,
-                  uint32_t lds_cap, const uint64_t* ovf_table, const uint32_t* ovf_next, const HotKeys* hot,
-                  const uint64_t* wave_base, uint64_t* total, int32_t* out_r, int32_t* out_s, uint64_t capacity,
-                  HeavyQueue* heavy, Recorder& rec) {
-    const size_t lds = join_lds_bytes(lds_cap, true);
+void join_write_t(const JoinArgs& a, Recorder& rec) {
+    const size_t lds = join_lds_bytes(a.lds_cap, true);
     allow_lds((const void*)k_join_write<kOnePass, RPT, kNt>, lds);
     rec.before(kOnePass ? "join_write_1pass" : "join_write");
-    const uint32_t item_grid = grid;
-    if (kOnePass && heavy) {
+    uint32_t grid = a.grid;
+    if (kOnePass && a.heavy) {
         // helpers: at most half the workgroups resident at once (by LDS and by
         // the waves the register budget allows: 6 per SIMD, 4 for the large build)
         const uint32_t by_lds = (uint32_t)(160u * 1024u / (lds + 1024u));  // lds: this launch's dynamic bytes
@@ -847,55 +849,55 @@ void join_write_t(const PartPair* pairs, const uint32_t* item_begin, const ItemR
         const uint32_t resident = 256u * std::max(1u, std::min(by_lds, by_waves));
         grid += std::max(1u, std::min(kMaxHelpers, resident / 2));
     }
-    hipLaunchKernelGGL((k_join_write<kOnePass, RPT, kNt>), dim3(grid), dim3(kJoinBlock), lds, rec.stream, pairs,
-                       item_begin, item_rec, P, rk, rr, sk, sr, lds_cap, ovf_table, ovf_next, hot, wave_base,
-                       (unsigned long long*)total, out_r, out_s, capacity, heavy, item_grid);
+    hipLaunchKernelGGL((k_join_write<kOnePass, RPT, kNt>), dim3(grid), dim3(kJoinBlock), lds, rec.stream, a.item_rec,
+                       a.rt, a.st, a.lds_cap, a.ovf_table, a.ovf_next, a.hot, a.wave, (unsigned long long*)a.total,
+                       a.out_r, a.out_s, a.capacity, a.heavy, a.grid);
     rec.after();
 }
 
-template <bool kOnePass, bool kNt>
-void join_write_p(const PartPair* pairs, const uint32_t* item_begin, const ItemRec* item_rec, uint32_t P,
-                  uint32_t grid, const int32_t* rk, const int32_t* rr, const int32_t* sk, const int32_t* sr,
-                  uint32_t lds_cap, const uint64_t* ovf_table, const uint32_t* ovf_next, const HotKeys* hot,
-                  const uint64_t* wave_base, uint64_t* total, int32_t* out_r, int32_t* out_s, uint64_t capacity,
-                  HeavyQueue* heavy, Recorder& rec) {
-    switch (join_rpt(lds_cap)) {
-        case kRptSmall:
-            join_write_t<kOnePass, kRptSmall, kNt>(pairs, item_begin, item_rec, P, grid, rk, rr, sk, sr, lds_cap,
-                                              ovf_table, ovf_next, hot, wave_base, total, out_r, out_s, capacity, heavy, rec);
-            break;
-        case kRptMid:
-            join_write_t<kOnePass, kRptMid, kNt>(pairs, item_begin, item_rec, P, grid, rk, rr, sk, sr, lds_cap,
-                                            ovf_table, ovf_next, hot, wave_base, total, out_r, out_s, capacity, heavy, rec);
-            break;
-        default:
-            join_write_t<kOnePass, kRptLarge, kNt>(pairs, item_begin, item_rec, P, grid, rk, rr, sk, sr, lds_cap,
-                                              ovf_table, ovf_next, hot, wave_base, total, out_r, out_s, capacity, heavy, rec);
-            break;
+template <bool kNt>
+void join_count_n(const JoinArgs& a, Recorder& rec) {
+    switch (join_rpt(a.lds_cap)) {
+        case kRptSmall: join_count_t<kRptSmall, kNt>(a, rec); break;
+        case kRptMid: join_count_t<kRptMid, kNt>(a, rec); break;
+        default: join_count_t<kRptLarge, kNt>(a, rec); break;
     }
 }
 
-void join_write(const PartPair* pairs, const uint32_t* item_begin, const ItemRec* item_rec, uint32_t P,
-                uint32_t grid,
-                const int32_t* rk, const int32_t* rr, const int32_t* sk, const int32_t* sr,
-                uint32_t lds_cap, const uint64_t* ovf_table, const uint32_t* ovf_next,
-                const uint64_t* wave_base, uint64_t* total, int32_t* out_r, int32_t* out_s,
-                const HotKeys* hot, uint64_t capacity, HeavyQueue* heavy, bool nt_s, Recorder& rec) {
+template <bool kOnePass, bool kNt>
+void join_write_n(const JoinArgs& a, Recorder& rec) {
+    switch (join_rpt(a.lds_cap)) {
+        case kRptSmall: join_write_t<kOnePass, kRptSmall, kNt>(a, rec); break;
+        case kRptMid: join_write_t<kOnePass, kRptMid, kNt>(a, rec); break;
+        default: join_write_t<kOnePass, kRptLarge, kNt>(a, rec); break;
+    }
+}
+
+}  // namespace
+
+void join_count(const ItemRec* item_rec, uint32_t grid, const Tuple* rt, const Tuple* st, uint32_t lds_cap,
+                const uint64_t* ovf_table, const uint32_t* ovf_next, const HotKeys* hot, uint64_t* wave_cnt, bool nt_s,
+                Recorder& rec) {
     if (grid == 0) return;
-    if (wave_base == nullptr) {
-        if (nt_s)
-            join_write_p<true, true>(pairs, item_begin, item_rec, P, grid, rk, rr, sk, sr, lds_cap, ovf_table,
-                                     ovf_next, hot, wave_base, total, out_r, out_s, capacity, heavy, rec);
-        else
-            join_write_p<true, false>(pairs, item_begin, item_rec, P, grid, rk, rr, sk, sr, lds_cap, ovf_table,
-                                      ovf_next, hot, wave_base, total, out_r, out_s, capacity, heavy, rec);
+    const JoinArgs a{item_rec, grid, rt, st, lds_cap, ovf_table, ovf_next, hot, wave_cnt, nullptr, nullptr, nullptr, 0,
+                     nullptr};
+    if (nt_s) join_count_n<true>(a, rec);
+    else join_count_n<false>(a, rec);
+}
+
+void join_write(const ItemRec* item_rec, uint32_t grid, const Tuple* rt, const Tuple* st, uint32_t lds_cap,
+                const uint64_t* ovf_table, const uint32_t* ovf_next, const HotKeys* hot, const uint64_t* wave_base,
+                uint64_t* total, int32_t* out_r, int32_t* out_s, uint64_t capacity, HeavyQueue* heavy, bool nt_s,
+                Recorder& rec) {
+    if (grid == 0) return;
+    const JoinArgs a{item_rec, grid, rt, st, lds_cap, ovf_table, ovf_next, hot, const_cast<uint64_t*>(wave_base),
+                     total, out_r, out_s, capacity, wave_base ? nullptr : heavy};
+    if (wave_base) {
+        if (nt_s) join_write_n<false, true>(a, rec);
+        else join_write_n<false, false>(a, rec);
     } else {
-        if (nt_s)
-            join_write_p<false, true>(pairs, item_begin, item_rec, P, grid, rk, rr, sk, sr, lds_cap, ovf_table,
-                                      ovf_next, hot, wave_base, total, out_r, out_s, capacity, nullptr, rec);
-        else
-            join_write_p<false, false>(pairs, item_begin, item_rec, P, grid, rk, rr, sk, sr, lds_cap, ovf_table,
-                                       ovf_next, hot, wave_base, total, out_r, out_s, capacity, nullptr, rec);
+        if (nt_s) join_write_n<true, true>(a, rec);
+        else join_write_n<true, false>(a, rec);
     }
 }
 

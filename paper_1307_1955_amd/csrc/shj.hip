@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(kShjBlock) k_shj_count(const int32_t* __restri
     uint32_t head[kSU], c[kSU];
     shj_probe<false>(s_key, nullptr, begin, n_s, table, next, nslots, heavy_limit(n_r), hk, hr, nhk, &hs, q, qr,
                      head, c);
-    heavy_counts<kShjBlock, kHeavyV>(r_key, n_r, &hs);
+    heavy_counts<kShjBlock, kHeavyV>(Column<1>{r_key}, n_r, &hs);
     uint64_t cnt = 0;
 #pragma unroll
     for (uint32_t u = 0; u < kSU; ++u) cnt += count_of(c[u], &hs);
@@ -180,7 +180,7 @@ __global__ void __launch_bounds__(kShjBlock) __attribute__((amdgpu_waves_per_eu(
     shj_probe<true>(s_key, s_rid, begin, n_s, table, next, nslots, lim, hk, hr, nhk, &hs, q, qr, head, c);
     // with R in one chunk the queue adds no workgroups to a tuple: keep the block's own scan
     if (kOnePass && n_r > kHelpChunk) hand_off(heavy, &hs, 0u, (uint32_t)n_r);
-    heavy_counts<kShjBlock, kHeavyV, kOnePass>(r_key, n_r, &hs);
+    heavy_counts<kShjBlock, kHeavyV, kOnePass>(Column<1>{r_key}, n_r, &hs);
     uint64_t pos0;
     if (kOnePass) {
         uint64_t mine = 0;
@@ -223,8 +223,9 @@ __global__ void __launch_bounds__(kShjBlock) __attribute__((amdgpu_waves_per_eu(
             }
         }
     }
-    heavy_writes<kShjBlock, kHeavyV, true>(r_key, r_rid, n_r, &hs, capacity, out_r, out_s);
-    if (kOnePass) help_heavy<kShjBlock>(heavy, r_key, r_rid, total, capacity, out_r, out_s, hs.wsum);
+    heavy_writes<kShjBlock, kHeavyV, true>(Column<1>{r_key}, Column<1>{r_rid}, n_r, &hs, capacity, out_r, out_s);
+    if (kOnePass)
+        help_heavy<kShjBlock>(heavy, Column<1>{r_key}, Column<1>{r_rid}, total, capacity, out_r, out_s, hs.wsum);
 }
 
 __global__ void __launch_bounds__(256) k_zero_one_pass(uint64_t* __restrict__ total, uint64_t* __restrict__ q,
