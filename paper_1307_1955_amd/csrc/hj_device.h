@@ -71,23 +71,23 @@ __device__ __forceinline__ uint64_t chain_slot(int32_t key, uint32_t head) {
 
 constexpr uint64_t kClaimed = ~0ull;  // chain_claim: the row took an empty slot
 
-// Finds key k's slot, probing from slot s with step(s).  A row whose key is
-// new claims an empty slot with one compare-and-swap and is done (kClaimed);
-// otherwise the key's slot is returned and the row still has to be pushed
-// onto its chain (WavePush).
+// Finds key k's slot, probing from slot *s with step(*s), and leaves it in *s.
+// A row whose key is new claims an empty slot with one compare-and-swap and is
+// done (true); otherwise the row still has to be pushed onto the slot's chain
+// (WavePush).
 template <typename Step>
-__device__ __forceinline__ uint64_t chain_claim(uint64_t* table, uint64_t s, int32_t k, uint32_t row, Step step) {
+__device__ __forceinline__ bool chain_claim(uint64_t* table, uint64_t* s, int32_t k, uint32_t row, Step step) {
     while (true) {
         // Read first and CAS only a free slot (faster on MI355X than an
         // unconditional CAS: the read brings the line in, the CAS then hits it).
-        uint64_t cur = __hip_atomic_load(&table[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint64_t cur = __hip_atomic_load(&table[*s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (cur == kEmptySlot) {
-            cur = atomicCAS((unsigned long long*)&table[s], (unsigned long long)kEmptySlot,
+            cur = atomicCAS((unsigned long long*)&table[*s], (unsigned long long)kEmptySlot,
                             (unsigned long long)chain_slot(k, row | kLast));
-            if (cur == kEmptySlot) return kClaimed;
+            if (cur == kEmptySlot) return true;
         }
-        if ((uint32_t)cur == (uint32_t)k) return s;
-        s = step(s);
+        if ((uint32_t)cur == (uint32_t)k) return false;
+        *s = step(*s);
     }
 }
 
@@ -142,21 +142,28 @@ __device__ __forceinline__ uint32_t hot_rows_of(int32_t q, const int32_t* hk, co
     return rows;
 }
 
-// Pushes of duplicate keys by one wave.  A row is pushed in front of its key's
+// Table rows of one wave: claim() finds a row's slot, add() pushes the rows
+// whose keys are not new.  A row is pushed in front of its key's
 // chain by exchanging the slot's head, which cannot fail (a claimed slot keeps
-// its key), so a heavy key costs no compare-and-swap retries.  Exchanges are
-// saved twice over: lanes pushing onto the same slot in one call are linked
-// among themselves (lowest lane in front), and the wave keeps that run as a
-// pending chain (slot, key, head row, tail row) that later runs onto the same
-// slot extend, with one exchange when the wave moves to another slot or
-// flushes.  Links are written before the exchange publishes them; tables are
-// read only after the build launch ends.  Every lane of the wave calls add()
-// and flush() (wave-uniform control flow); the pending fields are uniform.
+// its key), so a heavy key costs no compare-and-swap retries.  What bounds a
+// build with duplicates is accesses to one slot from many lanes (each waits for
+// the others, about 10 ns) and exchanges of a wave that wait for each other, so
+//  * lanes with one key look its slot up once (claim);
+//  * lanes pushing onto the same slot in one call are linked among themselves
+//    (lowest lane in front), and the wave keeps such a run as a pending chain
+//    (slot, key, head row, tail row) that later rows of the slot extend, with
+//    one exchange when a run on another slot takes its place or it is flushed;
+//  * rows alone on their slot are exchanged all at once.  Each of them in turn
+//    through the pending run took the SHJ build and join of 16M rows, 4 to a
+//    key, 2684 us against 2203 us.
+// Links are written before the exchange publishes them; tables are read only
+// after the build ends.  Every lane of the wave calls claim(), add() and flush()
+// (wave-uniform control flow); the pending fields are uniform.
 struct WavePush {
     uint64_t slot = kClaimed;
     int32_t key = 0;
     uint32_t head = 0, tail = 0;
-    uint32_t len = 0;          // rows in the pending run
+    uint32_t len = 0;          // rows in the pending run (0: none)
     HotKeys* hot_keys = nullptr;  // where runs of kHotRun or more rows record their key
     // The slot of the last key the wave pushed: a row with that key can skip
     // chain_claim (a claimed slot never moves), which keeps a heavy key's rows
@@ -165,6 +172,30 @@ struct WavePush {
     int32_t hot_key = 0;
 
     __device__ __forceinline__ bool hot(int32_t k) const { return hot_slot != kClaimed && k == hot_key; }
+
+    // The slot a row has to be pushed on, kClaimed if its key was new or the
+    // lane has no row.  seen: kSeen words of LDS of the wave's own, where lanes
+    // meet by key: the lane whose number an entry holds looks up the slot for
+    // all lanes of its key there; lanes of another key look up their own.
+    static constexpr uint32_t kSeen = 128;
+    template <typename Step>
+    __device__ __forceinline__ uint64_t claim(uint64_t* table, bool active, int32_t k, uint32_t row, uint64_t home,
+                                              Step step, volatile uint8_t* seen) {
+        const uint32_t lane = __lane_id();
+        const bool known = active && hot(k);
+        bool lead = active && !known;
+        const uint32_t e = slot_hash(k) % kSeen;
+        if (lead) seen[e] = (uint8_t)lane;
+        const uint32_t w = lead ? seen[e] : lane;
+        const int32_t wk = __shfl(k, (int)w);  // (all lanes take part)
+        lead = lead && (w == lane || wk != k);
+        uint64_t s = home;
+        bool fresh = false;
+        if (lead) fresh = chain_claim(table, &s, k, row, step);
+        const uint64_t other = __shfl(s, (int)w);
+        if (!active || fresh) return kClaimed;
+        return known ? hot_slot : lead ? s : other;
+    }
 
     __device__ __forceinline__ void flush(uint64_t* table, uint32_t* next) {
         if (slot != kClaimed) {
@@ -175,6 +206,7 @@ struct WavePush {
                 if (hot_keys && len >= kHotRun) record_hot(hot_keys, key, len);
             }
             slot = kClaimed;
+            len = 0;
         }
     }
 
@@ -191,6 +223,7 @@ struct WavePush {
     __device__ __forceinline__ void flush_block(uint64_t* table, uint32_t* next, Run* runs) {
         if (__lane_id() == 0) runs[threadIdx.x / kWave] = Run{slot, key, head, tail, len};
         slot = kClaimed;
+        len = 0;
         __syncthreads();
         if (threadIdx.x == 0) {
             for (uint32_t i = 0; i < kWaves; ++i) {
@@ -214,16 +247,21 @@ struct WavePush {
         __syncthreads();
     }
 
-    // s: the lane's slot from chain_claim (kClaimed: nothing to push).
+    // s: the lane's slot from claim (kClaimed: nothing to push).
     __device__ __forceinline__ void add(uint64_t* table, uint32_t* next, uint64_t s, int32_t k, uint32_t row) {
         const uint32_t lane = __lane_id();
         uint64_t todo = __ballot(s != kClaimed);
+        uint64_t singles = 0;
         while (todo) {
             const int lead = __ffsll((unsigned long long)todo) - 1;
             const uint64_t ls = __shfl(s, lead);
             const int32_t lk = __shfl(k, lead);
             const uint64_t peers = __ballot(s == ls) & todo;
             todo &= ~peers;
+            if (ls != slot && (peers & (peers - 1)) == 0) {
+                singles |= peers;
+                continue;
+            }
             const int last = 63 - __clzll((long long)peers);
             const uint32_t first_row = __shfl(row, lead);
             const uint32_t last_row = __shfl(row, last);
@@ -244,6 +282,27 @@ struct WavePush {
                 tail = last_row;
                 len = rows;
             }
+        }
+        if (singles == 0) return;
+        bool go = (singles >> lane) & 1u;
+        uint64_t to = s, v = chain_slot(k, row);
+        uint32_t link = row;
+        if (len < 2) {  // no run to keep: the first single takes the pending row's place and exchanges it
+            const int first = __ffsll((unsigned long long)singles) - 1;
+            if ((int)lane == first) {
+                go = slot != kClaimed;
+                to = slot;
+                v = chain_slot(key, head);
+                link = tail;
+            }
+            slot = hot_slot = __shfl(s, first);
+            key = hot_key = __shfl(k, first);
+            head = tail = __shfl(row, first);
+            len = 1;
+        }
+        if (go) {
+            const uint64_t prev = atomicExch((unsigned long long*)&table[to], (unsigned long long)v);
+            next[link] = (uint32_t)(prev >> 32);
         }
     }
 };

@@ -70,6 +70,7 @@ __global__ void __launch_bounds__(256) k_ovf_build(const PartPair* __restrict__ 
                                                   HeavyQueue* heavy) {
     constexpr uint32_t kWaves = 256 / kWave;
     __shared__ WavePush::Run runs[kWaves];
+    __shared__ uint8_t seen[kWaves * WavePush::kSeen];
     const uint32_t nitems = ovf_begin[P];
     for (uint32_t item = blockIdx.x; item < nitems; item += gridDim.x) {
         const uint32_t i = ovf_part[item];
@@ -91,11 +92,9 @@ __global__ void __launch_bounds__(256) k_ovf_build(const PartPair* __restrict__ 
         for (uint32_t j0 = c * chunk; j0 < end; j0 += blockDim.x) {  // uniform trip count
             const uint32_t j = j0 + threadIdx.x;
             int32_t k = 0;
-            uint64_t s = kClaimed;
-            if (j < end) {
-                k = key_of(rt[pp.r_off + j]);
-                s = push.hot(k) ? push.hot_slot : chain_claim(region, region_slot(k, step.H), k, j, step);
-            }
+            if (j < end) k = key_of(rt[pp.r_off + j]);
+            const uint64_t s = push.claim(region, j < end, k, j, region_slot(k, step.H), step,
+                                          seen + threadIdx.x / kWave * WavePush::kSeen);
             push.add(region, next, s, k, j);
         }
         push.flush_block<kWaves>(region, next, runs);

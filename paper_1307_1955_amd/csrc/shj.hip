@@ -60,6 +60,7 @@ __global__ void __launch_bounds__(256) k_shj_build(const int32_t* __restrict__ k
                                                   uint64_t nslots, HotKeys* hot) {
     constexpr uint32_t kWaves = 256 / kWave;
     __shared__ WavePush::Run runs[kWaves];
+    __shared__ uint8_t seen[kWaves * WavePush::kSeen];
     const WrapStep step{nslots};
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     WavePush push;
@@ -67,11 +68,9 @@ __global__ void __launch_bounds__(256) k_shj_build(const int32_t* __restrict__ k
     for (uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x; i0 < n; i0 += stride) {  // uniform trip count
         const uint64_t i = i0 + threadIdx.x;
         int32_t k = 0;
-        uint64_t s = kClaimed;
-        if (i < n) {
-            k = kNt ? __builtin_nontemporal_load(key + i) : key[i];  // read once
-            s = push.hot(k) ? push.hot_slot : chain_claim(table, home_slot(k, nslots), k, (uint32_t)i, step);
-        }
+        if (i < n) k = kNt ? __builtin_nontemporal_load(key + i) : key[i];  // read once
+        const uint64_t s = push.claim(table, i < n, k, (uint32_t)i, home_slot(k, nslots), step,
+                                      seen + threadIdx.x / kWave * WavePush::kSeen);
         push.add(table, next, s, k, (uint32_t)i);
     }
     push.flush_block<kWaves>(table, next, runs);
