@@ -6,8 +6,9 @@
 // SHJ: fill table -> build -> count -> scan -> write (or build -> one-pass write).
 // PHJ: hist -> starts -> scatter (R and S in the same launches; with more than
 // kFuseBits radix bits a second scatter, the partition pairs planned beside the
-// last one; small joins without the starts launch) -> HBM tables for oversized R partitions -> count -> scan -> write
-// (or one-pass write).
+// last one; small joins without the starts launch) -> count -> scan -> write
+// (or one-pass write); the first join launch builds the HBM tables of oversized
+// R partitions.
 // Everything is enqueued on one stream; no host synchronisation, no
 // host<->device copy and no allocation happen here.
 #include "engine.h"
@@ -64,15 +65,13 @@ struct Carver {
 };
 
 
-// LDS per CU on gfx950, and what a join workgroup takes beyond its dynamic
-// tables (static LDS plus allocation rounding; measured: a 54,080-byte table
-// set no longer fits three workgroups per CU, 53,312 bytes does).
+// LDS per CU on gfx950, and what a join workgroup is planned with: 12 bytes per
+// tuple and 1.5 KB (static LDS plus allocation rounding; measured: a 54,080-byte
+// table set no longer fits three workgroups per CU, 53,312 bytes does).  The
+// tables themselves (join_lds_bytes) take at most that.
 constexpr size_t kLdsPerCu = 160 * 1024;
-constexpr size_t kJoinStaticLds = 1024;
 
-uint32_t join_blocks_per_cu(uint32_t cap) {
-    return (uint32_t)(kLdsPerCu / (hj::join_lds_bytes(cap, true) + kJoinStaticLds));
-}
+uint32_t join_blocks_per_cu(uint32_t cap) { return (uint32_t)(kLdsPerCu / (12ull * cap + 1536)); }
 
 // Default LDS table capacity: room for a partition three standard deviations
 // above the mean size (uniform hashing), then grown to the largest capacity
@@ -208,7 +207,7 @@ struct PhjWs {
     uint64_t nzero;
     hj::HeavyQueue* heavy;  // one-pass heavy-tuple queue
     hj::HotKeys* hot;       // hot keys of the HBM-table build
-    uint32_t* words;        // [0]: an R partition is oversized
+    uint32_t* words;        // [0]: an R partition is oversized, [1], [2]: HBM-table build items taken, built
     uint64_t *st1, *st2;    // scan states: partition starts (pass 1, final),
     uint64_t* stw;          //   per-wave match counts,
     uint64_t* stp;          //   join plan
@@ -275,7 +274,7 @@ PhjWs phj_layout(const Plan& pl, uint64_t n_r, uint64_t n_s, uint64_t n_r_tab, v
     const uint64_t n2 = one ? 0 : hist2 ? hj::scan_state_words(2ull * pl.P) : hj::start_state_words(pl.P);
     const uint64_t nw = hj::scan_state_words(w.items_ub * hj::kJoinWaves);
     const uint64_t np = hj::plan_state_words(pl.P);
-    w.nzero = kHeavyWords + kHotWords + 1 + c2 + n1 + n2 + nw + np;
+    w.nzero = kHeavyWords + kHotWords + 2 + c2 + n1 + n2 + nw + np;
     w.zero = c.take<uint64_t>(w.nzero);
     w.bytes = c.off;
     if (w.zero) {  // (sizing only when there is no base: no arithmetic on a null pointer)
@@ -287,7 +286,7 @@ PhjWs phj_layout(const Plan& pl, uint64_t n_r, uint64_t n_s, uint64_t n_r_tab, v
         };
         w.heavy = reinterpret_cast<hj::HeavyQueue*>(part(kHeavyWords));
         w.hot = reinterpret_cast<hj::HotKeys*>(part(kHotWords));
-        w.words = reinterpret_cast<uint32_t*>(part(1));
+        w.words = reinterpret_cast<uint32_t*>(part(2));
         uint64_t* c2p = part(c2);
         if (hist2) w.cnt2 = reinterpret_cast<uint32_t*>(c2p);
         w.st1 = part(n1);
@@ -500,19 +499,19 @@ hj::Tuple* phj_partition(const Plan& pl, const hj_rel& R, const hj_rel& S, const
     return w.B;
 }
 
-// PHJ join of the planned partition pairs (Algorithm 1 per pair): HBM tables
-// for oversized R partitions, then count -> scan -> write (or one-pass write).
+// PHJ join of the planned partition pairs (Algorithm 1 per pair): count -> scan
+// -> write (or one-pass write).
 // rt: partitioned R, st: partitioned S.
 void phj_join_pairs(const Plan& pl, const PhjWs& w, const hj::Tuple* rt, const hj::Tuple* st, const hj_out& out,
                     uint64_t* d_count, hj::Recorder& rec) {
-    hj::join_ovf_build(w.pairs, w.ovf_begin, w.ovf_part, pl.P, (uint32_t)w.ovf_ub, rt, w.ovf_table, w.ovf_next,
-                       w.hot, pl.one_pass ? w.heavy : nullptr, rec, !w.clears);
+    const hj::OvfBuild ovf{w.pairs, w.ovf_begin, w.ovf_part, w.ovf_begin + pl.P, w.words, rec.ctl.err};
+    if (!w.clears) hj::join_ovf_clear(ovf, pl.P, (uint32_t)w.ovf_ub, w.ovf_table, rec);
     if (!pl.one_pass) {
-        hj::join_count(w.item_rec, (uint32_t)w.items_ub, rt, st, pl.lds_cap, w.ovf_table, w.ovf_next, w.hot,
-                       w.wave_cnt, pl.nt_s, rec);
+        hj::join_count(w.item_rec, (uint32_t)w.items_ub, rt, st, pl.lds_cap, pl.B, pl.hash, ovf, w.ovf_table,
+                       w.ovf_next, w.hot, w.wave_cnt, pl.nt_s, rec);
         hj::scan_u64(w.wave_cnt, w.wave_cnt, w.items_ub * hj::kJoinWaves, w.stw, d_count, rec);
     }
-    hj::join_write(w.item_rec, (uint32_t)w.items_ub, rt, st, pl.lds_cap, w.ovf_table, w.ovf_next, w.hot,
+    hj::join_write(w.item_rec, (uint32_t)w.items_ub, rt, st, pl.lds_cap, pl.B, pl.hash, ovf, w.ovf_table, w.ovf_next, w.hot,
                    pl.one_pass ? nullptr : w.wave_cnt, d_count, out.rid_r, out.rid_s, out.capacity,
                    pl.one_pass ? w.heavy : nullptr, pl.nt_s, rec);
 }

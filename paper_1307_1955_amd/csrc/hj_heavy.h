@@ -45,6 +45,11 @@ struct HeavySet {
     uint32_t wsum[kHeavyMaxWaves * kHeavyV];  // per-wave hit counts of one scan step
 };
 
+// A value equal in all lanes, as a scalar (loops around barriers are on scalars).
+__device__ __forceinline__ uint32_t uniform_word(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+
 // Length of the chain at head field h, or lim + 1 if longer.
 __device__ __forceinline__ uint32_t chain_len_bounded(const uint32_t* __restrict__ next, uint32_t h,
                                                       uint32_t lim) {
@@ -85,7 +90,7 @@ __device__ __forceinline__ void heavy_counts(Col rk, Len r_len, HeavySet* hs) {
     constexpr uint32_t kWaves = kBlock / kWave;
     static_assert(kWaves <= kHeavyMaxWaves, "block too large for the heavy set");
     __syncthreads();  // registrations done
-    const uint32_t ne = min(hs->n, kMaxHeavy);
+    const uint32_t ne = uniform_word(min(hs->n, kMaxHeavy));
     if (threadIdx.x < ne) {
         // queued entries are nobody's representative and have none
         const uint32_t queued = kQueued ? hs->queued : 0u;
@@ -101,7 +106,7 @@ __device__ __forceinline__ void heavy_counts(Col rk, Len r_len, HeavySet* hs) {
     __syncthreads();
     const uint32_t w = threadIdx.x / kWave;
     for (uint32_t e = 0; e < ne; ++e) {
-        if (hs->rep[e] != e) continue;  // uniform: LDS value
+        if (uniform_word(hs->rep[e]) != e) continue;
         const int32_t k = hs->key[e];
         uint32_t m = 0;
         Len j = threadIdx.x;
@@ -143,11 +148,11 @@ __device__ __forceinline__ void heavy_writes(Col rk, Col rr, Len r_len, HeavySet
     static_assert(kV <= 32 && kMaxHeavy <= sizeof(hs->wsum) / sizeof(uint32_t), "fill counters fit wsum");
     uint32_t* fill = hs->wsum;  // per representative entry
     __syncthreads();  // positions published
-    const uint32_t ne = min(hs->n, kMaxHeavy);
+    const uint32_t ne = uniform_word(min(hs->n, kMaxHeavy));
     if (threadIdx.x < ne) fill[threadIdx.x] = 0;
     __syncthreads();
     for (uint32_t e = 0; e < ne; ++e) {
-        if (hs->rep[e] != e) continue;
+        if (uniform_word(hs->rep[e]) != e) continue;
         const int32_t k = hs->key[e];
         for (Len j0 = 0; j0 < r_len; j0 += kStep) {
             // element u of the thread: row j0 + u * kBlock + threadIdx.x; rows
@@ -232,12 +237,13 @@ __device__ __forceinline__ uint32_t claim_chunk(uint32_t* counter, uint32_t* sh)
     __syncthreads();  // sh free
     if (threadIdx.x == 0) sh[0] = atomicAdd(counter, 1u);
     __syncthreads();
-    return sh[0];
+    return uniform_word(sh[0]);
 }
 
 // rk, rr: the columns the queued tuples' R rows index (job rows r_off ..
 // r_off + r_len - 1).  sh: LDS scratch of 9 + kHeavyV * kBlock / 64 words.
-template <uint32_t kBlock, typename Col>
+// kChunk: R rows per claimed chunk.
+template <uint32_t kBlock, uint32_t kChunk, typename Col>
 __device__ __forceinline__ void help_heavy(HeavyQueue* Q, Col rk, Col rr,
                                            unsigned long long* __restrict__ total, uint64_t capacity,
                                            int32_t* __restrict__ out_r, int32_t* __restrict__ out_s, uint32_t* sh) {
@@ -249,7 +255,7 @@ __device__ __forceinline__ void help_heavy(HeavyQueue* Q, Col rk, Col rr,
     __syncthreads();
     if (threadIdx.x == 0) sh[1] = min(__hip_atomic_load(&Q->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), kHeavyJobs);
     __syncthreads();
-    const uint32_t nj = sh[1];
+    const uint32_t nj = uniform_word(sh[1]);
     if (nj == 0) return;
     while (true) {
         // the lowest queued tuple that still has unclaimed chunks (one thread looks at each)
@@ -263,11 +269,11 @@ __device__ __forceinline__ void help_heavy(HeavyQueue* Q, Col rk, Col rr,
             HeavyJob* J = &Q->job[threadIdx.x];
             if (__hip_atomic_load(&J->valid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &&
                 __hip_atomic_load(&J->write_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
-                    (J->r_len + kHelpChunk - 1) / kHelpChunk)
+                    (J->r_len + kChunk - 1) / kChunk)
                 atomicMin(&sh[6], threadIdx.x);
         }
         __syncthreads();
-        const uint32_t e = sh[6];
+        const uint32_t e = uniform_word(sh[6]);
         if (e == ~0u) return;
         HeavyJob* J = &Q->job[e];
         __syncthreads();
@@ -280,12 +286,12 @@ __device__ __forceinline__ void help_heavy(HeavyQueue* Q, Col rk, Col rr,
         }
         __syncthreads();
         const int32_t k = (int32_t)sh[2], srid = (int32_t)sh[3];
-        const uint64_t r_off = sh[7], r_len = sh[8 + kV * kWaves];
-        const uint32_t nchunks = (uint32_t)((r_len + kHelpChunk - 1) / kHelpChunk);
+        const uint64_t r_off = uniform_word(sh[7]), r_len = uniform_word(sh[8 + kV * kWaves]);
+        const uint32_t nchunks = (uint32_t)((r_len + kChunk - 1) / kChunk);
         while (true) {
             const uint32_t c = claim_chunk(&J->write_next, sh);
             if (c >= nchunks) break;
-            const uint64_t lo = r_off + (uint64_t)c * kHelpChunk, hi = r_off + min((uint64_t)(c + 1) * kHelpChunk, r_len);
+            const uint64_t lo = r_off + (uint64_t)c * kChunk, hi = r_off + min((uint64_t)(c + 1) * kChunk, r_len);
             for (uint64_t j0 = lo; j0 < hi; j0 += (uint64_t)kV * kBlock) {
                 // element u of the thread: row j0 + u * kBlock + threadIdx.x; rows
                 // past the chunk read its last row (all loads issue together) and

@@ -104,7 +104,15 @@ void shj_build(const int32_t* key, uint64_t n, uint64_t* table, uint32_t* next, 
 // own work claims chunks of the tuple's R rows and writes their matches (one
 // 64-byte record per tuple; the queue is zeroed before each probe).
 constexpr uint32_t kHeavyJobs = 256;
-constexpr uint32_t kHelpChunk = 1u << 16;  // R rows per claimed chunk
+// R rows per claimed chunk of a table over all of R (SHJ) and of a partition's,
+// and how many R rows a tuple must have to be queued at all.  A partition's
+// queue holds few tuples: 2 steps of a workgroup per chunk spread them over the
+// device (1M x 16M, a tenth of R on one key, one-pass write: 237 us with chunks
+// of 65536 rows, 200 with 8192); SHJ's is full, where more claims and more
+// reservations cost (1M x 16M: 1157 us and 1404).
+constexpr uint32_t kHelpChunk = 1u << 16;
+constexpr uint32_t kHelpChunkPart = 1u << 13;
+constexpr uint32_t kQueueRows = 1u << 16;
 struct HeavyJob {
     int32_t key, srid;
     uint32_t valid;        // 1 once the fields below are written
@@ -115,7 +123,7 @@ struct HeavyJob {
 struct HeavyQueue {
     uint32_t n;            // tuples handed in (may exceed kHeavyJobs: the rest stay with their workgroup)
     // PHJ one-pass write: the HBM-table build sets `wait` when a partition can
-    // hand tuples in (more than kHelpChunk rows) and adds that partition's
+    // hand tuples in (more than kQueueRows rows) and adds that partition's
     // work items to items_expected; those items count themselves done, and the
     // write's helper workgroups help the queue until items_done reaches
     // items_expected
@@ -186,12 +194,13 @@ constexpr uint32_t kFuseBits = 12;
 inline bool one_scatter(uint32_t passes, uint32_t b1, uint32_t b2) { return passes == 1 || b1 + b2 <= kFuseBits; }
 // Whether the histogram of the input counts the final partitions (up to 2^15
 // counters of a workgroup in LDS, 128 KiB); else pass 2 has its own.  Plans of
-// two scatters do so while the workgroups' rows fit the first copy, where they
-// lie until it is written.
+// two scatters do so while the workgroups' rows fit the first copy (8 bytes a
+// tuple), where they lie until it is written: up to 520 rows of 4 bytes for each
+// final partition and half as many for pass 1.
 constexpr uint32_t kWideCountBits = 15;
 inline bool counts_final(uint32_t passes, uint32_t b1, uint32_t b2, uint64_t n) {
     return one_scatter(passes, b1, b2) ||
-           ((counted_pass2(passes, b1, b2) || b1 + b2 <= kWideCountBits) && n >= 160ull << (b1 + b2));
+           ((counted_pass2(passes, b1, b2) || b1 + b2 <= kWideCountBits) && n >= 400ull << (b1 + b2));
 }
 // Whether the last scatter clears the HBM tables of oversized partitions (it
 // needs the final partitions' sizes before it starts), else a launch of its own.
@@ -329,16 +338,23 @@ constexpr uint32_t kJoinBlock = 512;
 constexpr uint32_t kJoinWaves = kJoinBlock / 64;
 constexpr uint32_t kJoinSub = 4608;     // S tuples per probe round of a work item (9 per lane)
 constexpr uint32_t kJoinChunk = 2 * kJoinSub;  // S tuples per work item (probed kJoinSub at a time)
-// R tuples per HBM-table build item: 8 rounds of a workgroup, or 64 in a
-// partition of more than kOvfBigPart tuples.  Small items keep the build's
-// latency low; in a large partition, which is large because a key is heavy as
-// often as not, each item's pushes of that key end in one exchange on its
-// slot, and those exchanges serialize.
+// R tuples per HBM-table build item: 4 rounds of a workgroup, more in a
+// partition of more than kOvfBigPart tuples, about 128 items of it, up to 32
+// rounds.  Small items keep the build's latency low (a round is a chain of
+// dependent accesses, about 3 us); in a large partition, which is large because
+// a key is heavy as often as not, each item's pushes of that key end in one
+// exchange on its slot, and those exchanges serialize.  A partition of 106K
+// rows (1M x 16M, a tenth of R on one key) took 98 us in items of 16384.
 constexpr uint32_t kOvfChunk = 2048;
 constexpr uint32_t kOvfChunkBig = 16384;
 constexpr uint32_t kOvfBigPart = 1u << 16;
-constexpr uint32_t kOvfGrid = 2048;  // workgroups of the HBM-table build launches (8 per CU)
-__host__ __device__ inline uint32_t ovf_chunk(uint32_t r_len) { return r_len > kOvfBigPart ? kOvfChunkBig : kOvfChunk; }
+constexpr uint32_t kOvfGrid = 2048;  // workgroups of the HBM-table clear launch (8 per CU)
+__host__ __device__ inline uint32_t ovf_chunk(uint32_t r_len) {
+    uint32_t c = kOvfChunk;
+    if (r_len > kOvfBigPart)
+        while (c < kOvfChunkBig && c < r_len / 128) c *= 2;
+    return c;
+}
 constexpr uint32_t kMaxLdsCap = 8192;   // largest R partition held in LDS
 // R tuples per thread of the LDS build (a kernel template argument: the build
 // keeps them in registers), by lds_cap class.
@@ -354,28 +370,40 @@ size_t plan_state_words(uint32_t P);
 uint32_t ovf_grid(uint32_t P, uint64_t n_r);
 uint32_t join_grid(uint32_t P, uint64_t n_s);  // (a multiple of 8 kItemGroup)
 constexpr uint32_t kItemGroup = 16;  // consecutive join items dealt to one XCD
-// Dynamic LDS bytes of the join kernels for a given lds_cap.
-size_t join_lds_bytes(uint32_t lds_cap, bool write);
-// rt, st: partitioned R and S.
+// Dynamic LDS bytes of the join kernels for tables of up to lds_cap tuples of a
+// partition on `bits` radix bits (0: a direct join).
+size_t join_lds_bytes(uint32_t lds_cap, uint32_t bits, bool write);
+// The HBM tables of R's oversized partitions (from the join plan): build items
+// by partition, their number, and the words (zero before) [1], [2] that count
+// items taken and built.
+struct OvfBuild {
+    const PartPair* pairs;
+    const uint32_t* begin;  // [P + 1]
+    const uint32_t* part;   // partition of every item
+    const uint32_t* total;  // begin + P
+    uint32_t* words;
+    uint64_t* err;          // the call's error word
+};
+// Clears the HBM tables where the last scatter did not (ClearTables).
+void join_ovf_clear(const OvfBuild& b, uint32_t P, uint32_t grid, uint64_t* ovf_table, Recorder& rec);
+// rt, st: partitioned R and S.  The first of a plan's join launches (the count,
+// or the one-pass write) builds the HBM tables before it probes them.
 // hot: where the build records its hot keys (zeroed before); heavy: the
 // one-pass queue (nullptr for count -> scan -> write), whose `wait` it sets.
-// clear == false: the tables were cleared by the last scatter (ClearTables).
-void join_ovf_build(const PartPair* pairs, const uint32_t* ovf_begin, const uint32_t* ovf_part, uint32_t P,
-                    uint32_t grid, const Tuple* rt, uint64_t* ovf_table, uint32_t* ovf_next, HotKeys* hot,
-                    HeavyQueue* heavy, Recorder& rec, bool clear);
-// item_rec comes from the join plan; grid: join_grid.
+// item_rec comes from the join plan; grid: join_grid; bits, hash: how R and S are
+// partitioned (all radix bits).
 void join_count(const ItemRec* item_rec, uint32_t grid, const Tuple* rt, const Tuple* st, uint32_t lds_cap,
-                const uint64_t* ovf_table, const uint32_t* ovf_next, const HotKeys* hot, uint64_t* wave_cnt, bool nt_s,
-                Recorder& rec);
+                uint32_t bits, uint32_t hash, const OvfBuild& ovf, uint64_t* ovf_table, uint32_t* ovf_next,
+                HotKeys* hot, uint64_t* wave_cnt, bool nt_s, Recorder& rec);
 void join_write(const ItemRec* item_rec, uint32_t grid, const Tuple* rt, const Tuple* st, uint32_t lds_cap,
-                const uint64_t* ovf_table, const uint32_t* ovf_next, const HotKeys* hot, const uint64_t* wave_base,
-                uint64_t* total, int32_t* out_r, int32_t* out_s, uint64_t capacity, HeavyQueue* heavy, bool nt_s,
-                Recorder& rec);
+                uint32_t bits, uint32_t hash, const OvfBuild& ovf, uint64_t* ovf_table, uint32_t* ovf_next,
+                HotKeys* hot, const uint64_t* wave_base, uint64_t* total, int32_t* out_r, int32_t* out_s, uint64_t capacity,
+                HeavyQueue* heavy, bool nt_s, Recorder& rec);
 // nt_s: S chunks read with non-temporal loads (LDS-table items).
 // wave_base == nullptr selects the one-pass write: `total` must be zero on entry
 // and ends as the number of pairs; `heavy` (one-pass only, zeroed before the
 // HBM-table build, or nullptr) takes the heavy S tuples of HBM-table
-// partitions that span several kHelpChunk-row chunks.  `hot`: the keys the
+// partitions of more than kQueueRows rows.  `hot`: the keys the
 // HBM-table build recorded (their S tuples skip the chain walk).
 // Writes zero to *d_count (joins with an empty side) and clears the call's
 // error word (rec.err_clear).

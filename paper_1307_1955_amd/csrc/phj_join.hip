@@ -5,17 +5,17 @@
 // probed kJoinSub tuples at a time.  One workgroup per item:
 //  * |R_i| <= lds_cap: R_i becomes a chained table in LDS.  The paper's
 //    bucket header + key list + rid list (Section 3.1) is laid out without an
-//    allocator: one head word per bucket and one 64-bit record (key, link)
-//    per R tuple at its own row; a tuple is pushed on its bucket's chain with
-//    one LDS exchange (the latch of Section 3.3).  Probing walks the chain
-//    (p3) and compares keys (p4); rids are read from HBM for matches only.
+//    allocator: one head word per bucket, one 32-bit record (what the bucket
+//    does not say of the key, link) and the rid per R tuple at its own row; a
+//    tuple is pushed on its bucket's chain with one LDS exchange (the latch of
+//    Section 3.3).  Probing walks the chain (p3) and compares keys (p4).
 //  * |R_i| > lds_cap (few, large partitions: low radix bits, duplicate-heavy
 //    R): the pair is joined through a partition-local open-addressing table
 //    in HBM (2 |R_i| slots at twice R_i's offset, plus per-key row chains),
-//    cleared by the pass-2 scatter (counted plans of up to 6 pass-2 bits) or
-//    by a clear launch, and built by a build launch (compare-and-swap for a
-//    new key, exchange pushes for duplicates); S tuples on very long chains
-//    are counted and written by the whole workgroup (hj_heavy.h).
+//    cleared by the last scatter (or a launch of its own: scatter_clears) and
+//    built by the first join launch before it probes (compare-and-swap for a
+//    new key, exchange pushes for duplicates; build_tables); S tuples on very
+//    long chains are counted and written by the whole workgroup (hj_heavy.h).
 // Workgroups take items in groups of 16 consecutive ones per XCD
 // (item_of_block), so one partition's items share that XCD's L2.
 // Output: count pass -> per-wave counts -> scan -> write pass, which re-runs
@@ -61,21 +61,44 @@ struct RegionStep {
     __device__ __forceinline__ uint64_t operator()(uint64_t s) const { return s + 1 == H ? 0 : s + 1; }
 };
 
-__global__ void __launch_bounds__(256) k_ovf_build(const PartPair* __restrict__ pairs,
-                                                  const uint32_t* __restrict__ ovf_begin,
-                                                  const uint32_t* __restrict__ ovf_part, uint32_t P,
-                                                  const Tuple* __restrict__ rt,
-                                                  uint64_t* __restrict__ ovf_table,
-                                                  uint32_t* __restrict__ ovf_next, HotKeys* hot,
-                                                  HeavyQueue* heavy) {
-    constexpr uint32_t kWaves = 256 / kWave;
-    __shared__ WavePush::Run runs[kWaves];
-    __shared__ uint8_t seen[kWaves * WavePush::kSeen];
-    const uint32_t nitems = ovf_begin[P];
-    for (uint32_t item = blockIdx.x; item < nitems; item += gridDim.x) {
-        const uint32_t i = ovf_part[item];
-        const uint32_t c = item - ovf_begin[i];
-        const PartPair pp = pairs[i];
+struct ItemLoc {
+    uint32_t item;
+    bool live;
+    uint32_t r_off, r_len;
+    uint32_t s_begin, s_n;
+};
+
+// A value that is equal in all lanes, as a scalar: loops and branches around
+// barriers have to be on scalars, or the compiler may part a wave's lanes there.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return uniform_word(x); }
+
+// The HBM tables of the oversized partitions, built inside the join launch that
+// probes them first: a workgroup claims build items (ovf_chunk rows of a
+// partition) until none is left and, with `wait`, returns only when every item
+// is built.  A workgroup waits when all items are claimed, so each is in the
+// hands of a running workgroup that waits for nothing before it is done.
+// Workgroups whose own item needs a table build and wait; of the others the
+// first `nitems` build before they turn to their items (every claim is an atomic
+// on one word: claims by all workgroups, after their items, took the one-pass
+// write of 64K x 16M with a tenth of R on one key from 121 us to 226).
+// A build launch of its own cost every join 6 us, mostly for nothing to build.
+// What bounds a build is its chain of dependent accesses, about 3 us per 512
+// rows; the joins of other partitions run beside it.
+// lds: kJoinWaves runs, a word and kJoinWaves * WavePush::kSeen bytes.
+__device__ __forceinline__ void build_tables(const OvfBuild& B, const Tuple* rt, uint64_t* ovf_table,
+                                                      uint32_t* ovf_next, HotKeys* hot, HeavyQueue* heavy,
+                                                      uint32_t nitems, bool wait, uint32_t* lds) {
+    WavePush::Run* runs = reinterpret_cast<WavePush::Run*>(lds);
+    uint32_t* s_item = reinterpret_cast<uint32_t*>(runs + kJoinWaves);
+    uint8_t* seen = reinterpret_cast<uint8_t*>(s_item + 1) + threadIdx.x / kWave * WavePush::kSeen;
+    while (true) {
+        if (threadIdx.x == 0) *s_item = atomicAdd(&B.words[1], 1u);
+        __syncthreads();
+        const uint32_t item = uniform(*s_item);
+        if (item >= nitems) break;
+        const uint32_t i = uniform(B.part[item]);
+        const uint32_t c = item - uniform(B.begin[i]);
+        const PartPair pp{uniform(B.pairs[i].r_off), uniform(B.pairs[i].r_len), 0u, uniform(B.pairs[i].s_len)};
         uint64_t* region = ovf_table + 2ull * pp.r_off;
         uint32_t* next = ovf_next + pp.r_off;
         const RegionStep step{2u * pp.r_len};
@@ -83,115 +106,167 @@ __global__ void __launch_bounds__(256) k_ovf_build(const PartPair* __restrict__ 
         const uint32_t end = min((c + 1) * chunk, pp.r_len);
         // a partition the one-pass write may queue tuples of: the write's helpers
         // wait until its work items are done
-        if (heavy && c == 0 && threadIdx.x == 0 && pp.r_len > kHelpChunk) {
+        if (heavy && c == 0 && threadIdx.x == 0 && pp.r_len > kQueueRows) {
             atomicAdd(&heavy->items_expected, items_of(pp));
-            heavy->wait = 1;
+            __hip_atomic_store(&heavy->wait, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         WavePush push;
         push.hot_keys = hot;
-        for (uint32_t j0 = c * chunk; j0 < end; j0 += blockDim.x) {  // uniform trip count
+        for (uint32_t j0 = c * chunk; j0 < end; j0 += kJoinBlock) {  // uniform trip count
             const uint32_t j = j0 + threadIdx.x;
             int32_t k = 0;
             if (j < end) k = key_of(rt[pp.r_off + j]);
-            const uint64_t s = push.claim(region, j < end, k, j, region_slot(k, step.H), step,
-                                          seen + threadIdx.x / kWave * WavePush::kSeen);
+            const uint64_t s = push.claim(region, j < end, k, j, region_slot(k, step.H), step, seen);
             push.add(region, next, s, k, j);
         }
-        push.flush_block<kWaves>(region, next, runs);
+        push.flush_block<kJoinWaves>(region, next, runs);
+        await_memory();
+        __syncthreads();
+        if (threadIdx.x == 0) {  // (every wave's stores have reached this XCD's L2)
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            atomicAdd(&B.words[2], 1u);
+        }
+        // (and thread 0's branch here stays apart from the next claim's: joined
+        // into one, thread 0 would stay behind while its wave went to the barrier)
+        __syncthreads();
     }
+    if (!wait) return;
+    if (threadIdx.x == 0) {
+        uint32_t polls = 0;
+        while (__hip_atomic_load(&B.words[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < nitems) {
+            if (++polls > 8 * kMaxStatusPolls) {  // (cannot happen; the launch ends all the same)
+                atomicOr((unsigned long long*)B.err, (unsigned long long)kErrLookback);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(8);
+        }
+    }
+    if (threadIdx.x < kWave) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    __syncthreads();
 }
 
 constexpr uint32_t kSU = kSubJ / kWave;  // S tuples per lane of a probe round
 
 static_assert(kRptLarge * kJoinBlock == kMaxLdsCap, "largest build covers kMaxLdsCap");
 
-// Heads of the LDS table for n tuples: the largest power of two <= max(64, n)
-// (chains of one tuple on average).
-__device__ __forceinline__ uint32_t table_log2H(uint32_t n) {
-    const uint32_t v = n < 64 ? 64u : n;
-    return 31u - (uint32_t)__clz(v);
-}
-
 // Strided columns of the heavy-key scans (hj_heavy.h) over partitioned tuples.
 typedef Column<2> TupleColumn;
 __device__ __forceinline__ TupleColumn key_column(const Tuple* t) { return TupleColumn{reinterpret_cast<const int32_t*>(t)}; }
 __device__ __forceinline__ TupleColumn rid_column(const Tuple* t) { return TupleColumn{reinterpret_cast<const int32_t*>(t) + 1}; }
 
-// R_i's keys of this thread, n <= RPT * kJoinBlock.  Plain loads: every S
-// chunk (work item) of a partition reads R_i again, and the rids of its
-// matches come from the same lines.
+// R_i's tuples of this thread, 1 <= n <= RPT * kJoinBlock (rows past n: the last).
+// Plain loads: every S chunk (work item) of a partition reads R_i again.
 template <uint32_t RPT>
-__device__ __forceinline__ void load_r(const Tuple* __restrict__ rt, uint32_t n, int32_t* k) {
+__device__ __forceinline__ void load_r(const Tuple* __restrict__ rt, uint32_t n, int32_t* k, int32_t* rid) {
 #pragma unroll
     for (uint32_t u = 0; u < RPT; ++u) {
-        const uint32_t j = u * kJoinBlock + threadIdx.x;
-        k[u] = j < n ? key_of(rt[j]) : 0;
+        const Tuple t = rt[min(u * kJoinBlock + threadIdx.x, n - 1)];
+        k[u] = key_of(t);
+        rid[u] = rid_of(t);
     }
 }
-// The same from a key column (direct joins).
+// The same from two columns (direct joins).
 template <uint32_t RPT>
-__device__ __forceinline__ void load_r(const int32_t* __restrict__ rk, uint32_t n, int32_t* k) {
+__device__ __forceinline__ void load_r(const int32_t* __restrict__ rk, const int32_t* __restrict__ rr, uint32_t n,
+                                       int32_t* k, int32_t* rid) {
 #pragma unroll
     for (uint32_t u = 0; u < RPT; ++u) {
-        const uint32_t j = u * kJoinBlock + threadIdx.x;
-        k[u] = j < n ? rk[j] : 0;
+        const uint32_t j = min(u * kJoinBlock + threadIdx.x, n - 1);
+        k[u] = rk[j];
+        rid[u] = rr[j];
     }
 }
 
-// LDS table of a work item: one 64-bit record per R_i tuple at its row j --
-// the key and the link to the next row of its bucket's chain -- and the chain
-// heads (the paper's bucket header + key list of Section 3.1, with row
-// indices in place of pointers).  The rid list stays in HBM: a match's rid is
-// read from R_i's rid column at its row when the pair is written.  Layout:
-//   heads[cap + 64] | spare[64] | rec[cap] (uint64: key | next << 32)
-constexpr uint32_t kChainEnd = 0xFFFFFFFFu;
-struct LdsView {
+// LDS table of a work item: chain heads, one 32-bit record per R_i tuple at its
+// row j -- what the bucket does not say of its key, and the link to the next row
+// of the bucket's chain -- and its rid (the paper's bucket header, key list and
+// rid list of Section 3.1, with row indices in place of pointers).
+// A key is told by its radix hash (a bijection of the key).  Its low bits are
+// the same in all of a partition; the high 32 - bits are mixed (again a
+// bijection), the top log2H mixed bits are the bucket and the others, shifted
+// to the top, the record's part: two keys of a bucket are equal exactly when
+// those are.  A record's low link_bits are free for the link, as
+// bits + log2H >= link_bits (table_shape).
+// Layout: heads[H] | rec[cap + 128] | rid[cap + 128] (write); row cap ends every
+// chain (its own link is cap), rows cap + 64 .. cap + 127 take what has no row.
+// Against 64-bit records (key, link) with the rids read from HBM for matches
+// the 16M x 16M one-pass write went from 94 to 91 us.
+struct TableShape {
+    uint32_t log2H, link_bits;
+};
+__host__ __device__ inline TableShape table_shape(uint32_t cap, uint32_t bits) {
+    uint32_t l = 6;  // floor(log2(cap)), cap >= 64
+    while ((2u << l) <= cap) ++l;
+    return TableShape{bits ? l : l + 1, l + 1};  // rows 0 .. cap fit l + 1 bits
+}
+
+struct LdsTable {
     uint32_t* heads;
-    uint32_t* spare;
-    uint64_t* rec;
+    uint32_t* rec;
+    uint32_t* rid;
+    uint32_t cap, log2H, link_mask;
+    uint32_t keep;  // the radix-hash bits above the partition's
 };
 
-__device__ __forceinline__ LdsView lds_view(uint32_t* lds, uint32_t cap) {
-    LdsView v;
+__device__ __forceinline__ LdsTable lds_table(uint32_t* lds, uint32_t cap, uint32_t bits) {
+    const TableShape t = table_shape(cap, bits);
+    LdsTable v;
     v.heads = lds;
-    v.spare = lds + cap + kWave;
-    v.rec = (uint64_t*)(v.spare + kWave);  // 8-byte aligned: cap is a multiple of 64
+    v.rec = lds + (1u << t.log2H);
+    v.rid = v.rec + cap + 2 * kWave;
+    v.cap = cap;
+    v.log2H = t.log2H;
+    v.link_mask = (1u << t.link_bits) - 1u;
+    v.keep = ~0u << bits;  // (bits <= 20)
     return v;
 }
 
-__device__ __forceinline__ int32_t rec_key(uint64_t r) { return (int32_t)(uint32_t)r; }
-__device__ __forceinline__ uint32_t rec_next(uint64_t r) { return (uint32_t)(r >> 32); }
+// The mixed bits of a key: bucket in the top log2H, then the record's part.
+template <uint32_t kHash>
+__device__ __forceinline__ uint32_t mixed(const LdsTable& v, int32_t key) {
+    uint32_t h = (radix_hash(key, kHash) & v.keep) * 0x9E3779B1u;  // odd factors and a right shift
+    h ^= (h >> 15) & v.keep;                                       // within the kept bits: a bijection
+    return h * 0x85EBCA6Bu;
+}
 
-// Builds the table over the n <= RPT * kJoinBlock keys held in registers: b1-b2
+// Builds the table over the n <= RPT * kJoinBlock tuples held in registers: b1-b2
 // bucket of the key, b3-b4 the tuple is pushed on its bucket's chain with one
 // LDS exchange (the latch of Section 3.3 is the exchange itself) and its record
-// stored at its row.  Rounds past n are skipped as a whole (n is uniform over
-// the block); inside a round, lanes past n exchange on a private spare word so
-// the round's exchanges are issued without branches.
-template <uint32_t RPT>
-__device__ __forceinline__ void build_lds(const int32_t* k, uint32_t n, uint32_t log2H, const LdsView& v) {
-    const uint32_t H = 1u << log2H;
-    const uint32_t sh = 32 - log2H;
-    for (uint32_t x = threadIdx.x; x < H; x += kJoinBlock) v.heads[x] = kChainEnd;
+// stored at its row.  kGroup rounds at a time (those past n are skipped as a
+// whole, n is uniform over the block) without branches between their exchanges:
+// a lane past n exchanges on a spare row.
+template <uint32_t RPT, uint32_t kHash, bool kRids>
+__device__ __forceinline__ void build_lds(const int32_t* k, const int32_t* rid, uint32_t n, const LdsTable& v) {
+    constexpr uint32_t kGroup = RPT % 4 == 0 ? 4 : 3;
+    static_assert(RPT % kGroup == 0, "whole groups");
+    uint4* heads = reinterpret_cast<uint4*>(v.heads);
+    for (uint32_t x = threadIdx.x; x < (1u << v.log2H) / 4; x += kJoinBlock)
+        heads[x] = make_uint4(v.cap, v.cap, v.cap, v.cap);
+    if (threadIdx.x == 0) v.rec[v.cap] = v.cap;
     __syncthreads();
+    const uint32_t sh = 32 - v.log2H;
+    const uint32_t spare = v.cap + kWave + lane_id();
 #pragma unroll
-    for (uint32_t u = 0; u < RPT; ++u) {
-        if (u * kJoinBlock < n) {
-            const uint32_t j = u * kJoinBlock + threadIdx.x;
-            const uint32_t b = slot_hash(k[u]) >> sh;
-            const uint32_t old = atomicExch(j < n ? &v.heads[b] : &v.spare[lane_id()], j);
-            if (j < n) v.rec[j] = (uint64_t)(uint32_t)k[u] | ((uint64_t)old << 32);
+    for (uint32_t u0 = 0; u0 < RPT; u0 += kGroup) {
+        if (u0 * kJoinBlock < n) {
+            uint32_t m[kGroup], old[kGroup];
+#pragma unroll
+            for (uint32_t g = 0; g < kGroup; ++g) {
+                const uint32_t j = (u0 + g) * kJoinBlock + threadIdx.x;
+                m[g] = mixed<kHash>(v, k[u0 + g]);
+                old[g] = atomicExch(j < n ? &v.heads[m[g] >> sh] : &v.rec[spare], j);
+            }
+#pragma unroll
+            for (uint32_t g = 0; g < kGroup; ++g) {
+                const uint32_t j = (u0 + g) * kJoinBlock + threadIdx.x;
+                const uint32_t at = j < n ? j : spare;
+                v.rec[at] = (m[g] << v.log2H) | old[g];
+                if (kRids) v.rid[at] = (uint32_t)rid[u0 + g];
+            }
         }
     }
     __syncthreads();
 }
-
-struct ItemLoc {
-    uint32_t item;
-    bool live;
-    uint32_t r_off, r_len;
-    uint32_t s_begin, s_n;
-};
 
 // The work item of this workgroup, one dependent load (the plan writes the
 // records past the last item empty; an item has at least one S tuple).
@@ -216,64 +291,69 @@ __device__ __forceinline__ ItemLoc locate_item(const ItemRec* __restrict__ item_
     return L;
 }
 
-// S keys and rids of this lane for the wave's range [wb, we) of the item
-// (kNt: non-temporal loads, for large joins; see kNtMinTuples).
+// S keys and rids of this lane for the wave's range of the item from wb on,
+// of the item's s_n >= 1 tuples.  Lanes past the end load the last tuple again:
+// behind a branch each load would be awaited on its own (kNt: non-temporal loads, for large joins; see kNtMinTuples).
 template <bool kNt>
-__device__ __forceinline__ void load_s(const Tuple* __restrict__ st, uint32_t wb, uint32_t we, int32_t* q,
+__device__ __forceinline__ void load_s(const Tuple* __restrict__ st, uint32_t wb, uint32_t s_n, int32_t* q,
                                        int32_t* qr) {
 #pragma unroll
     for (uint32_t u = 0; u < kSU; ++u) {
         const uint32_t j = wb + u * kWave + lane_id();
-        const uint64_t t = j < we ? (kNt ? __builtin_nontemporal_load(st + j) : st[j]) : 0ull;
+        const Tuple* a = st + min(j, s_n - 1);
+        const uint64_t t = kNt ? __builtin_nontemporal_load(a) : *a;
         q[u] = key_of(t);
         qr[u] = rid_of(t);
     }
 }
 // The same from two columns (direct joins).
 __device__ __forceinline__ void load_s(const int32_t* __restrict__ skp, const int32_t* __restrict__ srp, uint32_t wb,
-                                       uint32_t we, int32_t* q, int32_t* qr) {
+                                       uint32_t s_n, int32_t* q, int32_t* qr) {
 #pragma unroll
     for (uint32_t u = 0; u < kSU; ++u) {
         const uint32_t j = wb + u * kWave + lane_id();
-        q[u] = j < we ? skp[j] : 0;
-        qr[u] = j < we ? srp[j] : 0;
+        const uint32_t i = min(j, s_n - 1);
+        q[u] = skp[i];
+        qr[u] = srp[i];
     }
 }
 
 // p1-p4 for the lane's kSU S keys against the LDS table, without branches per
 // key: the chain heads of all keys are read first, then the chains are walked
-// in lockstep (each step reads the current record -- key and link -- for every
-// key whose chain has not ended, at a clamped address), so each step keeps kSU
-// LDS reads in flight and a wave runs only as many steps as its longest chain.
-// cf[u] = matches | first << 16 (16-bit halves: cap < 2^16), first = row of
-// the first match met (meaningful when there is one).
-__device__ __forceinline__ void probe_lds(const LdsView& v, uint32_t log2H, const int32_t* q, uint32_t wb,
-                                          uint32_t we, uint32_t* cf) {
-    const uint32_t sh = 32 - log2H;
+// in lockstep (each step reads the current record of every key; an ended chain
+// stays at row cap), so each step keeps kSU LDS reads in flight and a wave runs
+// only as many steps as its longest chain.
+// cf[u] = matches | first << 16 (16-bit halves: rows < 2^16), first = row of
+// the first match met (cap when there is none).  m[u] becomes the record's part
+// of the key.
+template <uint32_t kHash>
+__device__ __forceinline__ void probe_lds(const LdsTable& v, const int32_t* q, uint32_t wb, uint32_t we, uint32_t* m,
+                                          uint32_t* cf) {
     uint32_t h[kSU];
 #pragma unroll
     for (uint32_t u = 0; u < kSU; ++u) {
         const bool ok = wb + u * kWave + lane_id() < we;
-        const uint32_t head = v.heads[slot_hash(q[u]) >> sh];
-        h[u] = ok ? head : kChainEnd;
-        cf[u] = 0;
+        m[u] = mixed<kHash>(v, q[u]);
+        const uint32_t head = v.heads[m[u] >> (32 - v.log2H)];
+        h[u] = ok ? head : v.cap;
+        m[u] <<= v.log2H;
+        cf[u] = v.cap << 16;
     }
     while (true) {
         bool live = false;
 #pragma unroll
-        for (uint32_t u = 0; u < kSU; ++u) live |= h[u] != kChainEnd;
+        for (uint32_t u = 0; u < kSU; ++u) live |= h[u] != v.cap;
         if (__ballot(live) == 0) break;
-        uint64_t rc[kSU];
+        uint32_t rc[kSU];
 #pragma unroll
-        for (uint32_t u = 0; u < kSU; ++u) rc[u] = v.rec[h[u] != kChainEnd ? h[u] : 0u];
+        for (uint32_t u = 0; u < kSU; ++u) rc[u] = v.rec[h[u]];
         __builtin_amdgcn_sched_barrier(0);  // keep the step's reads together, in flight at once
 #pragma unroll
         for (uint32_t u = 0; u < kSU; ++u) {
-            const bool on = h[u] != kChainEnd;
-            const bool hit = on && rec_key(rc[u]) == q[u];
-            const uint32_t first = (cf[u] & 0xFFFFu) == 0 ? h[u] << 16 : cf[u] & 0xFFFF0000u;
-            cf[u] = hit ? first | ((cf[u] & 0xFFFFu) + 1u) : cf[u];
-            h[u] = on ? rec_next(rc[u]) : kChainEnd;
+            const bool hit = (rc[u] ^ m[u]) <= v.link_mask && h[u] != v.cap;
+            const uint32_t first = (cf[u] & 0xFFFFu) == 0 ? h[u] << 16 : cf[u];
+            cf[u] = hit ? (first & 0xFFFF0000u) | ((cf[u] & 0xFFFFu) + 1u) : cf[u];
+            h[u] = rc[u] & v.link_mask;
         }
     }
 }
@@ -311,30 +391,20 @@ __device__ __forceinline__ void probe_hbm(const uint64_t* __restrict__ region, c
     }
 }
 
-// Writes the c >= 1 matches of `key` to o_r/o_s[p ...], slots below `room`
-// only (o_r, o_s and room are the wave's output window: uniform base pointers
-// and the capacity left there).  The first match is at row `first` and its
-// rid, rid0, was fetched already; further matches follow the chain and read
-// their rids from R_i's rid column `rrp`.
-template <typename Rids>
-__device__ __forceinline__ void write_lds_matches(const LdsView& v, Rids rrp, int32_t key,
-                                                  int32_t rs, uint32_t first, int32_t rid0, uint32_t c, uint32_t p,
-                                                  uint32_t room, int32_t* __restrict__ o_r,
-                                                  int32_t* __restrict__ o_s) {
-    if (p < room) {
-        o_r[p] = rid0;
-        o_s[p] = rs;
-    }
-    if (c == 1) return;
-    ++p;
-    for (uint32_t x = rec_next(v.rec[first]); x != kChainEnd; x = rec_next(v.rec[x])) {
-        if (rec_key(v.rec[x]) == key) {
+// Writes the matches after the first of an S tuple (m: the record's part of its
+// key, `first` the first match's row) to o_r/o_s[p ...], slots below `room` only.
+__device__ __forceinline__ void write_more(const LdsTable& v, uint32_t m, int32_t rs, uint32_t first, uint32_t p,
+                                           uint32_t room, int32_t* __restrict__ o_r, int32_t* __restrict__ o_s) {
+    for (uint32_t x = v.rec[first] & v.link_mask; x != v.cap;) {
+        const uint32_t r = v.rec[x];
+        if ((r ^ m) <= v.link_mask) {
             if (p < room) {
-                o_r[p] = rrp[x];
+                o_r[p] = (int32_t)v.rid[x];
                 o_s[p] = rs;
             }
             ++p;
         }
+        x = r & v.link_mask;
     }
 }
 
@@ -382,34 +452,33 @@ __device__ __forceinline__ uint32_t lane_pairs_lds(const uint32_t* cf) {
 // by match counts); returns the slot after the wave's last pair.  LDS table.
 // A round of a wave has fewer than 2^32 pairs (kSubJ keys x kMaxLdsCap
 // matches), so slots are 32-bit offsets from the wave's uniform base.
-template <typename Rids>
-__device__ __forceinline__ uint64_t write_round_lds(const LdsView& v, Rids rrp,
-                                                    const int32_t* q, const int32_t* qr, const uint32_t* cf,
-                                                    const int32_t* rid0, uint64_t pos0, uint64_t capacity,
+__device__ __forceinline__ uint64_t write_round_lds(const LdsTable& v, const uint32_t* m, const int32_t* qr,
+                                                    const uint32_t* cf, uint64_t pos0, uint64_t capacity,
                                                     int32_t* __restrict__ out_r, int32_t* __restrict__ out_s) {
     pos0 = uniform64(pos0);
     const uint64_t left = capacity > pos0 ? capacity - pos0 : 0ull;
     const uint32_t room = left > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)left;
     int32_t* __restrict__ o_r = out_r + pos0;
     int32_t* __restrict__ o_s = out_s + pos0;
+    int32_t rid0[kSU];  // (row cap + 64 .. hold no rid, but are readable: no branch)
+#pragma unroll
+    for (uint32_t u = 0; u < kSU; ++u) rid0[u] = (int32_t)v.rid[cf[u] >> 16];
     uint32_t done = 0;  // pairs of the wave written so far
 #pragma unroll
     for (uint32_t u = 0; u < kSU; ++u) {
         const uint32_t c = cf[u] & 0xFFFFu;
         uint32_t excl, wtotal;
         wave_offsets32(c, &excl, &wtotal);
-        if (c) write_lds_matches(v, rrp, q[u], qr[u], cf[u] >> 16, rid0[u], c, done + excl, room, o_r, o_s);
+        const uint32_t p = done + excl;
+        if (c && p < room) {
+            o_r[p] = rid0[u];
+            o_s[p] = qr[u];
+        }
+        if (wtotal > kWave || __ballot(c > 1))  // uniform: some key has several matches
+            if (c > 1) write_more(v, m[u], qr[u], cf[u] >> 16, p + 1, room, o_r, o_s);
         done += wtotal;
     }
     return pos0 + done;
-}
-
-// Rids of the first matches (issued right after the probe, so the loads are in
-// flight during the output reservation).
-template <typename Rids>
-__device__ __forceinline__ void fetch_first_rids(Rids rrp, const uint32_t* cf, int32_t* rid0) {
-#pragma unroll
-    for (uint32_t u = 0; u < kSU; ++u) rid0[u] = (cf[u] & 0xFFFFu) ? rrp[cf[u] >> 16] : 0;
 }
 
 // The same for the partition-local HBM table: c[u] matches on the row chain
@@ -450,8 +519,7 @@ __device__ __forceinline__ uint64_t write_round_hbm(const uint32_t* __restrict__
 
 // Count pass over a partition whose R exceeds the LDS table: probes the
 // partition-local HBM table and returns this lane's pair count.  hs takes the
-// LDS the table would have used.  Inlined: a call would give the kernel a
-// stack, and the LDS path measured a few percent slower with one.
+// LDS the table would have used.
 __device__ __forceinline__ uint64_t join_count_hbm(const ItemLoc L, uint32_t w, const Tuple* __restrict__ rt,
                                                    const Tuple* __restrict__ stp,
                                                    const uint64_t* __restrict__ ovf_table,
@@ -463,7 +531,7 @@ __device__ __forceinline__ uint64_t join_count_hbm(const ItemLoc L, uint32_t w, 
     load_hot(hot, sh->hk, sh->hr, &sh->nhk);  // read after the round's barrier
     for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
         const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-        load_s<false>(stp, wb, we, q, qr);
+        load_s<false>(stp, wb, L.s_n, q, qr);
         if (threadIdx.x == 0) hs->n = 0;
         __syncthreads();
         uint32_t c[kSU], at[kSU];
@@ -477,49 +545,48 @@ __device__ __forceinline__ uint64_t join_count_hbm(const ItemLoc L, uint32_t w, 
     return cnt;
 }
 
-template <uint32_t RPT, bool kNt>
-__global__ void __launch_bounds__(kJoinBlock) k_join_count(const ItemRec* __restrict__ item_rec,
+template <uint32_t RPT, bool kNt, uint32_t kHash>
+__global__ void __launch_bounds__(kJoinBlock) __attribute__((amdgpu_waves_per_eu(6))) k_join_count(const ItemRec* __restrict__ item_rec,
                                                           const Tuple* __restrict__ rt,
                                                           const Tuple* __restrict__ st, uint32_t lds_cap,
-                                                          const uint64_t* __restrict__ ovf_table,
-                                                          const uint32_t* __restrict__ ovf_next,
-                                                          const HotKeys* __restrict__ hot,
-                                                          uint64_t* __restrict__ wave_cnt) {
+                                                          uint32_t bits, uint64_t* ovf_table, uint32_t* ovf_next,
+                                                          HotKeys* hot, uint64_t* __restrict__ wave_cnt, OvfBuild B) {
     extern __shared__ uint32_t lds[];
     const uint32_t w = threadIdx.x / kWave;
     const uint32_t lane = lane_id();
     const ItemLoc L = locate_item(item_rec);
-    if (!L.live) {
-        if (lane == 0) wave_cnt[(uint64_t)L.item * kJoinWaves + w] = 0;
-        return;
-    }
+    const uint32_t novf = *B.total;  // uniform
     const Tuple* __restrict__ stp = st + L.s_begin;
+    const bool mine = novf && L.live && L.r_len > lds_cap;  // uniform
+    if (mine || blockIdx.x < novf) {
+        build_tables(B, rt, ovf_table, ovf_next, hot, nullptr, novf, mine, lds);
+        __syncthreads();
+    }
     uint64_t cnt = 0;
-    int32_t q[kSU], qr[kSU];
-    if (L.r_len <= lds_cap) {
-        int32_t k[RPT];
-        load_r<RPT>(rt + L.r_off, L.r_len, k);
-        load_s<kNt>(stp, w * kSubJ, min(w * kSubJ + kSubJ, L.s_n), q, qr);
-        const LdsView v = lds_view(lds, lds_cap);
-        const uint32_t log2H = table_log2H(L.r_len);
-        build_lds<RPT>(k, L.r_len, log2H, v);
+    if (L.live && L.r_len <= lds_cap) {
+        int32_t q[kSU], qr[kSU];
+        int32_t k[RPT], rid[RPT];
+        load_r<RPT>(rt + L.r_off, L.r_len, k, rid);
+        load_s<kNt>(stp, w * kSubJ, L.s_n, q, qr);
+        const LdsTable v = lds_table(lds, lds_cap, bits);
+        build_lds<RPT, kHash, false>(k, rid, L.r_len, v);
         for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
             const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-            if (sb) load_s<kNt>(stp, wb, we, q, qr);
-            uint32_t cf[kSU];
-            probe_lds(v, log2H, q, wb, we, cf);
+            if (sb) load_s<kNt>(stp, wb, L.s_n, q, qr);
+            uint32_t m[kSU], cf[kSU];
+            probe_lds<kHash>(v, q, wb, we, m, cf);
             cnt += lane_pairs_lds(cf);
         }
-    } else {
-        cnt = join_count_hbm(L, w, rt, stp, ovf_table, ovf_next, hot, reinterpret_cast<HbmLds*>(lds));
+        cnt = wave_sum(cnt);
     }
-    cnt = wave_sum(cnt);
+    if (mine)
+        cnt = wave_sum(join_count_hbm(L, w, rt, stp, ovf_table, ovf_next, hot, reinterpret_cast<HbmLds*>(lds)));
     if (lane == 0) wave_cnt[(uint64_t)L.item * kJoinWaves + w] = cnt;
 }
 
 // Write pass over a partition whose R exceeds the LDS table (see
 // join_count_hbm).  One-pass output with `heavy`: a heavy S tuple of a
-// partition that spans more than one kHelpChunk-row chunk is registered after
+// partition of more than kQueueRows rows is registered after
 // a walk of at most kQueueWalk rows (none for a recorded hot key) and handed
 // to the device-wide queue, whose chunks every workgroup of the launch helps
 // write (help_heavy); tuples the queue has no room for stay with this
@@ -535,13 +602,13 @@ __device__ __forceinline__ void join_write_hbm(
     const uint64_t* __restrict__ region = ovf_table + 2ull * L.r_off;
     const uint32_t* __restrict__ next = ovf_next + L.r_off;
     const TupleColumn rkp = key_column(rt + L.r_off), rrp = rid_column(rt + L.r_off);
-    const bool queue = kOnePass && heavy && L.r_len > kHelpChunk;  // uniform
+    const bool queue = kOnePass && heavy && L.r_len > kQueueRows;  // uniform
     const uint32_t lim = queue ? min(heavy_limit(L.r_len), kQueueWalk) : heavy_limit(L.r_len);
     int32_t q[kSU], qr[kSU];
     load_hot(hot, sh->hk, sh->hr, &sh->nhk);  // read after the round's barrier
     for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
         const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-        load_s<false>(stp, wb, we, q, qr);
+        load_s<false>(stp, wb, L.s_n, q, qr);
         if (threadIdx.x == 0) hs->n = hs->queued = 0;
         __syncthreads();
         uint32_t c[kSU], at[kSU];
@@ -558,41 +625,6 @@ __device__ __forceinline__ void join_write_hbm(
     }
 }
 
-// The pairs of one work item (R_i in an LDS table, or its HBM table).
-template <bool kOnePass, uint32_t RPT, bool kNt>
-__device__ __forceinline__ void write_item(const ItemLoc L, uint32_t w, uint32_t* lds, uint64_t* wtot,
-                                           const Tuple* __restrict__ rt, const Tuple* __restrict__ st,
-                                           uint32_t lds_cap, const uint64_t* __restrict__ ovf_table,
-                                           const uint32_t* __restrict__ ovf_next, const HotKeys* hot,
-                                           uint64_t base, unsigned long long* __restrict__ total,
-                                           int32_t* __restrict__ out_r, int32_t* __restrict__ out_s,
-                                           uint64_t capacity, HeavyQueue* heavy) {
-    const Tuple* __restrict__ stp = st + L.s_begin;
-    int32_t q[kSU], qr[kSU];
-    if (L.r_len <= lds_cap) {
-        const TupleColumn rrp = rid_column(rt + L.r_off);
-        int32_t k[RPT];
-        load_r<RPT>(rt + L.r_off, L.r_len, k);
-        load_s<kNt>(stp, w * kSubJ, min(w * kSubJ + kSubJ, L.s_n), q, qr);
-        const LdsView v = lds_view(lds, lds_cap);
-        const uint32_t log2H = table_log2H(L.r_len);
-        build_lds<RPT>(k, L.r_len, log2H, v);
-        for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
-            const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-            if (sb) load_s<kNt>(stp, wb, we, q, qr);
-            uint32_t cf[kSU];
-            int32_t rid0[kSU];
-            probe_lds(v, log2H, q, wb, we, cf);
-            fetch_first_rids(rrp, cf, rid0);
-            const uint64_t pos0 = kOnePass ? block_reserve(lane_pairs_lds(cf), total, wtot, sb != 0) : base;
-            base = write_round_lds(v, rrp, q, qr, cf, rid0, pos0, capacity, out_r, out_s);
-        }
-    } else {
-        join_write_hbm<kOnePass>(L, w, rt, stp, ovf_table, ovf_next, hot, base, total, wtot, out_r, out_s, capacity,
-                                 reinterpret_cast<HbmLds*>(lds), heavy);
-    }
-}
-
 // Polls of the item count by a helper workgroup before it leaves anyway (its
 // help is only a speed-up: every queued chunk is also taken by the workgroup
 // that queued it).
@@ -600,66 +632,119 @@ constexpr uint32_t kHelpWaitPolls = 1u << 20;
 constexpr uint32_t kMaxHelpers = 256;
 
 // A helper's loop: help with the queued tuples until the items the build
-// counted are done.  Not inlined: inside the write kernel its registers cost
-// the item path 6-10 us at 16M x 16M (measured), while as a call they do not.
-__device__ __attribute__((noinline)) void help_until_done(HeavyQueue* heavy, const Tuple* rt,
+// counted are done.
+__device__ __forceinline__ void help_until_done(HeavyQueue* heavy, const Tuple* rt,
                                                          unsigned long long* total, uint64_t capacity, int32_t* out_r,
                                                          int32_t* out_s, uint32_t* lds, uint32_t* s_word) {
-    const uint32_t expected = heavy->items_expected;
+    const uint32_t expected =
+        uniform(__hip_atomic_load(&heavy->items_expected, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     for (uint32_t polls = 0;; ++polls) {
         __syncthreads();
         if (threadIdx.x == 0)
             *s_word = __hip_atomic_load(&heavy->items_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        const bool all_done = *s_word >= expected;
-        help_heavy<kJoinBlock>(heavy, key_column(rt), rid_column(rt), total, capacity, out_r, out_s, lds);
+        const bool all_done = uniform(*s_word) >= expected;
+        help_heavy<kJoinBlock, kHelpChunkPart>(heavy, key_column(rt), rid_column(rt), total, capacity, out_r, out_s,
+                                               lds);
         if (all_done || polls >= kHelpWaitPolls) break;
         __builtin_amdgcn_s_sleep(32);
     }
 }
 
+struct WriteArgs {
+    const Tuple *rt, *st;
+    uint32_t lds_cap;
+    uint64_t* ovf_table;
+    uint32_t* ovf_next;
+    HotKeys* hot;
+    const uint64_t* wave_base;
+    unsigned long long* total;
+    int32_t *out_r, *out_s;
+    uint64_t capacity;
+    HeavyQueue* heavy;
+    uint32_t item_grid;
+};
+// The part of a write workgroup that HBM tables need (novf != 0): its item if
+// that has such a table and, one-pass, help with the heavy tuples any workgroup
+// queued.  Helpers (`helper`, one-pass) are workgroups past the items: when a
+// partition may queue tuples (heavy->wait, set by the build), the items of such
+// partitions count themselves done and the helpers keep helping until all of
+// them are (the build counted them in items_expected), so that a tuple queued
+// late still finds helpers.  (Counting every item instead cost the write
+// ~0.26 ms at 16M x 16M: thousands of atomics on the queue's line, which every
+// workgroup also reads.)  The helpers are at most half of the workgroups the
+// device holds at once, so items always have room to run, whatever order the
+// workgroups start in.
+template <bool kOnePass>
+__device__ __forceinline__ void write_hbm_part(const ItemLoc& L, bool helper, const WriteArgs& A, uint32_t* lds,
+                                               uint64_t* wtot, uint32_t* s_word) {
+    const bool mine = !helper && L.live && L.r_len > A.lds_cap;  // uniform
+    if (kOnePass && helper) {
+        if (uniform(__hip_atomic_load(&A.heavy->wait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))  // (final by now)
+            help_until_done(A.heavy, A.rt, A.total, A.capacity, A.out_r, A.out_s, lds, s_word);
+        return;
+    }
+    if (mine) {
+        const uint32_t w = threadIdx.x / kWave;
+        join_write_hbm<kOnePass>(L, w, A.rt, A.st + L.s_begin, A.ovf_table, A.ovf_next, A.hot,
+                                 kOnePass ? 0ull : A.wave_base[(uint64_t)L.item * kJoinWaves + w], A.total, wtot,
+                                 A.out_r, A.out_s, A.capacity, reinterpret_cast<HbmLds*>(lds), A.heavy);
+    }
+    if (kOnePass && A.heavy) {
+        if (mine && L.r_len > kQueueRows) {  // an item the helpers wait for (the build counted it)
+            __syncthreads();  // the item's hand-offs are made
+            if (threadIdx.x == 0) atomicAdd(&A.heavy->items_done, 1u);
+        }
+        help_heavy<kJoinBlock, kHelpChunkPart>(A.heavy, key_column(A.rt), rid_column(A.rt), A.total, A.capacity,
+                                               A.out_r, A.out_s, lds);
+    }
+}
+
 // Write pass.  kOnePass: instead of reading a scanned per-wave offset, each
-// probe round reserves its pairs' output slots with block_reserve.  One-pass
-// with `heavy`: every workgroup helps with the queued heavy tuples once its
-// own item is written, and the grid has helper workgroups past item_grid.
-// When the HBM-table build set heavy->wait (a partition may queue tuples), the
-// items of such partitions count themselves done and the helpers keep helping
-// until all of them are (the build counted them in items_expected), so that a
-// tuple queued late still finds helpers; otherwise the helpers leave at once.
-// (Counting every item instead cost the write ~0.26 ms at 16M x 16M: thousands
-// of atomics on the queue's line, which every workgroup also reads.)  The helpers are at most half
-// of the workgroups the device holds at once, so items always have room to
-// run, whatever order the workgroups start in.
-template <bool kOnePass, uint32_t RPT, bool kNt>
+// probe round reserves its pairs' output slots with block_reserve.
+template <bool kOnePass, uint32_t RPT, bool kNt, uint32_t kHash>
 __global__ void __launch_bounds__(kJoinBlock) __attribute__((amdgpu_waves_per_eu(RPT > kRptMid ? 4 : 6)))
-k_join_write(
-    const ItemRec* __restrict__ item_rec, const Tuple* __restrict__ rt, const Tuple* __restrict__ st, uint32_t lds_cap, const uint64_t* __restrict__ ovf_table,
-    const uint32_t* __restrict__ ovf_next, const HotKeys* __restrict__ hot, const uint64_t* __restrict__ wave_base,
-    unsigned long long* __restrict__ total, int32_t* __restrict__ out_r, int32_t* __restrict__ out_s,
-    uint64_t capacity, HeavyQueue* heavy, uint32_t item_grid) {
+k_join_write(const ItemRec* __restrict__ item_rec, uint32_t bits, WriteArgs A, OvfBuild B) {
     extern __shared__ uint32_t lds[];
     __shared__ uint64_t wtot[kJoinWaves + 1];
     __shared__ uint32_t s_word;
     const uint32_t w = threadIdx.x / kWave;
-    if (kOnePass && heavy && blockIdx.x >= item_grid) {  // a helper
-        if (!heavy->wait) return;  // written by an earlier launch: uniform
-        help_until_done(heavy, rt, total, capacity, out_r, out_s, lds, &s_word);
-        return;
+    const uint32_t novf = *B.total;  // uniform: build items of HBM tables
+    const bool helper = kOnePass && blockIdx.x >= A.item_grid;
+    if (helper && !novf) return;
+    ItemLoc L{};
+    if (!helper) {
+        L = locate_item(item_rec);
     }
-    const ItemLoc L = locate_item(item_rec);
-    if (!L.live) return;
-    const uint32_t item = L.item;
-    const uint64_t base = kOnePass ? 0ull : wave_base[(uint64_t)item * kJoinWaves + w];
-    write_item<kOnePass, RPT, kNt>(L, w, lds, wtot, rt, st, lds_cap, ovf_table, ovf_next, hot, base, total, out_r, out_s,
-                                   capacity, heavy);
-    // one-pass: help with the heavy tuples any workgroup queued (the LDS
-    // tables are free now and give the scratch)
-    if (kOnePass && heavy) {
-        if (L.r_len > kHelpChunk) {  // an item the helpers wait for (the build counted it)
-            __syncthreads();  // the item's hand-offs are made
-            if (threadIdx.x == 0) atomicAdd(&heavy->items_done, 1u);
+    if (kOnePass && novf) {
+        const bool wait = helper || (L.live && L.r_len > A.lds_cap);  // uniform
+        if (wait || blockIdx.x < novf) {
+            build_tables(B, A.rt, A.ovf_table, A.ovf_next, A.hot, A.heavy, novf, wait, lds);
+            __syncthreads();
         }
-        help_heavy<kJoinBlock>(heavy, key_column(rt), rid_column(rt), total, capacity, out_r, out_s, lds);
+    }
+    if (!helper) {
+        if (L.live && L.r_len <= A.lds_cap) {
+            const Tuple* __restrict__ stp = A.st + L.s_begin;
+            int32_t q[kSU], qr[kSU], k[RPT], rid[RPT];
+            uint64_t base = kOnePass ? 0ull : A.wave_base[(uint64_t)L.item * kJoinWaves + w];
+            load_r<RPT>(A.rt + L.r_off, L.r_len, k, rid);
+            load_s<kNt>(stp, w * kSubJ, L.s_n, q, qr);
+            const LdsTable v = lds_table(lds, A.lds_cap, bits);
+            build_lds<RPT, kHash, true>(k, rid, L.r_len, v);
+            for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
+                const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
+                if (sb) load_s<kNt>(stp, wb, L.s_n, q, qr);
+                uint32_t m[kSU], cf[kSU];
+                probe_lds<kHash>(v, q, wb, we, m, cf);
+                const uint64_t pos0 = kOnePass ? block_reserve(lane_pairs_lds(cf), A.total, wtot, sb != 0) : base;
+                base = write_round_lds(v, m, qr, cf, pos0, A.capacity, A.out_r, A.out_s);
+            }
+        }
+    }
+    if (novf) {
+        __syncthreads();  // the table is free
+        write_hbm_part<kOnePass>(L, helper, A, lds, wtot, &s_word);
     }
 }
 
@@ -682,23 +767,19 @@ k_direct_join(const DirectJob* __restrict__ jobs,
     const uint32_t r_len = min(J.n_r, lds_cap);  // the planner guarantees n_r <= lds_cap
     const int32_t* __restrict__ skp = J.sk + s_begin;
     const int32_t* __restrict__ srp = J.sr + s_begin;
-    const Column<1> rids{J.rr};
-    int32_t k[RPT];
-    load_r<RPT>(J.rk, r_len, k);
+    int32_t k[RPT], rid[RPT];
+    load_r<RPT>(J.rk, J.rr, r_len, k, rid);
     int32_t q[kSU], qr[kSU];
-    load_s(skp, srp, w * kSubJ, min(w * kSubJ + kSubJ, s_n), q, qr);
-    const LdsView v = lds_view(lds, lds_cap);
-    const uint32_t log2H = table_log2H(r_len);
-    build_lds<RPT>(k, r_len, log2H, v);
+    load_s(skp, srp, w * kSubJ, s_n, q, qr);
+    const LdsTable v = lds_table(lds, lds_cap, 0u);
+    build_lds<RPT, 0, true>(k, rid, r_len, v);
     for (uint32_t sb = 0; sb < s_n; sb += kJoinSub) {
         const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, s_n);
-        if (sb) load_s(skp, srp, wb, we, q, qr);
-        uint32_t cf[kSU];
-        int32_t rid0[kSU];
-        probe_lds(v, log2H, q, wb, we, cf);
-        fetch_first_rids(rids, cf, rid0);
+        if (sb) load_s(skp, srp, wb, s_n, q, qr);
+        uint32_t m[kSU], cf[kSU];
+        probe_lds<0>(v, q, wb, we, m, cf);
         const uint64_t pos0 = block_reserve(lane_pairs_lds(cf), (unsigned long long*)J.count, wtot, sb != 0);
-        write_round_lds(v, rids, q, qr, cf, rid0, pos0, J.capacity, J.out_r, J.out_s);
+        write_round_lds(v, m, qr, cf, pos0, J.capacity, J.out_r, J.out_s);
     }
 }
 
@@ -727,10 +808,11 @@ __global__ void k_write_zero(uint64_t* p, uint64_t* err_clear) {
 
 }  // namespace
 
-size_t join_lds_bytes(uint32_t lds_cap, bool /*write*/) {
-    static_assert(sizeof(HbmLds) <= sizeof(uint32_t) * (256 + 2 * kWave) + sizeof(uint64_t) * 256,
+size_t join_lds_bytes(uint32_t lds_cap, uint32_t bits, bool write) {
+    static_assert(sizeof(HbmLds) <= sizeof(uint32_t) * (256 + 256 + 2 * kWave),
                   "the heavy-key set and the hot keys fit the smallest table area");
-    return sizeof(uint32_t) * ((size_t)lds_cap + 2 * kWave) + sizeof(uint64_t) * lds_cap;
+    const size_t rows = (size_t)lds_cap + 2 * kWave;
+    return sizeof(uint32_t) * (((size_t)1 << table_shape(lds_cap, bits).log2H) + (write ? 2 : 1) * rows);
 }
 
 void direct_setup_one(DirectJob* job, uint32_t* item_job, const DirectJob& j, uint32_t nitems, Recorder& rec) {
@@ -754,7 +836,7 @@ static void allow_lds(const void* fn, size_t lds) {
 template <uint32_t RPT>
 void direct_join_t(const DirectJob* jobs, const uint32_t* item_job, uint32_t nitems, uint32_t lds_cap,
                    Recorder& rec) {
-    const size_t lds = join_lds_bytes(lds_cap, true);
+    const size_t lds = join_lds_bytes(lds_cap, 0, true);
     allow_lds((const void*)k_direct_join<RPT>, lds);
     rec.before("direct_join");
     hipLaunchKernelGGL(k_direct_join<RPT>, dim3(nitems), dim3(kJoinBlock), lds, rec.stream, jobs, item_job,
@@ -790,20 +872,11 @@ uint32_t join_grid(uint32_t P, uint64_t n_s) {
     return (uint32_t)((items + 8 * kItemGroup - 1) / (8 * kItemGroup) * (8 * kItemGroup));  // item_of_block
 }
 
-void join_ovf_build(const PartPair* pairs, const uint32_t* ovf_begin, const uint32_t* ovf_part, uint32_t P,
-                    uint32_t grid, const Tuple* rt, uint64_t* ovf_table, uint32_t* ovf_next, HotKeys* hot,
-                    HeavyQueue* heavy, Recorder& rec, bool clear) {
+void join_ovf_clear(const OvfBuild& b, uint32_t P, uint32_t grid, uint64_t* ovf_table, Recorder& rec) {
     if (grid == 0) return;
     grid = grid < kOvfGrid ? grid : kOvfGrid;  // grid-stride: few chunks in the common case
-    if (clear) {
-        rec.before("ovf_clear");
-        hipLaunchKernelGGL(k_ovf_clear, dim3(grid), dim3(256), 0, rec.stream, pairs, ovf_begin, ovf_part, P,
-                           ovf_table);
-        rec.after();
-    }
-    rec.before("ovf_build");
-    hipLaunchKernelGGL(k_ovf_build, dim3(grid), dim3(256), 0, rec.stream, pairs, ovf_begin, ovf_part, P, rt,
-                       ovf_table, ovf_next, hot, heavy);
+    rec.before("ovf_clear");
+    hipLaunchKernelGGL(k_ovf_clear, dim3(grid), dim3(256), 0, rec.stream, b.pairs, b.begin, b.part, P, ovf_table);
     rec.after();
 }
 
@@ -813,10 +886,11 @@ struct JoinArgs {
     const ItemRec* item_rec;
     uint32_t grid;
     const Tuple *rt, *st;
-    uint32_t lds_cap;
-    const uint64_t* ovf_table;
-    const uint32_t* ovf_next;
-    const HotKeys* hot;
+    uint32_t lds_cap, bits;
+    OvfBuild ovf;
+    uint64_t* ovf_table;
+    uint32_t* ovf_next;
+    HotKeys* hot;
     uint64_t* wave;   // per-wave counts (count), or their scan (write; nullptr: one-pass)
     uint64_t* total;
     int32_t *out_r, *out_s;
@@ -824,20 +898,20 @@ struct JoinArgs {
     HeavyQueue* heavy;
 };
 
-template <uint32_t RPT, bool kNt>
+template <uint32_t RPT, bool kNt, uint32_t kHash>
 void join_count_t(const JoinArgs& a, Recorder& rec) {
-    const size_t lds = join_lds_bytes(a.lds_cap, false);
-    allow_lds((const void*)k_join_count<RPT, kNt>, lds);
+    const size_t lds = join_lds_bytes(a.lds_cap, a.bits, false);
+    allow_lds((const void*)k_join_count<RPT, kNt, kHash>, lds);
     rec.before("join_count");
-    hipLaunchKernelGGL((k_join_count<RPT, kNt>), dim3(a.grid), dim3(kJoinBlock), lds, rec.stream, a.item_rec, a.rt,
-                       a.st, a.lds_cap, a.ovf_table, a.ovf_next, a.hot, a.wave);
+    hipLaunchKernelGGL((k_join_count<RPT, kNt, kHash>), dim3(a.grid), dim3(kJoinBlock), lds, rec.stream, a.item_rec, a.rt,
+                       a.st, a.lds_cap, a.bits, a.ovf_table, a.ovf_next, a.hot, a.wave, a.ovf);
     rec.after();
 }
 
-template <bool kOnePass, uint32_t RPT, bool kNt>
+template <bool kOnePass, uint32_t RPT, bool kNt, uint32_t kHash>
 void join_write_t(const JoinArgs& a, Recorder& rec) {
-    const size_t lds = join_lds_bytes(a.lds_cap, true);
-    allow_lds((const void*)k_join_write<kOnePass, RPT, kNt>, lds);
+    const size_t lds = join_lds_bytes(a.lds_cap, a.bits, true);
+    allow_lds((const void*)k_join_write<kOnePass, RPT, kNt, kHash>, lds);
     rec.before(kOnePass ? "join_write_1pass" : "join_write");
     uint32_t grid = a.grid;
     if (kOnePass && a.heavy) {
@@ -848,55 +922,64 @@ void join_write_t(const JoinArgs& a, Recorder& rec) {
         const uint32_t resident = 256u * std::max(1u, std::min(by_lds, by_waves));
         grid += std::max(1u, std::min(kMaxHelpers, resident / 2));
     }
-    hipLaunchKernelGGL((k_join_write<kOnePass, RPT, kNt>), dim3(grid), dim3(kJoinBlock), lds, rec.stream, a.item_rec,
-                       a.rt, a.st, a.lds_cap, a.ovf_table, a.ovf_next, a.hot, a.wave, (unsigned long long*)a.total,
-                       a.out_r, a.out_s, a.capacity, a.heavy, a.grid);
+    const WriteArgs args{a.rt, a.st, a.lds_cap, a.ovf_table, a.ovf_next, a.hot, a.wave, (unsigned long long*)a.total,
+                         a.out_r, a.out_s, a.capacity, a.heavy, a.grid};
+    hipLaunchKernelGGL((k_join_write<kOnePass, RPT, kNt, kHash>), dim3(grid), dim3(kJoinBlock), lds, rec.stream,
+                       a.item_rec, a.bits, args, a.ovf);
     rec.after();
 }
 
-template <bool kNt>
+template <bool kNt, uint32_t kHash>
 void join_count_n(const JoinArgs& a, Recorder& rec) {
     switch (join_rpt(a.lds_cap)) {
-        case kRptSmall: join_count_t<kRptSmall, kNt>(a, rec); break;
-        case kRptMid: join_count_t<kRptMid, kNt>(a, rec); break;
-        default: join_count_t<kRptLarge, kNt>(a, rec); break;
+        case kRptSmall: join_count_t<kRptSmall, kNt, kHash>(a, rec); break;
+        case kRptMid: join_count_t<kRptMid, kNt, kHash>(a, rec); break;
+        default: join_count_t<kRptLarge, kNt, kHash>(a, rec); break;
+    }
+}
+
+template <bool kOnePass, bool kNt, uint32_t kHash>
+void join_write_n(const JoinArgs& a, Recorder& rec) {
+    switch (join_rpt(a.lds_cap)) {
+        case kRptSmall: join_write_t<kOnePass, kRptSmall, kNt, kHash>(a, rec); break;
+        case kRptMid: join_write_t<kOnePass, kRptMid, kNt, kHash>(a, rec); break;
+        default: join_write_t<kOnePass, kRptLarge, kNt, kHash>(a, rec); break;
     }
 }
 
 template <bool kOnePass, bool kNt>
-void join_write_n(const JoinArgs& a, Recorder& rec) {
-    switch (join_rpt(a.lds_cap)) {
-        case kRptSmall: join_write_t<kOnePass, kRptSmall, kNt>(a, rec); break;
-        case kRptMid: join_write_t<kOnePass, kRptMid, kNt>(a, rec); break;
-        default: join_write_t<kOnePass, kRptLarge, kNt>(a, rec); break;
-    }
+void join_write_h(const JoinArgs& a, uint32_t hash, Recorder& rec) {
+    if (hash) join_write_n<kOnePass, kNt, 1>(a, rec);
+    else join_write_n<kOnePass, kNt, 0>(a, rec);
 }
 
 }  // namespace
 
 void join_count(const ItemRec* item_rec, uint32_t grid, const Tuple* rt, const Tuple* st, uint32_t lds_cap,
-                const uint64_t* ovf_table, const uint32_t* ovf_next, const HotKeys* hot, uint64_t* wave_cnt, bool nt_s,
-                Recorder& rec) {
+                uint32_t bits, uint32_t hash, const OvfBuild& ovf, uint64_t* ovf_table, uint32_t* ovf_next, HotKeys* hot,
+                uint64_t* wave_cnt, bool nt_s, Recorder& rec) {
     if (grid == 0) return;
-    const JoinArgs a{item_rec, grid, rt, st, lds_cap, ovf_table, ovf_next, hot, wave_cnt, nullptr, nullptr, nullptr, 0,
-                     nullptr};
-    if (nt_s) join_count_n<true>(a, rec);
-    else join_count_n<false>(a, rec);
+    const JoinArgs a{item_rec, grid, rt, st, lds_cap, bits, ovf, ovf_table, ovf_next, hot, wave_cnt, nullptr, nullptr,
+                     nullptr, 0, nullptr};
+    if (nt_s && hash) join_count_n<true, 1>(a, rec);
+    else if (nt_s) join_count_n<true, 0>(a, rec);
+    else if (hash) join_count_n<false, 1>(a, rec);
+    else join_count_n<false, 0>(a, rec);
 }
 
 void join_write(const ItemRec* item_rec, uint32_t grid, const Tuple* rt, const Tuple* st, uint32_t lds_cap,
-                const uint64_t* ovf_table, const uint32_t* ovf_next, const HotKeys* hot, const uint64_t* wave_base,
-                uint64_t* total, int32_t* out_r, int32_t* out_s, uint64_t capacity, HeavyQueue* heavy, bool nt_s,
-                Recorder& rec) {
+                uint32_t bits, uint32_t hash, const OvfBuild& ovf, uint64_t* ovf_table, uint32_t* ovf_next, HotKeys* hot,
+                const uint64_t* wave_base, uint64_t* total, int32_t* out_r, int32_t* out_s, uint64_t capacity,
+                HeavyQueue* heavy, bool nt_s, Recorder& rec) {
     if (grid == 0) return;
-    const JoinArgs a{item_rec, grid, rt, st, lds_cap, ovf_table, ovf_next, hot, const_cast<uint64_t*>(wave_base),
-                     total, out_r, out_s, capacity, wave_base ? nullptr : heavy};
+    const JoinArgs a{item_rec, grid, rt, st, lds_cap, bits, ovf, ovf_table, ovf_next, hot,
+                     const_cast<uint64_t*>(wave_base), total, out_r, out_s, capacity, wave_base ? nullptr : heavy};
     if (wave_base) {
-        if (nt_s) join_write_n<false, true>(a, rec);
-        else join_write_n<false, false>(a, rec);
+        if (nt_s) join_write_h<false, true>(a, hash, rec);
+        else join_write_h<false, false>(a, hash, rec);
     } else {
-        if (nt_s) join_write_n<true, true>(a, rec);
-        else join_write_n<true, false>(a, rec);
+        if (nt_s) join_write_h<true, true>(a, hash, rec);
+        else join_write_h<true, false>(a, hash, rec);
     }
 }
 

@@ -177,8 +177,8 @@ __global__ void __launch_bounds__(kShjBlock) __attribute__((amdgpu_waves_per_eu(
     // one-pass: a chain is heavy from kQueueWalk rows on (handed to every workgroup)
     const uint32_t lim = kOnePass ? min(heavy_limit(n_r), kQueueWalk) : heavy_limit(n_r);
     shj_probe<true>(s_key, s_rid, begin, n_s, table, next, nslots, lim, hk, hr, nhk, &hs, q, qr, head, c);
-    // with R in one chunk the queue adds no workgroups to a tuple: keep the block's own scan
-    if (kOnePass && n_r > kHelpChunk) hand_off(heavy, &hs, 0u, (uint32_t)n_r);
+    // with few rows of R the queue adds no workgroups to a tuple in time: keep the block's own scan
+    if (kOnePass && n_r > kQueueRows) hand_off(heavy, &hs, 0u, (uint32_t)n_r);
     heavy_counts<kShjBlock, kHeavyV, kOnePass>(Column<1>{r_key}, n_r, &hs);
     uint64_t pos0;
     if (kOnePass) {
@@ -224,7 +224,7 @@ __global__ void __launch_bounds__(kShjBlock) __attribute__((amdgpu_waves_per_eu(
     }
     heavy_writes<kShjBlock, kHeavyV, true>(Column<1>{r_key}, Column<1>{r_rid}, n_r, &hs, capacity, out_r, out_s);
     if (kOnePass)
-        help_heavy<kShjBlock>(heavy, Column<1>{r_key}, Column<1>{r_rid}, total, capacity, out_r, out_s, hs.wsum);
+        help_heavy<kShjBlock, kHelpChunk>(heavy, Column<1>{r_key}, Column<1>{r_rid}, total, capacity, out_r, out_s, hs.wsum);
 }
 
 __global__ void __launch_bounds__(256) k_zero_one_pass(uint64_t* __restrict__ total, uint64_t* __restrict__ q,

@@ -36,12 +36,15 @@ ROUTES = [
     (1 << 21, (1 << 21) + 1, dict(passes=2, bits=(6, 6))),
     ((1 << 21) - 1, 1 << 21, dict(passes=1, bits=(12,), hash="murmur2")),
     (1 << 21, 1 << 21, dict(passes=1, bits=(13,), tile=8192)),
-    # two scatters: counted by the one histogram from 160 tuples per partition on, else by a second one
+    # two scatters: counted by the one histogram from 400 tuples per partition on, else by a second one
     (400000, 160 * 8192 - 400000, dict(passes=2, bits=(7, 6))),
     (400000, 160 * 8192 - 400001, dict(passes=2, bits=(7, 6))),
     (1 << 20, 2 << 20, dict(passes=2, bits=(7, 7), lds_cap=256, hash="murmur2")),
     (1 << 20, 5 << 20, dict(passes=2, bits=(3, 12))),
     (1 << 20, 1 << 20, dict(passes=2, bits=(9, 6), lds_cap=256)),
+    (1400000, 400 * 8192 - 1400000, dict(passes=2, bits=(7, 6))),  # the line between the two
+    (1400000, 400 * 8192 - 1400001, dict(passes=2, bits=(7, 6))),
+    (1 << 20, 12 << 20, dict(passes=2, bits=(3, 12))),
     (500009, 700001, dict(passes=2, bits=(8, 8))),
 ]
 
