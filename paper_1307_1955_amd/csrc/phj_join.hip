@@ -191,13 +191,19 @@ __device__ __forceinline__ void load_r(const int32_t* __restrict__ rk, const int
 // chain (its own link is cap), rows cap + 64 .. cap + 127 take what has no row.
 // Against 64-bit records (key, link) with the rids read from HBM for matches
 // the 16M x 16M one-pass write went from 94 to 91 us.
+//
+// One bucket per row, or two where three workgroups, as many as the registers
+// of the write allow, still share a CU's LDS: shorter chains took 10M x 12M
+// tuples, 2 rows to a key, from 71 + 143 to 65 + 130 us (count + write).
+constexpr uint32_t kLdsOfThird = 160u * 1024u / 3u - 1536u;
 struct TableShape {
     uint32_t log2H, link_bits;
 };
 __host__ __device__ inline TableShape table_shape(uint32_t cap, uint32_t bits) {
     uint32_t l = 6;  // floor(log2(cap)), cap >= 64
     while ((2u << l) <= cap) ++l;
-    return TableShape{bits ? l : l + 1, l + 1};  // rows 0 .. cap fit l + 1 bits
+    const bool twice = bits == 0 || 4u * ((2u << l) + 2u * (cap + 2u * kWave)) <= kLdsOfThird;
+    return TableShape{twice ? l + 1 : l, l + 1};  // rows 0 .. cap fit l + 1 bits
 }
 
 struct LdsTable {
