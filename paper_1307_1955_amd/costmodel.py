@@ -147,12 +147,10 @@ def launches(plan: dict, n_r: int, n_s: int, m: float) -> list[tuple[str, dict]]
         out.append(("shj_fill", {"bytes": 8.0 * slots}))
         out.append(("shj_build", {"n": n_r, "tb": tb}))
         if plan["one_pass"]:
-            out.append(("zero_count", {}))
             out.append(("shj_write_1pass", {"n": n_s, "tb": tb, "m": m}))
         else:
             tiles = math.ceil(n_s / SHJ_TILE)
             out.append(("shj_count", {"n": n_s, "tb": tb}))
-            out.append(("zero_state", {}))
             out.append(("scan_u64", {"entries": 4 * tiles}))
             out.append(("shj_write", {"n": n_s, "tb": tb, "m": m}))
         return out

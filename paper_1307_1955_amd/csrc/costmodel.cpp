@@ -125,15 +125,13 @@ double model_seconds(const Plan& pl, uint64_t n_r_, uint64_t n_s_, double m) {
         t += d + std::max(n_r * ins, b_floor);     // build
         nl += 2;
         if (pl.one_pass) {
-            t += d;            // zero the count and the queue
             t += d + write_s;  // write
-            nl += 2;
+            nl += 1;
         } else {
             t += d + probe_s;                             // count
-            t += d;                                       // zero the scan state
             t += scan_s(4 * std::ceil(n_s / kShjTileD));  // scan of the per-wave counts
             t += d + write_s;                             // write
-            nl += 4;
+            nl += 3;
         }
         return t + nl * gap;
     }

@@ -420,19 +420,21 @@ hj_status check_call(const hj_params* p, const hj_rel* R, const hj_rel* S, const
 }
 
 // SHJ build (Algorithm 1, b1-b4): empty slots, then R inserted.
-void shj_build_table(const hj_rel& R, const ShjTableWs& t, hj::Recorder& rec) {
-    hj::shj_fill(t.table, t.nslots, t.hot, rec);
+// total, queue: see shj_fill.
+void shj_build_table(const hj_rel& R, const ShjTableWs& t, uint64_t* total, hj::HeavyQueue* queue, hj::Recorder& rec) {
+    hj::shj_fill(t.table, t.nslots, t.hot, total, queue, rec);
     hj::shj_build(R.key, R.n, t.table, t.next, t.nslots, t.hot, R.n >= hj::kNtMinBuild, rec);
 }
 
-// SHJ probe (Algorithm 1, p1-p4) of a table built over R.
+// SHJ probe (Algorithm 1, p1-p4) of a table built over R.  cleared: the one-pass
+// count and queue already are.
 void shj_probe_table(const Plan& pl, const ShjTableWs& t, const hj_rel& R, const hj_rel& S,
-                     const hj_out& out, const ShjProbeWs& w, uint64_t* d_count, hj::Recorder& rec) {
+                     const hj_out& out, const ShjProbeWs& w, uint64_t* d_count, bool cleared, hj::Recorder& rec) {
     if (!pl.one_pass) {
-        hj::shj_count(S.key, S.n, t.table, t.next, t.nslots, R.key, R.n, t.hot, w.wave_cnt, rec);
-        hj::zero_words(w.st, w.nst, rec);
+        hj::shj_count(S.key, S.n, t.table, t.next, t.nslots, R.key, R.n, t.hot, w.wave_cnt, w.st, w.nst,
+                      rec);
         hj::scan_u64(w.wave_cnt, w.wave_cnt, w.tiles * hj::kShjWavesPerBlock, w.st, d_count, rec);
-    } else {
+    } else if (!cleared) {
         hj::shj_zero_one_pass(d_count, w.heavy, rec);
     }
     hj::shj_write(S.key, S.rid, S.n, t.table, t.next, t.nslots, R.key, R.rid, R.n, t.hot,
@@ -444,8 +446,8 @@ void run_shj(const Plan& pl, const hj_rel& R, const hj_rel& S, const hj_out& out
              uint64_t* d_count, hj::Recorder& rec) {
     const ShjTableWs t = shj_table_layout(R.n, ws);
     const ShjProbeWs w = shj_probe_layout(S.n, (char*)ws + t.bytes);
-    shj_build_table(R, t, rec);
-    shj_probe_table(pl, t, R, S, out, w, d_count, rec);
+    shj_build_table(R, t, pl.one_pass ? d_count : nullptr, pl.one_pass ? w.heavy : nullptr, rec);
+    shj_probe_table(pl, t, R, S, out, w, d_count, true, rec);
 }
 
 // PHJ partitioning (Algorithm 2, n1-n3) of R and S (either may be empty) into
@@ -542,7 +544,7 @@ void run_build(const Plan& pl, const hj_rel& R, void* ws, hj::Recorder& rec) {
         return;
     }
     if (!pl.phj) {
-        shj_build_table(R, shj_table_layout(R.n, ws), rec);
+        shj_build_table(R, shj_table_layout(R.n, ws), nullptr, nullptr, rec);
         return;
     }
     const PhjWs w = phj_layout(pl, R.n, 0, 0, ws);
@@ -560,7 +562,7 @@ void run_probe(const Plan& pl, const hj_table& t, const hj_rel& S, const hj_out&
     } else if (!pl.phj) {
         const ShjTableWs tw = shj_table_layout(t.n_r, t.ws);
         const ShjProbeWs w = shj_probe_layout(S.n, ws);
-        shj_probe_table(pl, tw, R, S, out, w, d_count, rec);
+        shj_probe_table(pl, tw, R, S, out, w, d_count, false, rec);
     } else {
         // R's partitions and pair ranges are in the table; only S is partitioned here
         const PhjWs tw = phj_layout(pl, t.n_r, 0, 0, t.ws);

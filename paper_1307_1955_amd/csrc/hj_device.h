@@ -71,23 +71,47 @@ __device__ __forceinline__ uint64_t chain_slot(int32_t key, uint32_t head) {
 
 constexpr uint64_t kClaimed = ~0ull;  // chain_claim: the row took an empty slot
 
+// Slots s .. s + kW - 1 (kW even, s a multiple of it) by 16-byte loads.
+template <uint32_t kW>
+__device__ __forceinline__ void load_slots(const uint64_t* p, uint64_t* e) {
+    const ulonglong2* q = reinterpret_cast<const ulonglong2*>(p);
+#pragma unroll
+    for (uint32_t i = 0; i < kW / 2; ++i) {
+        const ulonglong2 v = q[i];
+        e[2 * i] = v.x;
+        e[2 * i + 1] = v.y;
+    }
+}
+
 // Finds key k's slot, probing from slot *s with step(*s), and leaves it in *s.
 // A row whose key is new claims an empty slot with one compare-and-swap and is
 // done (true); otherwise the row still has to be pushed onto the slot's chain
 // (WavePush).
-template <typename Step>
+template <uint32_t kW, typename Step>
 __device__ __forceinline__ bool chain_claim(uint64_t* table, uint64_t* s, int32_t k, uint32_t row, Step step) {
+    uint32_t from = (uint32_t)*s % kW;
+    uint64_t at = *s - from;
     while (true) {
         // Read first and CAS only a free slot (faster on MI355X than an
         // unconditional CAS: the read brings the line in, the CAS then hits it).
-        uint64_t cur = __hip_atomic_load(&table[*s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (cur == kEmptySlot) {
-            cur = atomicCAS((unsigned long long*)&table[*s], (unsigned long long)kEmptySlot,
-                            (unsigned long long)chain_slot(k, row | kLast));
-            if (cur == kEmptySlot) return true;
+        // An old value does no harm: a slot's key never changes, and the CAS
+        // returns what an apparently free one holds.
+        uint64_t e[kW];
+        load_slots<kW>(table + at, e);
+#pragma unroll
+        for (uint32_t i = 0; i < kW; ++i) {
+            if (i < from) continue;
+            uint64_t cur = e[i];
+            *s = at + i;
+            if (cur == kEmptySlot) {
+                cur = atomicCAS((unsigned long long*)&table[*s], (unsigned long long)kEmptySlot,
+                                (unsigned long long)chain_slot(k, row | kLast));
+                if (cur == kEmptySlot) return true;
+            }
+            if ((uint32_t)cur == (uint32_t)k) return false;
         }
-        if ((uint32_t)cur == (uint32_t)k) return false;
-        *s = step(*s);
+        from = 0;
+        at = step(*s);
     }
 }
 
@@ -178,7 +202,8 @@ struct WavePush {
     // meet by key: the lane whose number an entry holds looks up the slot for
     // all lanes of its key there; lanes of another key look up their own.
     static constexpr uint32_t kSeen = 128;
-    template <typename Step>
+    // kW: slots read at once.
+    template <uint32_t kW, typename Step>
     __device__ __forceinline__ uint64_t claim(uint64_t* table, bool active, int32_t k, uint32_t row, uint64_t home,
                                               Step step, volatile uint8_t* seen) {
         const uint32_t lane = __lane_id();
@@ -191,7 +216,7 @@ struct WavePush {
         lead = lead && (w == lane || wk != k);
         uint64_t s = home;
         bool fresh = false;
-        if (lead) fresh = chain_claim(table, &s, k, row, step);
+        if (lead) fresh = chain_claim<kW>(table, &s, k, row, step);
         const uint64_t other = __shfl(s, (int)w);
         if (!active || fresh) return kClaimed;
         return known ? hot_slot : lead ? s : other;
@@ -308,14 +333,26 @@ struct WavePush {
 };
 
 // Head field of key `k`'s chain, or kNotFound.
-template <typename Step>
+template <uint32_t kW, typename Step>
 __device__ __forceinline__ uint32_t chain_find(const uint64_t* __restrict__ table, uint64_t s, int32_t k,
                                                Step step) {
+    uint32_t from = (uint32_t)s % kW;
+    s -= from;
     while (true) {
-        const uint64_t e = table[s];
-        if (e == kEmptySlot) return kNotFound;
-        if ((uint32_t)e == (uint32_t)k) return (uint32_t)(e >> 32);
-        s = step(s);
+        uint64_t e[kW];
+        load_slots<kW>(table + s, e);
+        uint32_t found = kNotFound;
+        bool end = false;
+#pragma unroll
+        for (uint32_t i = 0; i < kW; ++i) {
+            if (i >= from && !end) {
+                end = e[i] == kEmptySlot || (uint32_t)e[i] == (uint32_t)k;
+                if (end && e[i] != kEmptySlot) found = (uint32_t)(e[i] >> 32);
+            }
+        }
+        if (end) return found;
+        from = 0;
+        s = step(s + kW - 1);
     }
 }
 

@@ -75,8 +75,6 @@ struct Recorder {
 size_t scan_state_words(uint64_t n);
 void scan_u32(const uint32_t* in, uint32_t* out, uint64_t n, uint64_t* state, uint32_t* total, Recorder& rec);
 void scan_u64(const uint64_t* in, uint64_t* out, uint64_t n, uint64_t* state, uint64_t* total, Recorder& rec);
-// Clears n words.
-void zero_words(uint64_t* p, uint64_t n, Recorder& rec);
 // Clears the words a and b (either may be nullptr) in one small launch.
 void zero_pair(uint64_t* a, uint64_t* b, Recorder& rec);
 
@@ -93,9 +91,11 @@ inline uint64_t shj_slots(uint64_t n_r) {
     return (s + 15) / 16 * 16;
 }
 struct HotKeys;  // keys the build saw in long push runs (hj_device.h)
+struct HeavyQueue;
 // Fills the table with empty slots, clears the hot-key record and the call's
-// error word (rec.err_clear).
-void shj_fill(uint64_t* table, uint64_t nslots, HotKeys* hot, Recorder& rec);
+// error word (rec.err_clear); total, queue (or nullptr): a one-pass join's count
+// and queue, cleared with them.
+void shj_fill(uint64_t* table, uint64_t nslots, HotKeys* hot, uint64_t* total, HeavyQueue* queue, Recorder& rec);
 // nt: R's keys read with non-temporal loads (kNtMinBuild).
 void shj_build(const int32_t* key, uint64_t n, uint64_t* table, uint32_t* next, uint64_t nslots,
                HotKeys* hot, bool nt, Recorder& rec);
@@ -140,10 +140,11 @@ void shj_zero_one_pass(uint64_t* d_count, HeavyQueue* q, Recorder& rec);
 
 // The probe kernels read R's columns (r_key, r_rid, n_r rows, the ones the
 // table was built from) for keys with long chains.  shj_count also clears the
-// call's error word (rec.err_clear): it runs before the count scan.
+// call's error word (rec.err_clear) and the count scan's state: it runs before
+// that scan.
 void shj_count(const int32_t* s_key, uint64_t n_s, const uint64_t* table, const uint32_t* next,
                uint64_t nslots, const int32_t* r_key, uint64_t n_r, const HotKeys* hot, uint64_t* wave_cnt,
-               Recorder& rec);
+               uint64_t* scan_state, uint64_t scan_words, Recorder& rec);
 void shj_write(const int32_t* s_key, const int32_t* s_rid, uint64_t n_s, const uint64_t* table,
                const uint32_t* next, uint64_t nslots, const int32_t* r_key, const int32_t* r_rid,
                uint64_t n_r, const HotKeys* hot, const uint64_t* wave_base, uint64_t* total, HeavyQueue* heavy,

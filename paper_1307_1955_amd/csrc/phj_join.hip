@@ -116,7 +116,7 @@ __device__ __forceinline__ void build_tables(const OvfBuild& B, const Tuple* rt,
             const uint32_t j = j0 + threadIdx.x;
             int32_t k = 0;
             if (j < end) k = key_of(rt[pp.r_off + j]);
-            const uint64_t s = push.claim(region, j < end, k, j, region_slot(k, step.H), step, seen);
+            const uint64_t s = push.claim<2>(region, j < end, k, j, region_slot(k, step.H), step, seen);
             push.add(region, next, s, k, j);
         }
         push.flush_block<kJoinWaves>(region, next, runs);
@@ -387,7 +387,7 @@ __device__ __forceinline__ void probe_hbm(const uint64_t* __restrict__ region, c
         c[u] = 0;
         at[u] = kNotFound;
         if (wb + u * kWave + lane_id() < we) {
-            at[u] = chain_find(region, region_slot(q[u], H), q[u], step);
+            at[u] = chain_find<2>(region, region_slot(q[u], H), q[u], step);
             if (at[u] != kNotFound) {
                 const uint32_t hot = (at[u] & kLast) ? 0u : hot_rows_of(q[u], sh->hk, sh->hr, sh->nhk);
                 c[u] = hot > lim ? register_heavy(next, at[u], q[u], qr ? qr[u] : 0, &sh->hs)

@@ -70,11 +70,6 @@ __global__ void k_scan_empty(T* __restrict__ total) {
     if (threadIdx.x == 0 && total) *total = 0;
 }
 
-__global__ void __launch_bounds__(256) k_zero_words(uint64_t* __restrict__ p, uint64_t n) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-        p[i] = 0;
-}
-
 template <typename T>
 void scan_impl(const T* in, T* out, uint64_t n, uint64_t* state, T* total, Recorder& rec, const char* name) {
     const uint64_t nt = (n + kScanChunk - 1) / kScanChunk;
@@ -111,15 +106,6 @@ void scan_u32(const uint32_t* in, uint32_t* out, uint64_t n, uint64_t* state, ui
 
 void scan_u64(const uint64_t* in, uint64_t* out, uint64_t n, uint64_t* state, uint64_t* total, Recorder& rec) {
     scan_impl<uint64_t>(in, out, n, state, total, rec, "scan_u64");
-}
-
-void zero_words(uint64_t* p, uint64_t n, Recorder& rec) {
-    if (n == 0) return;
-    uint64_t blocks = (n + 255) / 256;
-    if (blocks > 1024) blocks = 1024;
-    rec.before("zero_state");
-    hipLaunchKernelGGL(k_zero_words, dim3((uint32_t)blocks), dim3(256), 0, rec.stream, p, n);
-    rec.after();
 }
 
 }  // namespace hj

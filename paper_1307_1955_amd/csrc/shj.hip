@@ -28,11 +28,15 @@ namespace {
 
 __global__ void __launch_bounds__(256) k_fill_u64(uint64_t* __restrict__ p, uint64_t n, uint64_t v,
                                                  uint32_t* __restrict__ zero, uint32_t zero_words,
+                                                 uint64_t* __restrict__ total, uint64_t* __restrict__ queue,
                                                  uint64_t* __restrict__ err_clear) {
     if (blockIdx.x == 0) {
         for (uint32_t i = threadIdx.x; i < zero_words; i += blockDim.x) zero[i] = 0;
         if (threadIdx.x == 0 && err_clear) *err_clear = 0;
+        if (threadIdx.x == 0 && total) *total = 0;
     }
+    if (queue && blockIdx.x == gridDim.x - 1)
+        for (uint32_t i = threadIdx.x; i < sizeof(HeavyQueue) / 8; i += blockDim.x) queue[i] = 0;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x * 2;
     for (uint64_t i = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * 2; i < n; i += stride) {
         if (i + 1 < n) {
@@ -49,6 +53,15 @@ struct WrapStep {
     uint64_t nslots;
     __device__ __forceinline__ uint64_t operator()(uint64_t s) const { return s + 1 == nslots ? 0 : s + 1; }
 };
+
+// Slots a look-up reads at once (two 16-byte loads of an aligned 32): a probe
+// sequence is a chain of dependent reads, as long as the longest of the wave's
+// 64, and takes a quarter of them.  300K x 1.2M: build 37.4 -> 30.9 us, count
+// 44.7 -> 31.8, write 48.1 -> 35.0; 16M x 16M, bound by the fetch of its random
+// lines, 734 -> 722 and 513 -> 501.  Eight at once cost the write registers
+// (1K rows: 18.6 and 22.1 us), pairs in lockstep over a lane's eight keys
+// suit tables of up to 64K rows only (65K x 262K count 20.6 and 21.7; 1M x 4M 87.9 and 68.5).
+constexpr uint32_t kSlotsAtOnce = 4;
 
 __device__ __forceinline__ uint64_t home_slot(int32_t k, uint64_t nslots) {
     return ((uint64_t)slot_hash(k) * nslots) >> 32;
@@ -69,7 +82,7 @@ __global__ void __launch_bounds__(256) k_shj_build(const int32_t* __restrict__ k
         const uint64_t i = i0 + threadIdx.x;
         int32_t k = 0;
         if (i < n) k = kNt ? __builtin_nontemporal_load(key + i) : key[i];  // read once
-        const uint64_t s = push.claim(table, i < n, k, (uint32_t)i, home_slot(k, nslots), step,
+        const uint64_t s = push.claim<kSlotsAtOnce>(table, i < n, k, (uint32_t)i, home_slot(k, nslots), step,
                                       seen + threadIdx.x / kWave * WavePush::kSeen);
         push.add(table, next, s, k, (uint32_t)i);
     }
@@ -107,7 +120,7 @@ __device__ __forceinline__ void shj_probe(const int32_t* __restrict__ s_key, con
         if (j < n_s) {
             q[u] = s_key[j];
             if (kRids) qr[u] = s_rid[j];
-            head[u] = chain_find(table, home_slot(q[u], nslots), q[u], step);
+            head[u] = chain_find<kSlotsAtOnce>(table, home_slot(q[u], nslots), q[u], step);
             if (head[u] != kNotFound) {
                 // a chain of one row is never heavy
                 const uint32_t hot_rows = (head[u] & kLast) ? 0u : hot_rows_of(q[u], hk, hr, nhk);
@@ -128,9 +141,13 @@ __global__ void __launch_bounds__(kShjBlock) k_shj_count(const int32_t* __restri
                                                         uint64_t nslots, const int32_t* __restrict__ r_key,
                                                         uint64_t n_r, const HotKeys* __restrict__ hot,
                                                         uint64_t* __restrict__ wave_cnt,
+                                                        uint64_t* __restrict__ scan_state, uint64_t scan_words,
                                                         uint64_t* __restrict__ err_clear) {
     __shared__ HeavySet hs;
     if (blockIdx.x == 0 && threadIdx.x == 0 && err_clear) *err_clear = 0;
+    // the state of the scan that comes next
+    const uint64_t stride = (uint64_t)gridDim.x * kShjBlock;
+    for (uint64_t i = (uint64_t)blockIdx.x * kShjBlock + threadIdx.x; i < scan_words; i += stride) scan_state[i] = 0;
     __shared__ int32_t hk[kHotKeys];
     __shared__ uint32_t hr[kHotKeys];
     __shared__ uint32_t nhk;
@@ -238,13 +255,14 @@ __global__ void __launch_bounds__(256) k_zero_one_pass(uint64_t* __restrict__ to
 
 }  // namespace
 
-void shj_fill(uint64_t* table, uint64_t nslots, HotKeys* hot, Recorder& rec) {
+void shj_fill(uint64_t* table, uint64_t nslots, HotKeys* hot, uint64_t* total, HeavyQueue* queue, Recorder& rec) {
     uint64_t blocks = (nslots / 2 + 255) / 256;
     if (blocks > 8192) blocks = 8192;
     if (blocks == 0) blocks = 1;
     rec.before("shj_fill");
     hipLaunchKernelGGL(k_fill_u64, dim3((uint32_t)blocks), dim3(256), 0, rec.stream, table, nslots,
-                       kEmptySlot, reinterpret_cast<uint32_t*>(hot), (uint32_t)(sizeof(HotKeys) / 4), rec.err_clear);
+                       kEmptySlot, reinterpret_cast<uint32_t*>(hot), (uint32_t)(sizeof(HotKeys) / 4), total,
+                       reinterpret_cast<uint64_t*>(queue), rec.err_clear);
     rec.after();
 }
 
@@ -272,12 +290,13 @@ void shj_build(const int32_t* key, uint64_t n, uint64_t* table, uint32_t* next, 
 
 void shj_count(const int32_t* s_key, uint64_t n_s, const uint64_t* table, const uint32_t* next,
                uint64_t nslots, const int32_t* r_key, uint64_t n_r, const HotKeys* hot, uint64_t* wave_cnt,
-               Recorder& rec) {
+               uint64_t* scan_state, uint64_t scan_words, Recorder& rec) {
     const uint64_t tiles = (n_s + kShjTile - 1) / kShjTile;
     if (tiles == 0) return;
     rec.before("shj_count");
     hipLaunchKernelGGL(k_shj_count, dim3((uint32_t)tiles), dim3(kShjBlock), 0, rec.stream, s_key, n_s,
-                       table, next, nslots, r_key, n_r, hot, wave_cnt, rec.err_clear);
+                       table, next, nslots, r_key, n_r, hot, wave_cnt, scan_state, scan_words,
+                       rec.err_clear);
     rec.after();
 }
 
