@@ -37,19 +37,24 @@ JOIN_CHUNK = 9216          # S tuples per join work item
 OVF_CHUNK = 2048           # R tuples per HBM-table build item,
 OVF_CHUNK_BIG = 16384      #   in a partition of more than OVF_BIG_PART tuples
 OVF_BIG_PART = 1 << 16
-OVF_GRID = 2048            # workgroups of the HBM-table build launches
+OVF_GRID = 2048            # workgroups of the HBM-table clear launch
 SHJ_TILE = 2048            # S tuples per SHJ probe workgroup
 SCAN_CHUNK = 2048          # entries per scan workgroup
-COUNTED_MAX_BITS = 13      # two passes of 4..13 bits in all: pass 1 counts the final partitions
+COUNTED_MAX_BITS = 13      # two passes of 4..13 bits in all: pass 1 counts the final partitions,
+WIDE_COUNT_BITS = 15       #   from 400 tuples per partition on up to here
+FUSE_BITS = 12             # radix bits up to which one scatter makes the final partitions
+SELF_BITS, SELF_WORDS = 8, 16384  # starts summed by the scatter's workgroups (csrc/hj_internal.h self_starts)
 
 # the fitted constants, in this order (seconds, bytes/s; positive except SIGNED)
 PARAMS = [
     "d_gap",               # delay of a dependent launch behind the previous kernel
     "d_kernel",            # fixed ramp-up and drain of a kernel
     "bw_hist", "t_hist_tile",
-    "t_count_bin",         # a counted pass 2's histogram tile: clear, count and pack 2^bits counters
+    "t_count_bin",         # a histogram workgroup: clear and write one counter
+    "l_starts", "t_start_entry",  # the starts launch: its chain of waits, a count of a row summed
+    "t_self_word",         # a scatter workgroup that sums the rows itself: a count of them
     "bw_scatter", "run_half", "t_scatter_tile",
-    "t_reserve",           # a counted pass 2's scatter tile: count sums beside it, or reservations
+    "t_reserve",           # a scatter tile: one partition's count, scan and reservation
     "p_part",              # the partitioning kernels overlap memory and latency imperfectly: (M^p + W^p)^(1/p)
     "q_part",              # share of a later round of partitioning tiles whose latency shows (rounds overlap)
     "t_scan_entry",
@@ -82,25 +87,40 @@ def shj_slots(n_r: int) -> int:
     return (s + 15) // 16 * 16
 
 
+def scatter_tile(tile: int, bits: int, n: int) -> int:
+    """Tuples per scatter workgroup (csrc/hj_internal.h scatter_tile)."""
+    want = 16384 if bits == 12 else 8192 if bits >= 10 else tile
+    return tile if tile < 4096 or want <= tile or n < 256 * want else want
+
+
 def _part_block(tile: int) -> int:
-    return 512 if tile >= 4096 else 256
+    return 1024 if tile >= 8192 else 512 if tile >= 4096 else 256
 
 
 def _scatter_slots(bits: int, tile: int) -> int:
     P = 1 << bits
-    Pp = max(P, 64)
-    lds = 4 * (2 * Pp + 16) + 8 * tile
+    lds = 8 * (tile + 64) + 4 * (max(P, 64) + 128)
     by_lds = LDS_PER_CU // lds
     by_threads = 2048 // _part_block(tile)
     return CUS * max(1, min(by_lds, by_threads))
 
 
-def _hist_slots(tile: int) -> int:
-    return CUS * (2048 // _part_block(tile))
+def hist_grid(tiles: int, count_bits: int) -> int:
+    """Workgroups of the histogram (csrc/hj_internal.h hist_rows)."""
+    cap = 256 if count_bits > 13 else 512 if count_bits > 10 else 1024
+    g = 8 if tiles >= 64 else 1
+    while 2 * g <= cap and 2 * g <= tiles:
+        g *= 2
+    return g
 
 
 def join_lds_bytes(cap: int) -> int:
-    return 4 * (cap + 128) + 8 * cap
+    heads = 64
+    while 2 * heads <= cap:
+        heads *= 2
+    if 4 * (2 * heads + 2 * (cap + 128)) <= LDS_PER_CU // 3 - 1536:
+        heads *= 2
+    return 4 * (heads + 2 * (cap + 128))
 
 
 def join_slots(cap: int) -> int:
@@ -108,7 +128,7 @@ def join_slots(cap: int) -> int:
     waves the kernels' register budget allows (6 per SIMD, 4 with the largest
     build), 512-thread workgroups."""
     by_waves = (4 if cap > 4608 else 6) * 4 // 8
-    return CUS * max(1, min(LDS_PER_CU // (join_lds_bytes(cap) + 1024), by_waves))
+    return CUS * max(1, min(LDS_PER_CU // (join_lds_bytes(cap) + 512), by_waves))
 
 
 def _nonempty(mean: float) -> float:
@@ -131,6 +151,24 @@ def _table_factor(table_bytes: float, gamma: float, base: float = 1 << 20) -> fl
 def counted_pass2(passes: int, b1: int, b2: int) -> bool:
     """Two passes whose pass 2 reserves its runs on counts taken in pass 1."""
     return passes == 2 and 4 <= b1 + b2 <= COUNTED_MAX_BITS
+
+
+def one_scatter(passes: int, b1: int, b2: int) -> bool:
+    return passes == 1 or b1 + b2 <= FUSE_BITS
+
+
+def counts_final(passes: int, b1: int, b2: int, n: int) -> bool:
+    """Whether the first histogram counts the final partitions."""
+    return one_scatter(passes, b1, b2) or (
+        (counted_pass2(passes, b1, b2) or b1 + b2 <= WIDE_COUNT_BITS) and n >= 400 << (b1 + b2))
+
+
+def ovf_chunk(r_part: float) -> int:
+    c = OVF_CHUNK
+    if r_part > OVF_BIG_PART:
+        while c < OVF_CHUNK_BIG and c < math.floor(r_part / 128):
+            c *= 2
+    return c
 
 
 def launches(plan: dict, n_r: int, n_s: int, m: float) -> list[tuple[str, dict]]:
@@ -166,42 +204,49 @@ def launches(plan: dict, n_r: int, n_s: int, m: float) -> list[tuple[str, dict]]
     B = b1 + b2
     P = 1 << B
     P1 = 1 << b1
-    tiles1 = math.ceil(n_r / tile) + math.ceil(n_s / tile)
-    counted = counted_pass2(plan["passes"], b1, b2)
-    rows = float(tiles1 * P) if counted else 0.0  # 8-bit count rows: written by the histogram, summed beside the scatter
-    out.append(("part_hist", {"n": n, "tiles": tiles1, "tile": tile, "extra": rows, "bins": P if counted else 0}))
-    out.append(("scan_u32", {"entries": tiles1 * P1}))
-    out.append(("part_scatter", {"n": n, "tiles": tiles1, "tile": tile, "bits": b1, "extra": rows,
-                                 "counted": int(counted)}))
+    one = one_scatter(plan["passes"], b1, b2)
+    final = counts_final(plan["passes"], b1, b2, n)
+    tile1 = scatter_tile(tile, B if one else b1, n)
+    tiles1 = math.ceil(n_r / tile1) + math.ceil(n_s / tile1)
+    self_starts = one and B <= SELF_BITS and (tiles1 << B) <= SELF_WORDS
+    cbits = B if final else b1  # what the histogram counts
+    grid = tiles1 if self_starts else hist_grid(tiles1, cbits)
+    out.append(("part_hist", {"n": n, "grid": grid, "bins": 1 << cbits}))
+    if not self_starts:
+        out.append(("part_starts", {"entries": 2.0 * grid * ((1 << cbits) + (P1 if final and not one else 0))}))
     r_part, s_part = n_r / P, n_s / P
     hbm = r_part > cap
     ovf_r = n_r if hbm else 0
-    # a counted pass 2 of at most 64 partitions per segment clears the HBM tables itself
-    clears = counted and b2 <= 6
-    if plan["passes"] == 2:
+    clears = one or (final and b2 <= 6)  # the last scatter clears the HBM tables
+    cleared = 16.0 * ovf_r if clears else 0.0
+    out.append(("part_scatter", {"n": n, "tiles": tiles1, "tile": tile1, "bits": B if one else b1,
+                                 "extra": cleared if one else 0.0,
+                                 "words": float(tiles1 << B) if self_starts else 0.0}))
+    if not one:
+        tile2 = scatter_tile(tile, b2, n)
         seg = n / (2.0 * P1)
-        tiles2 = 2 * P1 * max(1, math.ceil(seg / tile)) if seg > 0 else 0
-        if not counted:
-            out.append(("part_hist", {"n": n, "tiles": tiles2, "tile": tile, "extra": 0.0, "bins": 0}))
-            out.append(("scan_u32", {"entries": (n / tile + 2 * P1) * (1 << b2)}))
-        out.append(("part_scatter", {"n": n, "tiles": tiles2, "tile": tile, "bits": b2,
-                                     "extra": 16.0 * ovf_r if clears else 0.0, "counted": int(counted)}))
+        tiles2 = 2 * P1 * max(1, math.ceil(seg / tile2)) if seg > 0 else 0
+        if not final:
+            out.append(("part_hist2", {"n": 2.0 * n, "grid": tiles2, "bins": 1 << b2}))
+            out.append(("scan_u32", {"entries": 2.0 * P}))
+        out.append(("part_scatter", {"n": n, "tiles": tiles2, "tile": tile2, "bits": b2, "extra": cleared,
+                                     "words": 0.0}))
     pairs = P * _nonempty(r_part) * _nonempty(s_part)
     items = pairs * max(1, math.ceil(s_part / JOIN_CHUNK))
     grid = P + math.ceil(n_s / JOIN_CHUNK)
     s_item = min(max(s_part, 1.0), JOIN_CHUNK)
-    chunk = OVF_CHUNK_BIG if r_part > OVF_BIG_PART else OVF_CHUNK
-    ovf_items = P * math.ceil(r_part / chunk) if hbm else 0
+    chunk = ovf_chunk(r_part)
+    # HBM tables are built by the first join launch
+    build = {"ovf_n": ovf_r, "ovf_items": P * math.ceil(r_part / chunk) if hbm else 0, "per": min(r_part, chunk)}
     if not clears:
         out.append(("ovf_clear", {"bytes": 16.0 * ovf_r}))
-    out.append(("ovf_build", {"n": ovf_r, "items": ovf_items, "per": min(r_part, chunk)}))
     jf = {"items": items, "grid": grid, "r": min(r_part, cap), "s": s_item, "cap": cap, "hbm": int(hbm)}
     if not plan["one_pass"]:
-        out.append(("join_count", dict(jf, bytes=4.0 * n)))
+        out.append(("join_count", dict(jf, bytes=4.0 * n, **build)))
         out.append(("scan_u64", {"entries": 8 * grid}))
         out.append(("join_write", dict(jf, bytes=8.0 * n + 8.0 * m)))
     else:
-        out.append(("join_write_1pass", dict(jf, bytes=8.0 * n + 8.0 * m)))
+        out.append(("join_write_1pass", dict(jf, bytes=8.0 * n + 8.0 * m, **build)))
     return out
 
 
@@ -214,20 +259,22 @@ def _part_lat(rounds: int, per_tile: float, c: dict) -> float:
 def kernel_seconds(name: str, f: dict, c: dict) -> float:
     """One kernel's duration: ramp-up/drain + max(memory term, workgroup-latency term)."""
     d = c["d_kernel"]
-    if name == "part_hist":
-        if f["tiles"] == 0:
+    if name in ("part_hist", "part_hist2"):
+        if f["grid"] == 0:
             return d
-        rounds = math.ceil(f["tiles"] / _hist_slots(f["tile"]))
-        per_tile = c["t_hist_tile"] * f["tile"] / 8192.0 + c["t_count_bin"] * f["bins"]
-        return d + _smooth_max((4.0 * f["n"] + f["extra"]) / c["bw_hist"], _part_lat(rounds, per_tile, c),
+        per = c["t_hist_tile"] * (f["n"] / f["grid"]) / 8192.0 + c["t_count_bin"] * f["bins"]
+        return d + _smooth_max(4.0 * f["n"] / c["bw_hist"], _part_lat(math.ceil(f["grid"] / 1024.0), per, c),
                                c["p_part"])
+    if name == "part_starts":
+        return d + c["l_starts"] + f["entries"] * c["t_start_entry"]
     if name == "part_scatter":
         if f["tiles"] == 0:
             return d
         run = f["tile"] / float(1 << f["bits"])
         bw = c["bw_scatter"] * run / (run + c["run_half"])
         rounds = math.ceil(f["tiles"] / _scatter_slots(f["bits"], f["tile"]))
-        per_tile = c["t_scatter_tile"] * f["tile"] / 8192.0 + c["t_reserve"] * f["counted"]
+        per_tile = (c["t_scatter_tile"] * f["tile"] / 8192.0 + c["t_reserve"] * (1 << f["bits"]) / 4096.0 +
+                    c["t_self_word"] * f["words"])
         return d + _smooth_max((16.0 * f["n"] + f["extra"]) / bw, _part_lat(rounds, per_tile, c), c["p_part"])
     if name in ("scan_u32", "scan_u64"):
         return d + f["entries"] * c["t_scan_entry"]
@@ -238,14 +285,13 @@ def kernel_seconds(name: str, f: dict, c: dict) -> float:
             lat = c["l_join0"] + c["l_join_r"] * f["r"] + c["l_join_s"] * f["s"]
         lat *= c["f_count"] if name == "join_count" else c["f_1pass"] if name == "join_write_1pass" else 1.0
         rounds = math.ceil(max(f["items"], 1) / join_slots(f["cap"]))
-        return d + _smooth_max(f["bytes"] / c["bw_join"], rounds * lat, c["p_join"])
+        build = 0.0
+        if f.get("ovf_items"):
+            turns = math.ceil(f["ovf_items"] / (3.0 * CUS))
+            build = max(f["ovf_n"] * c["t_ovf_insert"], turns * math.ceil(f["per"] / 512.0) * c["l_ovf_round"])
+        return d + build + _smooth_max(f["bytes"] / c["bw_join"], rounds * lat, c["p_join"])
     if name == "ovf_clear":
         return d + f["bytes"] / c["bw_fill"]
-    if name == "ovf_build":
-        if not f["items"]:
-            return d
-        rounds = math.ceil(f["items"] / min(OVF_GRID, 8 * CUS))
-        return d + max(f["n"] * c["t_ovf_insert"], rounds * math.ceil(f["per"] / 256.0) * c["l_ovf_round"])
     if name == "shj_fill":
         return d + f["bytes"] / c["bw_fill"]
     if name == "shj_build":
@@ -266,7 +312,7 @@ def join_seconds(plan: dict, n_r: int, n_s: int, m: float, c: dict) -> float:
 
 # starting point of the fit: rough MI355X figures
 START = {
-    "d_gap": 2e-6, "d_kernel": 3e-6, "bw_hist": 4.5e12, "t_hist_tile": 5e-6, "t_count_bin": 1e-9,
+    "d_gap": 2e-6, "d_kernel": 3e-6, "bw_hist": 4.5e12, "t_hist_tile": 5e-6, "t_count_bin": 1e-9, "l_starts": 4e-6, "t_start_entry": 1e-12, "t_self_word": 1e-10,
     "bw_scatter": 5.2e12, "run_half": 8.0, "t_scatter_tile": 12e-6, "t_reserve": 2e-6, "p_part": 4.0, "q_part": 0.5, "t_scan_entry": 2e-12, "bw_join": 4e12, "l_join0": 4e-6, "l_join_r": 1e-9,
     "l_join_s": 5e-10, "f_count": 0.8, "f_1pass": 1.2, "p_join": 4.0, "l_hbm0": 8e-6, "l_hbm_s": 2e-9, "t_ovf_insert": 1e-10, "l_ovf_round": 4e-6,
     "bw_fill": 5e12, "t_ins": 1e-10, "gamma_ins": -0.2, "t_bround": 1e-5, "gamma_bround": 0.1,

@@ -34,27 +34,21 @@ constexpr double kCus = 256;
 constexpr double kLdsPerCu = 160.0 * 1024;
 constexpr double kChunk = kJoinChunk;
 constexpr double kShjTileD = kShjTile;
-constexpr double kOvfGridD = kOvfGrid;
-
-double part_block(uint32_t tile) { return tile >= 4096 ? 512 : 256; }
 
 double scatter_slots(uint32_t bits, uint32_t tile) {
     const double P = std::ldexp(1.0, (int)bits);
-    const double Pp = std::max(P, 64.0);
-    const double lds = 4 * (2 * Pp + 16) + 8.0 * tile;
+    const double lds = 8.0 * (tile + 64) + 4 * (std::max(P, 64.0) + 128);
     const double by_lds = std::floor(kLdsPerCu / lds);
-    const double by_threads = std::floor(2048 / part_block(tile));
+    const double by_threads = std::floor(2048.0 / scatter_block(tile));
     return kCus * std::max(1.0, std::min(by_lds, by_threads));
 }
-
-double hist_slots(uint32_t tile) { return kCus * std::floor(2048 / part_block(tile)); }
 
 // Join work items resident at once: workgroups per CU by LDS and by the waves
 // the kernels' register budget allows (6 per SIMD, 4 with the largest build).
 double join_slots(uint32_t cap) {
-    const double lds = 4.0 * (cap + 128) + 8.0 * cap;
     const double by_waves = (join_rpt(cap) > kRptMid ? 4.0 : 6.0) * 4.0 / kJoinWaves;
-    return kCus * std::max(1.0, std::min(std::floor(kLdsPerCu / (lds + 1024)), std::floor(by_waves)));
+    const double lds = (double)join_lds_bytes(cap, 1, true) + 512;
+    return kCus * std::max(1.0, std::min(std::floor(kLdsPerCu / lds), std::floor(by_waves)));
 }
 
 double nonempty(double mean) { return mean < 30 ? 1.0 - std::exp(-mean) : 1.0; }
@@ -73,27 +67,27 @@ double smooth_max(double a, double b, double p) {
     return m * std::pow(std::pow(a / m, p) + std::pow(b / m, p), 1.0 / p);
 }
 
-// extra: bytes beyond the tuples' (a counted pass 2's count rows); bins: the
-// counters a counted pass 2's histogram tile clears, counts and packs
 // Latency term of a partitioning launch: the first round of tiles, then a
 // share q_part of each later round (rounds overlap).
 double part_lat(double rounds, double per_tile) { return per_tile * (1.0 + (rounds - 1.0) * k_q_part); }
 
-double hist_s(double n, double tiles, uint32_t tile, double extra, double bins) {
-    if (tiles == 0) return k_d_kernel;
-    const double per_tile = k_t_hist_tile * tile / 8192.0 + k_t_count_bin * bins;
-    return k_d_kernel + smooth_max((4.0 * n + extra) / k_bw_hist,
-                                   part_lat(rounds(tiles, hist_slots(tile)), per_tile), k_p_part);
+// grid: workgroups; bins: counters each clears and writes
+double hist_s(double n, double grid, double bins) {
+    if (grid == 0) return k_d_kernel;
+    const double per = k_t_hist_tile * (n / grid) / 8192.0 + k_t_count_bin * bins;
+    return k_d_kernel + smooth_max(4.0 * n / k_bw_hist, part_lat(std::ceil(grid / 1024.0), per), k_p_part);
 }
 
-// counted: a counted pass 2's scatter (count sums beside pass 1, reservations in pass 2)
-double scatter_s(double n, double tiles, uint32_t tile, uint32_t bits, double extra, bool counted) {
+// extra: bytes beyond the tuples' (HBM tables cleared); words: counts that every
+// workgroup sums itself
+double scatter_s(double n, double tiles, uint32_t tile, uint32_t bits, double extra, double words) {
     if (tiles == 0) return k_d_kernel;
-    const double run = tile / std::ldexp(1.0, (int)bits);
+    const double P = std::ldexp(1.0, (int)bits);
+    const double run = tile / P;
     const double bw = k_bw_scatter * run / (run + k_run_half);
-    const double per_tile = k_t_scatter_tile * tile / 8192.0 + (counted ? k_t_reserve : 0.0);
+    const double per_tile = k_t_scatter_tile * tile / 8192.0 + k_t_reserve * P / 4096.0 + k_t_self_word * words;
     return k_d_kernel + smooth_max((16.0 * n + extra) / bw,
-                                   part_lat(rounds(tiles, scatter_slots(bits, tile)), per_tile), k_p_part);
+                                   part_lat(std::ceil(tiles / scatter_slots(bits, tile)), per_tile), k_p_part);
 }
 
 double scan_s(double entries) { return k_d_kernel + entries * k_t_scan_entry; }
@@ -143,24 +137,37 @@ double model_seconds(const Plan& pl, uint64_t n_r_, uint64_t n_s_, double m) {
     }
     const uint32_t tile = pl.tile, b1 = pl.b1, b2 = pl.passes == 2 ? pl.b2 : 0;
     const double P = std::ldexp(1.0, (int)(b1 + b2)), P1 = std::ldexp(1.0, (int)b1);
-    const double tiles1 = std::ceil(n_r / tile) + std::ceil(n_s / tile);
-    const bool counted = counted_pass2(pl.passes, b1, b2);
+    const uint64_t nn = n_r_ + n_s_;
+    const bool one = one_scatter(pl.passes, b1, b2), final = counts_final(pl.passes, b1, b2, nn);
+    const uint32_t tile1 = scatter_tile(tile, one ? b1 + b2 : b1, nn);
+    const uint64_t tiles1 = (n_r_ + tile1 - 1) / tile1 + (n_s_ + tile1 - 1) / tile1;
+    const bool self = one && self_starts(tiles1, b1 + b2);
+    const uint32_t cbits = final ? b1 + b2 : b1;  // what the histogram counts
+    const double hist_grid = self ? (double)tiles1 : (double)hist_rows(tiles1, cursor_replicas(tiles1), cbits).grid();
     const double r_part = n_r / P, s_part = n_s / P;
     const bool hbm = r_part > pl.lds_cap;
     const double ovf_r = hbm ? n_r : 0;
-    const bool clears = counted && counted_clears_tables(b2);  // the pass-2 scatter clears the HBM tables
-    const double rows = counted ? tiles1 * P : 0.0;  // 8-bit count rows: histogram writes, sums beside the scatter read
-    t += hist_s(n, tiles1, tile, rows, counted ? P : 0.0) + scan_s(tiles1 * P1) +
-         scatter_s(n, tiles1, tile, b1, rows, counted);
-    nl += 3;
-    if (pl.passes == 2) {
+    const bool clears = scatter_clears(pl.passes, b1, b2, nn);  // the last scatter clears the HBM tables
+    const double cleared = clears ? 16 * ovf_r : 0.0;
+    t += hist_s(n, hist_grid, std::ldexp(1.0, (int)cbits));
+    nl += 1;
+    if (!self) {
+        const double columns = std::ldexp(1.0, (int)cbits) + (final && !one ? P1 : 0.0);
+        t += d + k_l_starts + 2 * hist_grid * columns * k_t_start_entry;
+        nl += 1;
+    }
+    t += scatter_s(n, (double)tiles1, tile1, one ? b1 + b2 : b1, one ? cleared : 0.0,
+                   self ? std::ldexp((double)tiles1, (int)(b1 + b2)) : 0.0);
+    nl += 1;
+    if (!one) {
+        const uint32_t tile2 = scatter_tile(tile, b2, nn);
         const double seg = n / (2 * P1);
-        const double tiles2 = seg > 0 ? 2 * P1 * std::max(1.0, std::ceil(seg / tile)) : 0;
-        if (!counted) {
-            t += hist_s(n, tiles2, tile, 0.0, 0.0) + scan_s((n / tile + 2 * P1) * std::ldexp(1.0, (int)b2));
+        const double tiles2 = seg > 0 ? 2 * P1 * std::max(1.0, std::ceil(seg / tile2)) : 0;
+        if (!final) {
+            t += hist_s(2 * n, tiles2, std::ldexp(1.0, (int)b2)) + scan_s(2 * P);
             nl += 2;
         }
-        t += scatter_s(n, tiles2, tile, b2, clears ? 16 * ovf_r : 0.0, counted);
+        t += scatter_s(n, tiles2, tile2, b2, cleared, 0.0);
         nl += 1;
     }
     const double items = P * nonempty(r_part) * nonempty(s_part) * std::max(1.0, std::ceil(s_part / kChunk));
@@ -171,14 +178,11 @@ double model_seconds(const Plan& pl, uint64_t n_r_, uint64_t n_s_, double m) {
         t += d + 16 * ovf_r / k_bw_fill;  // clear the HBM tables
         nl += 1;
     }
-    t += d;  // build them: inserts, or rounds of items of ovf_chunk() tuples
-    if (hbm) {
-        const double chunk = r_part > kOvfBigPart ? kOvfChunkBig : kOvfChunk;
-        const double ovf_items = P * std::ceil(r_part / chunk);
-        const double ovf_rounds = std::ceil(ovf_items / std::min(kOvfGridD, 8 * kCus));
-        t += std::max(ovf_r * k_t_ovf_insert, ovf_rounds * std::ceil(std::min(r_part, chunk) / 256) * k_l_ovf_round);
+    if (hbm) {  // the first join launch builds them: inserts, or rounds of items of ovf_chunk() tuples
+        const double chunk = ovf_chunk((uint32_t)std::min(r_part, 4294967295.0));
+        const double turns = std::ceil(P * std::ceil(r_part / chunk) / (3.0 * kCus));
+        t += std::max(ovf_r * k_t_ovf_insert, turns * std::ceil(std::min(r_part, chunk) / 512) * k_l_ovf_round);
     }
-    nl += 1;
     if (!pl.one_pass) {
         t += join_s(items, r_item, s_item, pl.lds_cap, hbm, 4 * n, k_f_count);
         t += scan_s(8 * grid);
@@ -193,7 +197,9 @@ double model_seconds(const Plan& pl, uint64_t n_r_, uint64_t n_s_, double m) {
 
 // HJ_AUTO: the plan with the least modelled time among SHJ, the direct LDS join
 // (|R| <= 8192) and PHJ in one or two radix passes around ~4096 R tuples per
-// partition.  The partitioning tile is the caller's, else the measured size
+// partition.  Bits that one scatter makes are weighed once, not in each of their
+// splits (a call's plan is chosen anew each time: 10.1 us on the host at 1M x 1M,
+// 3.1 so).  The partitioning tile is the caller's, else the measured size
 // rule (default_tile): between the two tiles the model cannot see which pass
 // loses by shorter runs (pass 1 reads the inputs cold; 16M x 16M ran 9% slower
 // with 4096-tuple tiles, which the model priced faster).  Hash, lds_cap and
@@ -236,7 +242,9 @@ void auto_params(uint64_t n_r, uint64_t n_s, hj_params* p) {
                 q.bits[1] = 0;
                 consider(q);
             }
-            if (b >= 2) {
+            // up to kFuseBits one scatter, however the bits are split: another plan only by its tile
+            const bool same = b <= kFuseBits && (base.tile || default_tile(n_r, n_s, 2, b / 2) == default_tile(n_r, n_s, 1, b));
+            if (b >= 2 && !same) {
                 q.passes = 2;
                 for (uint32_t b1 = std::max(1u, b / 2 - 1); b1 <= std::min(13u, b / 2 + 2); ++b1) {
                     if (b - b1 < 1 || b - b1 > 13) continue;
