@@ -61,6 +61,7 @@ def algorithmic_bytes(name: str, n_r: int, n_s: int, m: int) -> float | None:
     n = n_r + n_s
     return {
         "part_hist": 4.0 * n,            # read keys
+        "part_hist2": 8.0 * n,           # read tuples
         "part_scatter": 16.0 * n,        # read key+rid, write key+rid
         "join_count": 4.0 * n,           # read R_i and S_i keys
         "join_write": 8.0 * n + 8.0 * m,  # read key+rid of R_i and S_i, write the pairs
@@ -369,12 +370,13 @@ def measure_phj(hj, torch, p, t, out_r, out_s, d_count, n_r, n_s, steps, warmup,
     m = int(d_count.item())
     reps = 5
     phases = summarize(kernel_times(hj, p, t, out_r, out_s, ws, d_count, reps), reps, n_r, n_s, m)
-    # partition passes 20 B/tuple each (histogram read + scatter read and write), less the histogram read of a
-    # counted pass 2 (its counts come from pass 1); join: count pass 4 B/tuple (two-pass output) + write pass
-    # 8 B/tuple
-    from paper_1307_1955_amd import costmodel
-    counted = costmodel.counted_pass2(passes, int(p.bits[0]), int(p.bits[1]) if passes == 2 else 0)
-    total_bytes = (20.0 * passes - (4.0 if counted else 0.0) + (8.0 if one_pass else 12.0)) * (n_r + n_s) + 8.0 * m
+    # histogram of the input 4 B/tuple, scatters 16 B/tuple each (one up to 12 bits, else two; a second
+    # histogram reads 8 B/tuple); join: count pass 4 B/tuple (two-pass output) + write pass 8 B/tuple
+    def launched(k):
+        return phases[k]["launches_per_join"] if k in phases else 0.0
+    per_tuple = (4.0 * launched("part_hist") + 8.0 * launched("part_hist2") + 16.0 * launched("part_scatter") +
+                 (8.0 if one_pass else 12.0))
+    total_bytes = per_tuple * (n_r + n_s) + 8.0 * m
     del ws
     return {"ms": ms, "value": (n_r + n_s) / (ms * 1e-3), "matches": m, "kernels": phases, "clock_ramp_ms": round(ramp_ms, 1),
             "path_gbs": round(total_bytes / (ms * 1e-3) / 1e9, 1),

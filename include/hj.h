@@ -58,8 +58,8 @@ typedef enum hj_status {
 
 /* HJ_AUTO: the library evaluates its cost model (hj_model_seconds) for SHJ, for
    PHJ without partitioning (|R| <= 8192), and for PHJ in one or two radix
-   passes around 4096 R tuples per partition with both partitioning tiles (one
-   tile when p->tile is set), and runs the plan with the least modelled time;
+   passes around 4096 R tuples per partition (at p->tile, or the tile chosen from
+   the sizes), and runs the plan with the least modelled time;
    hash, lds_cap and flags are kept.  hj_resolve_params shows the choice. */
 typedef enum hj_algo { HJ_SHJ = 0, HJ_PHJ = 1, HJ_AUTO = 2 } hj_algo;
 
@@ -103,7 +103,8 @@ typedef struct hj_out {
    bits    PHJ: radix bits of pass 1 and pass 2.  B = bits[0] (+ bits[1] when
            passes == 2) must be in 1..20 and each used entry in 1..13.  The
            2^B partitions are the values of the B low bits of the hash; pass 1
-           splits on the high bits[0] of them, pass 2 on the low bits[1].
+           splits on the high bits[0] of them, pass 2 on the low bits[1] (up
+           to 12 bits in all both passes are made as one scatter).
    hash    an hj_hash value.
    tile    tuples per partitioning tile: a power of two in 1024..8192, or 0
            = chosen from the sizes (8192 when |R| + |S| >= 2^25, or >= 2^24

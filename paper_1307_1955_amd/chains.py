@@ -2,8 +2,9 @@
 length could save (Section 3.3, "workload divergence").
 
 The join kernel builds, per work item, a chained table over R_i in LDS: 2^h
-chain heads, h = floor(log2(max(64, |R_i|))), a record per R tuple pushed on
-the chain of its bucket (slot_hash(key) >> (32 - h)); a probe walks the whole
+chain heads, h = floor(log2(lds_cap)) (4416 rows here), a record per R tuple
+pushed on the chain of its bucket (the top h bits of the mixed radix hash
+above the partition's bits); a probe walks the whole
 chain of its S key's bucket.  A wave probes 9 S keys per lane in lockstep, so
 a wave's round takes as many steps as the longest chain among its 576 keys.
 The paper groups tuples of similar key-list length so that a wave's lanes
@@ -29,31 +30,25 @@ ROUND = KSU * WAVE * WAVES   # 4608 S keys per round of a work item
 CHUNK = 2 * ROUND            # S keys per work item
 
 
-def slot_hash(k: np.ndarray) -> np.ndarray:
-    """The table's 32-bit finaliser mix (the published MurmurHash3 finaliser)."""
-    h = k.astype(np.uint32).astype(np.uint64)
-    m = np.uint64(0xFFFFFFFF)
-    h ^= h >> np.uint64(16)
-    h = (h * np.uint64(0x85EBCA6B)) & m
-    h ^= h >> np.uint64(13)
-    h = (h * np.uint64(0xC2B2AE35)) & m
-    h ^= h >> np.uint64(16)
-    return h
+def mixed(k: np.ndarray, bits: int) -> np.ndarray:
+    """The LDS table's 32-bit mix of the key's radix hash (identity) above the
+    partition's bits (csrc/phj_join.hip mixed())."""
+    m, keep = np.uint64(0xFFFFFFFF), np.uint64((0xFFFFFFFF << bits) & 0xFFFFFFFF)
+    h = ((k.astype(np.uint32).astype(np.uint64) & keep) * np.uint64(0x9E3779B1)) & m
+    h ^= (h >> np.uint64(15)) & keep
+    return (h * np.uint64(0x85EBCA6B)) & m
 
 
-def walk_lengths(r_key: np.ndarray, s_key: np.ndarray, bits: int = 12):
+def walk_lengths(r_key: np.ndarray, s_key: np.ndarray, bits: int = 12, log2_heads: int = 12):
     """Per S tuple: its partition and the length of the chain its probe walks."""
     mask = np.int64((1 << bits) - 1)
-    rp = r_key.astype(np.int64) & mask
     sp = s_key.astype(np.int64) & mask
-    r_len = np.bincount(rp, minlength=1 << bits)
-    h = np.floor(np.log2(np.maximum(64, r_len))).astype(np.int64)  # heads per partition: 2^h
-    # bucket of every R and S tuple inside its partition's table; global bucket id
-    # = partition * 2^13 + bucket (h <= 13 for partitions up to 8192 tuples)
-    rb = (slot_hash(r_key) >> (np.uint64(32) - h[rp].astype(np.uint64))).astype(np.int64)
-    sb = (slot_hash(s_key) >> (np.uint64(32) - h[sp].astype(np.uint64))).astype(np.int64)
-    chain = np.bincount(rp * (1 << 14) + rb, minlength=(1 << bits) << 14)
-    return sp, chain[sp * (1 << 14) + sb]
+    # global bucket id = partition * 2^log2_heads + bucket
+    sh = np.uint64(32 - log2_heads)
+    rb = (mixed(r_key, bits) >> sh).astype(np.int64)
+    sb = (mixed(s_key, bits) >> sh).astype(np.int64)
+    chain = np.bincount(((r_key.astype(np.int64) & mask) << log2_heads) + rb, minlength=1 << (bits + log2_heads))
+    return sp, chain[(sp << log2_heads) + sb]
 
 
 def wave_steps(sp: np.ndarray, walk: np.ndarray, grouped: bool) -> tuple[int, int]:

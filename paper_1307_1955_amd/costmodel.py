@@ -60,6 +60,7 @@ PARAMS = [
     "t_scan_entry",
     "bw_join", "l_join0", "l_join_r", "l_join_s",
     "f_count", "f_1pass",  # a work item's latency in the count pass and the one-pass write, against the write pass
+    "t_out",               # one reservation on the output count: they serialize (one per item and probe round)
     "p_join",              # the join kernels overlap memory and latency imperfectly: (M^p + W^p)^(1/p)
     "l_hbm0", "l_hbm_s", "t_ovf_insert", "l_ovf_round",
     "bw_fill",
@@ -194,9 +195,12 @@ def launches(plan: dict, n_r: int, n_s: int, m: float) -> list[tuple[str, dict]]
         return out
     cap = plan["lds_cap"]
     if plan["passes"] == 0:
-        items = math.ceil(n_s / JOIN_CHUNK)
-        out.append(("direct_setup", {}))
-        out.append(("direct_join", {"items": items, "grid": items, "r": n_r, "s": min(n_s, JOIN_CHUNK), "cap": cap,
+        slots = 256 if cap > 4608 else 640
+        chunk = JOIN_CHUNK // 2 if n_s <= slots * (JOIN_CHUNK // 2) else JOIN_CHUNK
+        items = math.ceil(n_s / chunk)
+        if items > 1:
+            out.append(("zero_count", {}))
+        out.append(("direct_join", {"items": items, "grid": items, "r": n_r, "s": min(n_s, chunk), "cap": cap,
                                     "bytes": 8.0 * n + 8.0 * m, "hbm": 0}))
         return out
     tile = plan["tile"]
@@ -289,7 +293,11 @@ def kernel_seconds(name: str, f: dict, c: dict) -> float:
         if f.get("ovf_items"):
             turns = math.ceil(f["ovf_items"] / (3.0 * CUS))
             build = max(f["ovf_n"] * c["t_ovf_insert"], turns * math.ceil(f["per"] / 512.0) * c["l_ovf_round"])
-        return d + build + _smooth_max(f["bytes"] / c["bw_join"], rounds * lat, c["p_join"])
+        # the first round, then its later ones beside the memory traffic
+        t = lat + _smooth_max(f["bytes"] / c["bw_join"], (rounds - 1) * lat, c["p_join"])
+        if name == "join_write_1pass":
+            t = _smooth_max(t, f["items"] * math.ceil(f["s"] / (JOIN_CHUNK / 2)) * c["t_out"], 4.0)
+        return d + build + t
     if name == "ovf_clear":
         return d + f["bytes"] / c["bw_fill"]
     if name == "shj_fill":
@@ -314,7 +322,7 @@ def join_seconds(plan: dict, n_r: int, n_s: int, m: float, c: dict) -> float:
 START = {
     "d_gap": 2e-6, "d_kernel": 3e-6, "bw_hist": 4.5e12, "t_hist_tile": 5e-6, "t_count_bin": 1e-9, "l_starts": 4e-6, "t_start_entry": 1e-12, "t_self_word": 1e-10,
     "bw_scatter": 5.2e12, "run_half": 8.0, "t_scatter_tile": 12e-6, "t_reserve": 2e-6, "p_part": 4.0, "q_part": 0.5, "t_scan_entry": 2e-12, "bw_join": 4e12, "l_join0": 4e-6, "l_join_r": 1e-9,
-    "l_join_s": 5e-10, "f_count": 0.8, "f_1pass": 1.2, "p_join": 4.0, "l_hbm0": 8e-6, "l_hbm_s": 2e-9, "t_ovf_insert": 1e-10, "l_ovf_round": 4e-6,
+    "l_join_s": 5e-10, "f_count": 0.8, "f_1pass": 1.2, "t_out": 1e-8,  "p_join": 4.0, "l_hbm0": 8e-6, "l_hbm_s": 2e-9, "t_ovf_insert": 1e-10, "l_ovf_round": 4e-6,
     "bw_fill": 5e12, "t_ins": 1e-10, "gamma_ins": -0.2, "t_bround": 1e-5, "gamma_bround": 0.1,
     "t_probe": 3e-11, "gamma_probe": 0.0, "t_pround": 2e-5, "gamma_pround": 0.1, "t_match": 1e-11,
 }

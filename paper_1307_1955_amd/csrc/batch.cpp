@@ -261,6 +261,7 @@ hj_status create_plan(uint32_t njobs, const hj_job* jobs, const hj_params* param
             dj.n_r = (uint32_t)j.R.n;
             dj.n_s = (uint32_t)j.S.n;
             dj.item0 = item;
+            dj.chunk = hj::kJoinChunk;
             const uint32_t n_items = (j.R.n && j.S.n) ? (uint32_t)cdiv(j.S.n, hj::kJoinChunk) : 0u;
             for (uint32_t k = 0; k < n_items; ++k) b->h_item_job[item + k] = d;
             item += n_items;

@@ -93,9 +93,12 @@ double scatter_s(double n, double tiles, uint32_t tile, uint32_t bits, double ex
 double scan_s(double entries) { return k_d_kernel + entries * k_t_scan_entry; }
 
 // f: the kernel's work-item latency against the write pass (k_f_count, k_f_1pass, or 1)
-double join_s(double items, double r, double s, uint32_t cap, bool hbm, double bytes, double f) {
+// least: what the reservations on the output count take (one-pass write)
+double join_s(double items, double r, double s, uint32_t cap, bool hbm, double bytes, double f, double least = 0) {
     const double lat = f * (hbm ? k_l_hbm0 + k_l_hbm_s * s : k_l_join0 + k_l_join_r * r + k_l_join_s * s);
-    return k_d_kernel + smooth_max(bytes / k_bw_join, rounds(items, join_slots(cap)) * lat, k_p_join);
+    // the first round, then its later ones beside the memory traffic
+    const double later = (rounds(items, join_slots(cap)) - 1.0) * lat;
+    return k_d_kernel + smooth_max(lat + smooth_max(bytes / k_bw_join, later, k_p_join), least, 4.0);
 }
 
 }  // namespace
@@ -130,10 +133,10 @@ double model_seconds(const Plan& pl, uint64_t n_r_, uint64_t n_s_, double m) {
         return t + nl * gap;
     }
     if (pl.passes == 0) {
-        const double items = std::ceil(n_s / kChunk);
-        t += d;  // setup
-        t += join_s(items, n_r, std::min(n_s, kChunk), pl.lds_cap, false, 8 * n + 8 * m, 1.0);
-        return t + 2 * gap;
+        const double chunk = direct_chunk(n_s_, pl.lds_cap), items = std::ceil(n_s / chunk);
+        if (items > 1) t += d;  // zero the count
+        t += join_s(items, n_r, std::min(n_s, chunk), pl.lds_cap, false, 8 * n + 8 * m, 1.0);
+        return t + (items > 1 ? 2 : 1) * gap;
     }
     const uint32_t tile = pl.tile, b1 = pl.b1, b2 = pl.passes == 2 ? pl.b2 : 0;
     const double P = std::ldexp(1.0, (int)(b1 + b2)), P1 = std::ldexp(1.0, (int)b1);
@@ -189,7 +192,8 @@ double model_seconds(const Plan& pl, uint64_t n_r_, uint64_t n_s_, double m) {
         t += join_s(items, r_item, s_item, pl.lds_cap, hbm, 8 * n + 8 * m, 1.0);
         nl += 3;
     } else {
-        t += join_s(items, r_item, s_item, pl.lds_cap, hbm, 8 * n + 8 * m, k_f_1pass);
+        t += join_s(items, r_item, s_item, pl.lds_cap, hbm, 8 * n + 8 * m, k_f_1pass,
+                    items * std::ceil(s_item / kJoinSub) * k_t_out);
         nl += 1;
     }
     return t + nl * gap;

@@ -346,28 +346,15 @@ size_t shj_bytes(uint64_t n_r, uint64_t n_s) {
     return shj_table_layout(n_r, nullptr).bytes + shj_probe_layout(n_s, nullptr).bytes;
 }
 
-// Direct join (PHJ with no partitioning pass): one job descriptor and the item map.
-struct DirectWs {
-    uint64_t* err;
-    hj::DirectJob* job;
-    uint32_t* item_job;
-    uint32_t nitems;
-    size_t bytes;
-};
-
-DirectWs direct_layout(uint64_t n_s, void* base) {
-    DirectWs w{};
-    Carver c(base);
-    w.nitems = (uint32_t)cdiv(n_s, hj::kJoinChunk);
-    w.err = c.take<uint64_t>(1);
-    w.job = c.take<hj::DirectJob>(1);
-    w.item_job = c.take<uint32_t>(w.nitems);
-    w.bytes = c.off;
-    return w;
+// Direct join (PHJ with no partitioning pass): the error word alone.
+size_t direct_bytes() {
+    Carver c(nullptr);
+    c.take<uint64_t>(1);
+    return c.off;
 }
 
 size_t ws_bytes_for(const Plan& pl, uint64_t n_r, uint64_t n_s) {
-    if (pl.phj && pl.passes == 0) return direct_layout(n_s, nullptr).bytes;
+    if (pl.phj && pl.passes == 0) return direct_bytes();
     return pl.phj ? phj_layout(pl, n_r, n_s, n_r, nullptr).bytes : shj_bytes(n_r, n_s);
 }
 
@@ -377,13 +364,12 @@ size_t table_bytes_for(const Plan& pl, uint64_t n_r) {
 }
 
 size_t probe_bytes_for(const Plan& pl, uint64_t n_r, uint64_t n_s) {
-    if (pl.phj && pl.passes == 0) return direct_layout(n_s, nullptr).bytes;
+    if (pl.phj && pl.passes == 0) return direct_bytes();
     return pl.phj ? phj_layout(pl, 0, n_s, n_r, nullptr).bytes : shj_probe_layout(n_s, nullptr).bytes;
 }
 
-void run_direct(const Plan& pl, const hj_rel& R, const hj_rel& S, const hj_out& out, void* ws,
+void run_direct(const Plan& pl, const hj_rel& R, const hj_rel& S, const hj_out& out,
                 uint64_t* d_count, hj::Recorder& rec) {
-    DirectWs w = direct_layout(S.n, ws);
     hj::DirectJob j{};
     j.rk = R.key;
     j.rr = R.rid;
@@ -395,9 +381,8 @@ void run_direct(const Plan& pl, const hj_rel& R, const hj_rel& S, const hj_out& 
     j.count = d_count;
     j.n_r = (uint32_t)R.n;
     j.n_s = (uint32_t)S.n;
-    j.item0 = 0;
-    hj::direct_setup_one(w.job, w.item_job, j, w.nitems, rec);
-    hj::direct_join(w.job, w.item_job, w.nitems, pl.lds_cap, rec);
+    j.chunk = hj::direct_chunk(S.n, pl.lds_cap);
+    hj::direct_join_one(j, pl.lds_cap, rec);
 }
 
 hj_status check_call(const hj_params* p, const hj_rel* R, const hj_rel* S, const hj_out* out, void* ws,
@@ -530,7 +515,7 @@ void run_join(const Plan& pl, const hj_rel& R, const hj_rel& S, const hj_out& ou
     if (R.n == 0 || S.n == 0) {
         hj::write_zero_count(d_count, rec);
     } else if (pl.phj && pl.passes == 0) {
-        run_direct(pl, R, S, out, ws, d_count, rec);
+        run_direct(pl, R, S, out, d_count, rec);
     } else if (pl.phj) {
         run_phj(pl, R, S, out, ws, d_count, rec);
     } else {
@@ -558,7 +543,7 @@ void run_probe(const Plan& pl, const hj_table& t, const hj_rel& S, const hj_out&
     if (t.n_r == 0 || S.n == 0) {
         hj::write_zero_count(d_count, rec);
     } else if (pl.phj && pl.passes == 0) {
-        run_direct(pl, R, S, out, ws, d_count, rec);
+        run_direct(pl, R, S, out, d_count, rec);
     } else if (!pl.phj) {
         const ShjTableWs tw = shj_table_layout(t.n_r, t.ws);
         const ShjProbeWs w = shj_probe_layout(S.n, ws);

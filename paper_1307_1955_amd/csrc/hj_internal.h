@@ -411,8 +411,8 @@ void join_write(const ItemRec* item_rec, uint32_t grid, const Tuple* rt, const T
 void write_zero_count(uint64_t* d_count, Recorder& rec);
 
 // ---- direct joins (no partitioning: R fits one LDS table) ----
-// One job of the multi-job direct kernel.  Work item = (job, chunk of
-// kJoinChunk S tuples); items of job j are [item0, item0 + ceil(n_s / chunk)).
+// One job of the direct kernels.  Work item = (job, `chunk` S tuples); items of
+// job j are [item0, item0 + ceil(n_s / chunk)).
 struct DirectJob {
     const int32_t* rk;
     const int32_t* rr;
@@ -422,11 +422,22 @@ struct DirectJob {
     int32_t* out_s;
     uint64_t capacity;
     uint64_t* count;  // running total of the job's pairs (zeroed by direct_zero)
-    uint32_t n_r, n_s, item0, pad;
+    uint32_t n_r, n_s, item0, chunk;
 };
-// Writes one job descriptor and item map from kernel arguments, zeroes the
-// job's count and clears the call's error word (rec.err_clear) (single join).
-void direct_setup_one(DirectJob* job, uint32_t* item_job, const DirectJob& j, uint32_t nitems, Recorder& rec);
+// S tuples per work item of a single direct join: one probe round while every
+// item still runs at once (1 a CU with the largest tables, else 3: up to 640,
+// 4.4K x 3.5M took 27.4 us in 760 of them, 26.7 before), else kJoinChunk.  An item is a chain of
+// dependent steps and a second round adds a load, a probe and a reservation to
+// it; on idle CUs building R's table again costs nothing (2.2K x 26.7K:
+// 18.3 to 13.7 us, 4K x 2M 23.3 to 19.0).  Batches keep kJoinChunk: their items fill the device.
+inline uint32_t direct_chunk(uint64_t n_s, uint32_t lds_cap) {
+    const uint64_t slots = join_rpt(lds_cap) > kRptMid ? 256 : 640;
+    return n_s <= slots * kJoinSub ? kJoinSub : kJoinChunk;
+}
+// A single direct join, its job a kernel argument.  One work item zeroes the
+// job's count and the call's error word (rec.err_clear) itself; more need a
+// launch before them (1K x 3K, two launches and one: 13.9 and 11.0 us).
+void direct_join_one(const DirectJob& j, uint32_t lds_cap, Recorder& rec);
 void direct_zero(const DirectJob* jobs, uint32_t njobs, Recorder& rec);
 // lds_cap >= every job's n_r (<= kMaxLdsCap).
 void direct_join(const DirectJob* jobs, const uint32_t* item_job, uint32_t nitems, uint32_t lds_cap,

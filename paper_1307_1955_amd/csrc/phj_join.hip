@@ -755,21 +755,26 @@ k_join_write(const ItemRec* __restrict__ item_rec, uint32_t bits, WriteArgs A, O
 }
 
 // Joins whose whole R fits one LDS table, several jobs per launch: one
-// workgroup per (job, chunk of up to kJoinChunk S tuples) builds the table over
+// workgroup per (job, chunk of S tuples) builds the table over
 // the job's R and writes the chunk's pairs to the job's output with one-pass
 // reservation.
-template <uint32_t RPT>
+// kOne: the only job is `one`; a grid of one workgroup clears its count and
+// err_clear.
+template <uint32_t RPT, bool kOne>
 __global__ void __launch_bounds__(kJoinBlock) __attribute__((amdgpu_waves_per_eu(RPT > kRptMid ? 4 : 6)))
-k_direct_join(const DirectJob* __restrict__ jobs,
-                                                           const uint32_t* __restrict__ item_job,
-                                                           uint32_t lds_cap) {
+k_direct_join(const DirectJob* __restrict__ jobs, const uint32_t* __restrict__ item_job, DirectJob one,
+              uint64_t* err_clear, uint32_t lds_cap) {
     extern __shared__ uint32_t lds[];
     __shared__ uint64_t wtot[kJoinWaves + 1];
     const uint32_t w = threadIdx.x / kWave;
     const uint32_t item = xcd_remap(blockIdx.x, gridDim.x);
-    const DirectJob J = jobs[item_job[item]];
-    const uint32_t s_begin = (item - J.item0) * kJoinChunk;
-    const uint32_t s_n = min(kJoinChunk, J.n_s - s_begin);
+    const DirectJob J = kOne ? one : jobs[item_job[item]];
+    if (kOne && gridDim.x == 1 && threadIdx.x == 0) {  // (the thread that reserves later)
+        *J.count = 0;
+        if (err_clear) *err_clear = 0;
+    }
+    const uint32_t s_begin = (item - J.item0) * J.chunk;
+    const uint32_t s_n = min(J.chunk, J.n_s - s_begin);
     const uint32_t r_len = min(J.n_r, lds_cap);  // the planner guarantees n_r <= lds_cap
     const int32_t* __restrict__ skp = J.sk + s_begin;
     const int32_t* __restrict__ srp = J.sr + s_begin;
@@ -794,17 +799,6 @@ __global__ void k_direct_zero(const DirectJob* __restrict__ jobs, uint32_t njobs
         *jobs[j].count = 0;
 }
 
-__global__ void k_direct_setup_one(DirectJob* job, uint32_t* item_job, DirectJob j, uint32_t nitems,
-                                   uint64_t* err_clear) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        *job = j;
-        *j.count = 0;
-        if (err_clear) *err_clear = 0;
-    }
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nitems; i += gridDim.x * blockDim.x)
-        item_job[i] = 0;
-}
-
 __global__ void k_write_zero(uint64_t* p, uint64_t* err_clear) {
     if (threadIdx.x == 0) {
         *p = 0;
@@ -821,13 +815,6 @@ size_t join_lds_bytes(uint32_t lds_cap, uint32_t bits, bool write) {
     return sizeof(uint32_t) * (((size_t)1 << table_shape(lds_cap, bits).log2H) + (write ? 2 : 1) * rows);
 }
 
-void direct_setup_one(DirectJob* job, uint32_t* item_job, const DirectJob& j, uint32_t nitems, Recorder& rec) {
-    rec.before("direct_setup");
-    hipLaunchKernelGGL(k_direct_setup_one, dim3(1), dim3(256), 0, rec.stream, job, item_job, j, nitems,
-                       rec.err_clear);
-    rec.after();
-}
-
 void direct_zero(const DirectJob* jobs, uint32_t njobs, Recorder& rec) {
     if (njobs == 0) return;
     rec.before("direct_zero");
@@ -839,25 +826,37 @@ static void allow_lds(const void* fn, size_t lds) {
     if (lds > 65536) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
-template <uint32_t RPT>
-void direct_join_t(const DirectJob* jobs, const uint32_t* item_job, uint32_t nitems, uint32_t lds_cap,
-                   Recorder& rec) {
+template <uint32_t RPT, bool kOne>
+void direct_join_t(const DirectJob* jobs, const uint32_t* item_job, const DirectJob& one, uint32_t nitems,
+                   uint32_t lds_cap, Recorder& rec) {
     const size_t lds = join_lds_bytes(lds_cap, 0, true);
-    allow_lds((const void*)k_direct_join<RPT>, lds);
+    allow_lds((const void*)k_direct_join<RPT, kOne>, lds);
     rec.before("direct_join");
-    hipLaunchKernelGGL(k_direct_join<RPT>, dim3(nitems), dim3(kJoinBlock), lds, rec.stream, jobs, item_job,
-                       lds_cap);
+    hipLaunchKernelGGL((k_direct_join<RPT, kOne>), dim3(nitems), dim3(kJoinBlock), lds, rec.stream, jobs, item_job, one,
+                       rec.err_clear, lds_cap);
     rec.after();
+}
+
+template <bool kOne>
+void direct_join_rpt(const DirectJob* jobs, const uint32_t* item_job, const DirectJob& one, uint32_t nitems,
+                     uint32_t lds_cap, Recorder& rec) {
+    switch (join_rpt(lds_cap)) {
+        case kRptSmall: direct_join_t<kRptSmall, kOne>(jobs, item_job, one, nitems, lds_cap, rec); break;
+        case kRptMid: direct_join_t<kRptMid, kOne>(jobs, item_job, one, nitems, lds_cap, rec); break;
+        default: direct_join_t<kRptLarge, kOne>(jobs, item_job, one, nitems, lds_cap, rec); break;
+    }
 }
 
 void direct_join(const DirectJob* jobs, const uint32_t* item_job, uint32_t nitems, uint32_t lds_cap,
                  Recorder& rec) {
     if (nitems == 0) return;
-    switch (join_rpt(lds_cap)) {
-        case kRptSmall: direct_join_t<kRptSmall>(jobs, item_job, nitems, lds_cap, rec); break;
-        case kRptMid: direct_join_t<kRptMid>(jobs, item_job, nitems, lds_cap, rec); break;
-        default: direct_join_t<kRptLarge>(jobs, item_job, nitems, lds_cap, rec); break;
-    }
+    direct_join_rpt<false>(jobs, item_job, DirectJob{}, nitems, lds_cap, rec);
+}
+
+void direct_join_one(const DirectJob& j, uint32_t lds_cap, Recorder& rec) {
+    const uint32_t nitems = (j.n_s + j.chunk - 1) / j.chunk;
+    if (nitems > 1) write_zero_count(j.count, rec);
+    direct_join_rpt<true>(nullptr, nullptr, j, nitems, lds_cap, rec);
 }
 
 void write_zero_count(uint64_t* d_count, Recorder& rec) {

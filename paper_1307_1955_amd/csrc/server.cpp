@@ -106,6 +106,7 @@ hj_status launch_slot(hj_server* sv, SlotDev& s, const std::vector<Core::Req>& r
             d.n_r = (uint32_t)r.job.R.n;
             d.n_s = (uint32_t)r.job.S.n;
             d.item0 = items;
+            d.chunk = hj::kJoinChunk;
             for (uint32_t k = 0; k < it; ++k) s.h_items[items + k] = nd;
             items += it;
             ++nd;

@@ -240,7 +240,7 @@ def calibration_grid(quick: bool = False) -> list[dict]:
     """Join settings whose per-kernel times calibrate the model: PHJ with one and
     two radix passes over a range of fan-outs, tiles and both output modes, the
     direct LDS join, and SHJ, over |R| = 2^10..2^24, |S| = 1..16 x |R| and match
-    rates of 25-100%."""
+    rates of 25-100%, and two scatters up to |R| = 2^27."""
     g = []
     sizes = [1 << e for e in range(10, 25, 2)]
     for n_r in sizes:
@@ -265,6 +265,14 @@ def calibration_grid(quick: bool = False) -> list[dict]:
                         for tile in (4096, 8192):
                             g.append(dict(base, algo="phj", passes=2, bits=(b1, b2), tile=tile, one_pass=True))
                         g.append(dict(base, algo="phj", passes=2, bits=(b1, b2), tile=0, one_pass=False))
+    # two scatters at sizes that need them: long launches, where their bandwidth is all there is
+    for n_r in (1 << 25, 1 << 26, 1 << 27):
+        B = _bits_for(n_r)
+        for b in (B, B + 1, B + 2):
+            for b1 in ((b + 1) // 2, (b + 1) // 2 + 1):
+                for ratio in (1, 2):
+                    g.append(dict(n_r=n_r, n_s=n_r * ratio, match=0.5, algo="phj", passes=2, bits=(b1, b - b1), tile=8192,
+                                  one_pass=True))
     return g[::7] if quick else g
 
 
