@@ -404,7 +404,7 @@ hj_status hj_join_external(const hj_params* p, const hj_rel* R, const hj_rel* S,
    itself; a server marks the requests of such a batch HJ_ERR_DEVICE.
    Failure injection for tests of these paths: the environment variable
    HJ_DEBUG_FAIL_PHASE, read at every call, set to "scan_stall" makes the first
-   tile of every chained scan withhold its status (the waits give
+   tile of every histogram and count scan withhold its status (the waits give
    up after 64 polls), and set to "launch:<phase>" (e.g. "launch:part_scatter") makes that
    launch report a launch failure (HJ_ERR_DEVICE from the call). */
 hj_status hj_workspace_status(const void* ws, void* stream);

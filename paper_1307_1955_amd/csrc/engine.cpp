@@ -458,11 +458,15 @@ hj::Tuple* phj_partition(const Plan& pl, const hj_rel& R, const hj_rel& S, const
     p1.err_clear = rec.err_clear;
     const hj::StartArgs starts{w.cur1, one ? w.start : w.start1, fine ? w.cnt2 : nullptr, w.start, w.st1, w.st2,
                                w.words, r_pairs, pl.lds_cap, one || fine ? pl.P : 0, rec.ctl};
+    // The plan's records are written at offsets from its chained scan and read
+    // without a clamp, so its wait keeps the full bound and no injected stall
+    // (every consumer of the other scans clamps what it reads and writes).
+    const hj::ScanCtl plan_ctl{rec.ctl.err, hj::kMaxStatusPolls, 0};
     hj::SideJob plan;
     plan.kind = hj::kSidePlan;
     plan.blocks = hj::plan_blocks(pl.P, hj::scatter_block(one ? w.tile1 : w.tile2));
     plan.plan = hj::PlanArgs{w.start, n_r, n_s, pl.B, pl.lds_cap, w.pairs, w.item_begin, w.ovf_begin, w.item_rec,
-                             w.ovf_part, zero_total, w.stp, r_pairs, rec.ctl, (uint32_t)w.items_ub};
+                             w.ovf_part, zero_total, w.stp, r_pairs, plan_ctl, (uint32_t)w.items_ub, (uint32_t)w.ovf_ub};
     const hj::ClearTables clr{w.clears ? w.ovf_table : nullptr, w.words, w.start, r_pairs, pl.P, (uint32_t)n_r_tab,
                               pl.lds_cap};
     hj::part_hist(p1, c1, rec);
@@ -584,9 +588,9 @@ void init_recorder(Recorder& rec, hipStream_t stream, uint64_t* err, bool clear)
     rec.ctl.stall = 0;
     rec.fail_phase = nullptr;
     // HJ_DEBUG_FAIL_PHASE (tests of the failure paths, read per call):
-    //   scan_stall     the first tile of every chained scan never publishes and
-    //                  waits give up after 64 polls (every kernel still ends;
-    //                  the call's error word reports it)
+    //   scan_stall     the first tile of every chained scan but the join plan's
+    //                  never publishes and waits give up after 64 polls (every
+    //                  kernel still ends; the call's error word reports it)
     //   launch:<name>  the launch of phase <name> reports a launch failure
     thread_local std::string phase;
     const char* v = getenv("HJ_DEBUG_FAIL_PHASE");

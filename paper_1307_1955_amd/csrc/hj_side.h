@@ -39,7 +39,7 @@ struct PlanArgs {
     ScanCtl ctl;  // the chained scan of the plan reports a give-up here
     // records of item_rec up to here that have no item are written empty (the
     // join kernels' workgroup b takes record b)
-    uint32_t items_ub;
+    uint32_t items_ub, ovf_ub;  // records of item_rec, of ovf_part
 };
 
 enum SideKind : uint32_t { kSideNone = 0, kSideSetup2 = 1, kSidePlan = 2 };
@@ -73,7 +73,8 @@ __device__ __forceinline__ uint32_t ovf_chunks_of(const PartPair& pp, uint32_t l
 // state[0]: ticket; state[1 + b]: status of workgroup b (cleared beforehand).
 // Run by plan_blocks(P, blockDim.x) workgroups.  When the chained scan gives
 // up, its prefixes come out too small, never too large: records overlap, and
-// the last workgroup still empties everything past the last one.
+// the last workgroup still empties everything past the last one.  No record is
+// written past its array, whatever the prefix.
 // start, end: the starts and their end ([2^(total_bits + 1)]); `start` may be LDS.
 __device__ __forceinline__ void join_plan_block(const PlanArgs& A, const uint32_t* start, uint32_t end) {
     const uint32_t n_r = A.n_r, n_s = A.n_s;
@@ -128,10 +129,10 @@ __device__ __forceinline__ void join_plan_block(const PlanArgs& A, const uint32_
         pairs[i] = pp;
         item_begin[i] = ib;
         ovf_begin[i] = ob;
-        for (uint32_t x = 0; x < ni; ++x)
+        for (uint32_t x = 0; x < ni && ib + x < A.items_ub; ++x)
             item_rec[ib + x] = ItemRec{pp.r_off, pp.r_len, pp.s_off + x * kJoinChunk,
                                        min(kJoinChunk, pp.s_len - x * kJoinChunk)};
-        for (uint32_t x = 0; x < no; ++x) ovf_part[ob + x] = i;
+        for (uint32_t x = 0; x < no && ob + x < A.ovf_ub; ++x) ovf_part[ob + x] = i;
     }
     if (i == P - 1) {  // the last pair also writes the totals
         item_begin[P] = ib + ni;
