@@ -496,7 +496,7 @@ hj::Tuple* phj_partition(const Plan& pl, const hj_rel& R, const hj_rel& S, const
 void phj_join_pairs(const Plan& pl, const PhjWs& w, const hj::Tuple* rt, const hj::Tuple* st, const hj_out& out,
                     uint64_t* d_count, hj::Recorder& rec) {
     const hj::OvfBuild ovf{w.pairs, w.ovf_begin, w.ovf_part, w.ovf_begin + pl.P, w.words, rec.ctl.err};
-    if (!w.clears) hj::join_ovf_clear(ovf, pl.P, (uint32_t)w.ovf_ub, w.ovf_table, rec);
+    if (!w.clears) hj::join_ovf_clear(ovf, (uint32_t)w.ovf_ub, w.ovf_table, rec);
     if (!pl.one_pass) {
         hj::join_count(w.item_rec, (uint32_t)w.items_ub, rt, st, pl.lds_cap, pl.B, pl.hash, ovf, w.ovf_table,
                        w.ovf_next, w.hot, w.wave_cnt, pl.nt_s, rec);

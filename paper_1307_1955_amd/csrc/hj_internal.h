@@ -386,7 +386,7 @@ struct OvfBuild {
     uint64_t* err;          // the call's error word
 };
 // Clears the HBM tables where the last scatter did not (ClearTables).
-void join_ovf_clear(const OvfBuild& b, uint32_t P, uint32_t grid, uint64_t* ovf_table, Recorder& rec);
+void join_ovf_clear(const OvfBuild& b, uint32_t grid, uint64_t* ovf_table, Recorder& rec);
 // rt, st: partitioned R and S.  The first of a plan's join launches (the count,
 // or the one-pass write) builds the HBM tables before it probes them.
 // hot: where the build records its hot keys (zeroed before); heavy: the

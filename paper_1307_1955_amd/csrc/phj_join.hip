@@ -39,15 +39,25 @@ __device__ __forceinline__ uint64_t region_slot(int32_t key, uint32_t H) {
     return ((uint64_t)slot_hash(key) * H) >> 32;
 }
 
-__global__ void __launch_bounds__(256) k_ovf_clear(const PartPair* __restrict__ pairs,
-                                                  const uint32_t* __restrict__ ovf_begin,
-                                                  const uint32_t* __restrict__ ovf_part, uint32_t P,
-                                                  uint64_t* __restrict__ ovf_table) {
-    const uint32_t nitems = ovf_begin[P];
+// A value that is equal in all lanes, as a scalar: loops and branches around
+// barriers have to be on scalars, or the compiler may part a wave's lanes there.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return uniform_word(x); }
+
+// Build items of the HBM tables, or 0 when a chained scan of the call gave up
+// (which the call reports): partitions made from wrong starts may share table
+// slots, and a look-up in a table without an empty slot would not end.
+__device__ __forceinline__ uint32_t table_items(const OvfBuild& B) {
+    const uint32_t n = *B.total;
+    if (n == 0) return 0;
+    return uniform((uint32_t)(status_load(B.err) & kErrLookback)) ? 0u : n;
+}
+
+__global__ void __launch_bounds__(256) k_ovf_clear(OvfBuild B, uint64_t* __restrict__ ovf_table) {
+    const uint32_t nitems = table_items(B);
     for (uint32_t item = blockIdx.x; item < nitems; item += gridDim.x) {
-        const uint32_t i = ovf_part[item];
-        const uint32_t c = item - ovf_begin[i];
-        const PartPair pp = pairs[i];
+        const uint32_t i = B.part[item];
+        const uint32_t c = item - B.begin[i];
+        const PartPair pp = B.pairs[i];
         uint64_t* region = ovf_table + 2ull * pp.r_off;
         const uint64_t H = 2ull * pp.r_len;
         const uint32_t chunk = ovf_chunk(pp.r_len);
@@ -67,10 +77,6 @@ struct ItemLoc {
     uint32_t r_off, r_len;
     uint32_t s_begin, s_n;
 };
-
-// A value that is equal in all lanes, as a scalar: loops and branches around
-// barriers have to be on scalars, or the compiler may part a wave's lanes there.
-__device__ __forceinline__ uint32_t uniform(uint32_t x) { return uniform_word(x); }
 
 // The HBM tables of the oversized partitions, built inside the join launch that
 // probes them first: a workgroup claims build items (ovf_chunk rows of a
@@ -561,7 +567,7 @@ __global__ void __launch_bounds__(kJoinBlock) __attribute__((amdgpu_waves_per_eu
     const uint32_t w = threadIdx.x / kWave;
     const uint32_t lane = lane_id();
     const ItemLoc L = locate_item(item_rec);
-    const uint32_t novf = *B.total;  // uniform
+    const uint32_t novf = table_items(B);  // uniform
     const Tuple* __restrict__ stp = st + L.s_begin;
     const bool mine = novf && L.live && L.r_len > lds_cap;  // uniform
     if (mine || blockIdx.x < novf) {
@@ -715,7 +721,7 @@ k_join_write(const ItemRec* __restrict__ item_rec, uint32_t bits, WriteArgs A, O
     __shared__ uint64_t wtot[kJoinWaves + 1];
     __shared__ uint32_t s_word;
     const uint32_t w = threadIdx.x / kWave;
-    const uint32_t novf = *B.total;  // uniform: build items of HBM tables
+    const uint32_t novf = table_items(B);  // uniform
     const bool helper = kOnePass && blockIdx.x >= A.item_grid;
     if (helper && !novf) return;
     ItemLoc L{};
@@ -877,11 +883,11 @@ uint32_t join_grid(uint32_t P, uint64_t n_s) {
     return (uint32_t)((items + 8 * kItemGroup - 1) / (8 * kItemGroup) * (8 * kItemGroup));  // item_of_block
 }
 
-void join_ovf_clear(const OvfBuild& b, uint32_t P, uint32_t grid, uint64_t* ovf_table, Recorder& rec) {
+void join_ovf_clear(const OvfBuild& b, uint32_t grid, uint64_t* ovf_table, Recorder& rec) {
     if (grid == 0) return;
     grid = grid < kOvfGrid ? grid : kOvfGrid;  // grid-stride: few chunks in the common case
     rec.before("ovf_clear");
-    hipLaunchKernelGGL(k_ovf_clear, dim3(grid), dim3(256), 0, rec.stream, b.pairs, b.begin, b.part, P, ovf_table);
+    hipLaunchKernelGGL(k_ovf_clear, dim3(grid), dim3(256), 0, rec.stream, b, ovf_table);
     rec.after();
 }
 
