@@ -179,7 +179,7 @@ hj_status check_params(const hj_params* p, uint64_t n_r, uint64_t n_s, Plan* pl)
 struct PhjWs {
     uint64_t* err;
     hj::Tuple* A;        // partitioned R, then S: of pass 1, or of a plan's only scatter
-    hj::Tuple* B;        //   of pass 2
+    hj::Tuple* B;        //   of pass 2 (two scatters)
     hj::PartSeg* segs2;  // two scatters
     uint32_t* tb2;
     uint32_t* tseg2;
@@ -232,8 +232,8 @@ PhjWs phj_layout(const Plan& pl, uint64_t n_r, uint64_t n_s, uint64_t n_r_tab, v
     w.h = hj::hist_rows(w.tiles1, hj::cursor_replicas(w.tiles1), cbits);
     w.err = c.take<uint64_t>(1);
     w.A = c.take<hj::Tuple>(n);
-    if (pl.passes == 2) w.B = c.take<hj::Tuple>(n);  // (two passes that run as one scatter leave it unused)
     if (!one) {
+        w.B = c.take<hj::Tuple>(n);
         w.tile2 = hj::scatter_tile(pl.tile, pl.b2, n);
         w.tiles2_ub = cdiv(n, w.tile2) + 2ull * pl.P1;
         w.segs2 = c.take<hj::PartSeg>(2ull * pl.P1);
@@ -257,17 +257,29 @@ PhjWs phj_layout(const Plan& pl, uint64_t n_r, uint64_t n_s, uint64_t n_r_tab, v
     static_assert(sizeof(hj::HotKeys) % sizeof(uint64_t) == 0, "hot keys in whole words");
     constexpr uint64_t kHeavyWords = sizeof(hj::HeavyQueue) / sizeof(uint64_t);
     constexpr uint64_t kHotWords = sizeof(hj::HotKeys) / sizeof(uint64_t);
+    // Words that only launches before the first join launch use lie in the wave
+    // counts' too, past the starts (at least 13 rows of P words are free there):
+    // the first scatter's cursors, and the histogram's rows.  Rows that the
+    // starts launch sums lie where copy A will when they fit; a histogram of few
+    // tuples into many partitions makes fewer rows rather than grow the workspace.
+    uint64_t spare = (2ull * pl.P + 1 + kAlign / 4 - 1) / (kAlign / 4) * (kAlign / 4);
+    const uint64_t spare_end = w.items_ub * hj::kJoinWaves * 2;
+    auto take_spare = [&](uint64_t words) {
+        if (words > spare_end - spare) return c.take<uint32_t>(words);
+        uint32_t* p = w.start ? w.start + spare : nullptr;
+        spare += (words + kAlign / 4 - 1) / (kAlign / 4) * (kAlign / 4);
+        return p;
+    };
     if (w.self) {
-        w.rows = c.take<uint32_t>(w.tiles1 << cbits);
+        w.rows = take_spare(w.tiles1 << cbits);
     } else {
-        // the rows are read by the last launch before the one that first writes
-        // a copy: they lie where copy A will
-        const uint64_t fine = !one && !hist2 ? (uint64_t)w.h.rows() << bits1 : 0;
-        const uint64_t words = ((uint64_t)w.h.rows() << cbits) + fine;
-        w.rows = 4 * words <= 8 * n ? reinterpret_cast<uint32_t*>(w.A) : c.take<uint32_t>(words);
+        w.cur1 = take_spare(2ull * w.h.nx() * Pc);
+        const uint64_t fine = !one && !hist2 ? (uint64_t)1 << bits1 : 0, row = ((uint64_t)1 << cbits) + fine;
+        while (w.h.log_groups && w.h.rows() * row > std::max(2 * n, spare_end - spare)) --w.h.log_groups;
+        const uint64_t words = w.h.rows() * row;
+        w.rows = words <= 2 * n ? reinterpret_cast<uint32_t*>(w.A) : take_spare(words);
         if (fine) w.rows1 = w.rows ? w.rows + ((uint64_t)w.h.rows() << cbits) : nullptr;
     }
-    if (!w.self) w.cur1 = c.take<uint32_t>(2ull * w.h.nx() * Pc);
     if (!one && !hist2) w.cnt2 = c.take<uint32_t>(2ull * pl.P);
     const uint64_t c2 = hist2 ? pl.P : 0;  // 64-bit words of a pass-2 histogram's counts
     const uint64_t n1 = w.self ? 0 : hj::start_state_words(Pc);

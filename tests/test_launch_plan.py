@@ -54,3 +54,33 @@ def test_injected_stall_spares_the_join_plan(exe, mode, bits):
     plans = [f["plan"] for _, f in seq if "plan" in f]
     assert plans and set(plans) == {"%d/0" % (1 << 20)}
     assert {f["scan"] for k, f in seq if k == "k_part_starts"} <= {"64/1"}
+
+
+# (mode, |R|, |S|, options, bytes that were enough before two passes could be one scatter)
+ENOUGH = [
+    ("join", 1 << 20, 1 << 24, dict(algo=AUTO), 166010368),
+    ("join", 390000, 22800000, dict(algo=AUTO), 196460544),
+    ("join", 1 << 24, 1 << 24, dict(bits=(6, 6)), 891502336),
+    ("join", 100000, 100000, dict(bits=(1, 2)), 5231872),
+    ("join", 5000, 300, dict(bits=(9, 8)), 15485952),
+    ("join", 48000, 700, dict(bits=(13,), tile=1024), 3838464),
+    ("join", 5749, 281242, dict(bits=(5, 7), tile=1024), 6472960),
+    ("build", 1200000, 1, dict(bits=(2, 10), tile=1024), 24702464),
+    ("build", 66791, 1, dict(bits=(6, 6), tile=1024), 1899008),
+    ("build", 42, 1, dict(bits=(13,), lds_cap=4096), 937728),
+    ("build", 3400000, 1, dict(bits=(7, 6)), 62791168),
+]
+
+
+@pytest.mark.parametrize("case", range(len(ENOUGH)))
+def test_workspaces_have_not_grown(exe, case):
+    """A program's or a server slot's fixed workspace stays enough for the calls it was enough for."""
+    mode, n_r, n_s, kw, enough = ENOUGH[case]
+    assert launches(exe, mode, n_r, n_s, **kw)[1][mode] <= enough
+
+
+@pytest.mark.parametrize("n", [1000, 1 << 17, 1 << 24])
+def test_two_passes_of_one_scatter_need_one_copy(exe, n):
+    """12 bits as two passes of 6 are the same launches in the same workspace."""
+    tile = 4096  # (one pass of 12 bits has larger tiles by default)
+    assert launches(exe, "join", n, n, bits=(6, 6), tile=tile) == launches(exe, "join", n, n, bits=(12,), tile=tile)
