@@ -238,25 +238,29 @@ void auto_params(uint64_t n_r, uint64_t n_s, hj_params* p) {
     uint32_t B = 0;
     while (B < kMaxRadixBits && (n_r >> B) > 4096) ++B;
     for (uint32_t b = (B > 2 ? B - 2 : 1); b <= std::min(B + 2, kMaxRadixBits); ++b) {
-        {
-            q.tile = base.tile;  // 0: the size rule
-            if (b <= 13) {
-                q.passes = 1;
-                q.bits[0] = b;
-                q.bits[1] = 0;
-                consider(q);
-            }
-            // up to kFuseBits one scatter, however the bits are split: another plan only by its tile
-            const bool same = b <= kFuseBits && (base.tile || default_tile(n_r, n_s, 2, b / 2) == default_tile(n_r, n_s, 1, b));
-            if (b >= 2 && !same) {
-                q.passes = 2;
-                for (uint32_t b1 = std::max(1u, b / 2 - 1); b1 <= std::min(13u, b / 2 + 2); ++b1) {
-                    if (b - b1 < 1 || b - b1 > 13) continue;
-                    q.bits[0] = b1;
-                    q.bits[1] = b - b1;
-                    consider(q);
-                }
-            }
+        q.tile = base.tile;  // 0: the size rule
+        if (b <= 13) {
+            q.passes = 1;
+            q.bits[0] = b;
+            q.bits[1] = 0;
+            consider(q);
+        }
+        if (b < 2) continue;
+        if (b <= kFuseBits) {
+            // one scatter however the bits are split: another plan only by the tile that the rule gives two
+            // passes (one pass with that tile: two passes reserve a second copy of the tuples)
+            const uint32_t two = default_tile(n_r, n_s, 2, b / 2);
+            if (base.tile || two == default_tile(n_r, n_s, 1, b)) continue;
+            q.tile = two;
+            consider(q);
+            continue;
+        }
+        q.passes = 2;
+        for (uint32_t b1 = std::max(1u, b / 2 - 1); b1 <= std::min(13u, b / 2 + 2); ++b1) {
+            if (b - b1 < 1 || b - b1 > 13) continue;
+            q.bits[0] = b1;
+            q.bits[1] = b - b1;
+            consider(q);
         }
     }
     *p = best;

@@ -232,8 +232,10 @@ PhjWs phj_layout(const Plan& pl, uint64_t n_r, uint64_t n_s, uint64_t n_r_tab, v
     w.h = hj::hist_rows(w.tiles1, hj::cursor_replicas(w.tiles1), cbits);
     w.err = c.take<uint64_t>(1);
     w.A = c.take<hj::Tuple>(n);
+    // (plans of two passes have always reserved two copies: one scatter leaves
+    // the second unused, and HJ_AUTO asks for one pass where one will do)
+    if (pl.passes == 2) w.B = c.take<hj::Tuple>(n);
     if (!one) {
-        w.B = c.take<hj::Tuple>(n);
         w.tile2 = hj::scatter_tile(pl.tile, pl.b2, n);
         w.tiles2_ub = cdiv(n, w.tile2) + 2ull * pl.P1;
         w.segs2 = c.take<hj::PartSeg>(2ull * pl.P1);
@@ -271,7 +273,8 @@ PhjWs phj_layout(const Plan& pl, uint64_t n_r, uint64_t n_s, uint64_t n_r_tab, v
         return p;
     };
     if (w.self) {
-        w.rows = take_spare(w.tiles1 << cbits);
+        const uint64_t words = w.tiles1 << cbits;
+        w.rows = pl.passes == 2 && words <= 2 * n ? reinterpret_cast<uint32_t*>(w.B) : take_spare(words);
     } else {
         w.cur1 = take_spare(2ull * w.h.nx() * Pc);
         const uint64_t fine = !one && !hist2 ? (uint64_t)1 << bits1 : 0, row = ((uint64_t)1 << cbits) + fine;

@@ -79,8 +79,11 @@ def test_workspaces_have_not_grown(exe, case):
     assert launches(exe, mode, n_r, n_s, **kw)[1][mode] <= enough
 
 
-@pytest.mark.parametrize("n", [1000, 1 << 17, 1 << 24])
-def test_two_passes_of_one_scatter_need_one_copy(exe, n):
-    """12 bits as two passes of 6 are the same launches in the same workspace."""
-    tile = 4096  # (one pass of 12 bits has larger tiles by default)
-    assert launches(exe, "join", n, n, bits=(6, 6), tile=tile) == launches(exe, "join", n, n, bits=(12,), tile=tile)
+@pytest.mark.parametrize("n_r,n_s", [(1 << 20, 15 << 20), (1 << 20, 1 << 24), (390000, 22800000), (1 << 21, 1 << 24),
+                                     (1 << 22, 3 << 22), (1 << 23, 1 << 23)])
+def test_auto_reserves_one_copy_for_one_scatter(exe, n_r, n_s):
+    """HJ_AUTO's plans of up to 12 bits move the tuples once and reserve one copy (8 bytes a tuple,
+    20 bytes a row of R for its tables, and the plan's small parts)."""
+    seq, nbytes = launches(exe, "join", n_r, n_s, algo=AUTO)
+    assert sum(k == "k_part_scatter" for k, _ in seq) == 1
+    assert nbytes["join"] < 8 * (n_r + n_s) + 20 * n_r + (8 << 20)
