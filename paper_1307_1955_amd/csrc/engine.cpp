@@ -483,7 +483,7 @@ hj::Tuple* phj_partition(const Plan& pl, const hj_rel& R, const hj_rel& S, const
     plan.plan = hj::PlanArgs{w.start, n_r, n_s, pl.B, pl.lds_cap, w.pairs, w.item_begin, w.ovf_begin, w.item_rec,
                              w.ovf_part, zero_total, w.stp, r_pairs, plan_ctl, (uint32_t)w.items_ub, (uint32_t)w.ovf_ub};
     const hj::ClearTables clr{w.clears ? w.ovf_table : nullptr, w.words, w.start, r_pairs, pl.P, (uint32_t)n_r_tab,
-                              pl.lds_cap};
+                              pl.lds_cap, hj::clear_share(n_r_tab)};
     hj::part_hist(p1, c1, rec);
     hj::part_starts(p1, c1, starts, rec);
     if (one) {

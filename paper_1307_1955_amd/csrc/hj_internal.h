@@ -311,15 +311,20 @@ void part_starts(const Pass1& p1, const PassCfg& cfg, const StartArgs& st, Recor
 void part_hist2(const Tuple* in, const PartSeg* segs, const uint32_t* tile_begin, const uint32_t* tile_seg,
                 uint32_t nseg, uint32_t grid, const PassCfg& cfg, uint32_t* cnt2, Recorder& rec);
 // HBM tables a scatter clears (two slots per R tuple at twice its position):
-// those of R's partitions of more than lds_cap tuples, when *big is set
-// (self_starts: the scatter's workgroups see for themselves).
+// those of R's partitions of more than lds_cap tuples that S has tuples for,
+// when *big is set (self_starts: the scatter's workgroups see for themselves).
 struct ClearTables {
     uint64_t* table;          // nullptr: nothing to clear
     const uint32_t* big;
-    const uint32_t* start;    // starts of R's npart partitions (positions in R), [npart] = n_r
-    const PartPair* r_pairs;  // instead of start, for a built table
+    const uint32_t* start;    // starts of R's npart partitions (positions in R), then of S's, and their end
+    const PartPair* r_pairs;  // instead of R's starts, for a built table
     uint32_t npart, n_r, lds_cap;
+    // Workgroups that share the clearing: the tiles, or more, which then only clear (a probe of a
+    // large table by few tuples: 16M rows in 256 partitions by one tuple, one tile: 1.9 ms, so 0.08).
+    uint32_t share;
 };
+// (one per CU at most, and 4096 rows, one round of 64 KB, at least)
+inline uint32_t clear_share(uint64_t n_r) { return (uint32_t)(n_r < 4096ull * 256 ? (n_r + 4095) / 4096 : 256); }
 // `side`: extra workgroups appended to the grid that run the next step's setup
 // (hj_side.h: the pass-2 segment table or the join plan).
 struct SideJob;

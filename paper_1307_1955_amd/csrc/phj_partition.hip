@@ -305,14 +305,15 @@ __global__ void __launch_bounds__(BLOCK) k_part_hist2(const Tuple* __restrict__ 
     }
 }
 
-// Clears this workgroup's share (tile of ntiles) of the HBM tables of R's
-// oversized partitions: the slots of R positions [a, b), a partition at a time.
-// begin(i): the first position of R's partition i (i == npart: its end).
-template <typename Begin>
-__device__ __forceinline__ void clear_tables(const ClearTables& C, uint32_t tile, uint32_t ntiles, Begin begin) {
-    const uint32_t per = (uint32_t)(((uint64_t)C.n_r + ntiles - 1) / ntiles);
-    const uint32_t a = (uint32_t)min((uint64_t)tile * per, (uint64_t)C.n_r);
-    const uint32_t b = min(a + per, C.n_r);
+// Clears share c of n of the HBM tables of R's oversized partitions: the slots
+// of R positions [a, b), a partition at a time.  begin(i): the first position
+// of R's partition i (i == npart: its end); probed(i): whether S has tuples
+// for it (else its table is neither built nor read).
+template <typename Begin, typename Probed>
+__device__ __forceinline__ void clear_tables(const ClearTables& C, uint32_t c, uint32_t n, Begin begin, Probed probed) {
+    const uint32_t per = (uint32_t)(((uint64_t)C.n_r + n - 1) / n);
+    const uint32_t a = (uint32_t)min((uint64_t)c * per, (uint64_t)C.n_r);
+    const uint32_t b = (uint32_t)min((uint64_t)a + per, (uint64_t)C.n_r);
     if (a >= b) return;
     uint32_t lo = 0, hi = C.npart;  // the last partition that starts at or before a (uniform)
     while (hi - lo > 1) {
@@ -323,7 +324,7 @@ __device__ __forceinline__ void clear_tables(const ClearTables& C, uint32_t tile
     for (uint32_t i = lo; i < C.npart; ++i) {
         const uint32_t s = begin(i), e = begin(i + 1);
         if (s >= b) break;
-        if (e - s <= C.lds_cap) continue;
+        if (e - s <= C.lds_cap || !probed(i)) continue;
         for (uint32_t j = max(s, a) + threadIdx.x; j < min(e, b); j += blockDim.x)
             slots[j] = make_uint4(~0u, ~0u, ~0u, ~0u);
     }
@@ -406,7 +407,33 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(IPT 
     const uint32_t G = gridDim.x - side.blocks;
     uint32_t tile = kSeg ? live_remap(blockIdx.x, ntiles)  // an XCD's tiles are contiguous: it writes whole segments
                          : blockIdx.x;
-    if (tile >= ntiles) return;
+    // share c of the HBM tables' clearing (rare; uniform)
+    auto clear = [&](uint32_t c) {
+        const uint32_t n = max(ntiles, clr.share);
+        if (kSelf && !clr.r_pairs) {  // R's tiles know R's partitions, and share the clearing among them
+            clear_tables(clr, c, A.nt_r, [&](uint32_t i) { return i < P ? tot[i] : clr.n_r; }, [](uint32_t) { return true; });
+            return;
+        }
+        auto begin = [&](uint32_t i) { return i >= clr.npart ? clr.n_r : clr.r_pairs ? clr.r_pairs[i].r_off : clr.start[i]; };
+        if (kSelf) clear_tables(clr, c, n, begin, [&](uint32_t i) { return (i + 1 < P ? tot[i + 1] : A.n_s) != tot[i]; });
+        else clear_tables(clr, c, n, begin, [&](uint32_t i) { return clr.start[clr.npart + i + 1] != clr.start[clr.npart + i]; });
+    };
+    if (tile >= ntiles) {  // a workgroup that only clears
+        if (!clr.table || tile >= clr.share) return;
+        if (!kSelf) {
+            if (*clr.big != 0) clear(tile);
+            return;
+        }
+        if (!clr.r_pairs || !__syncthreads_or(threadIdx.x < P && clr.r_pairs[threadIdx.x].r_len > clr.lds_cap)) return;
+        for (uint32_t i = threadIdx.x; i < Pp; i += BLOCK) tot[i] = 0;
+        __syncthreads();
+        sum_rows<BLOCK>(A.rows, P, A.nt_r, A.ntiles, 0u, tot, nullptr);
+        __syncthreads();
+        lds_excl_scan(tot, Pp, wt);
+        __syncthreads();
+        clear(tile);
+        return;
+    }
     uint32_t len, lo, n;  // tuples; positions [lo, lo + n) they may take
     uint32_t* cur;
     const uint32_t* st = nullptr;
@@ -550,14 +577,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(IPT 
                 }
             }
         }
-        if (clr.table && (kSelf ? big : *clr.big != 0)) {  // uniform; rare
-            if (clr.r_pairs)
-                clear_tables(clr, tile, ntiles, [&](uint32_t i) { return i < clr.npart ? clr.r_pairs[i].r_off : clr.n_r; });
-            else if (kSelf)
-                clear_tables(clr, tile, A.nt_r, [&](uint32_t i) { return i < P ? tot[i] : clr.n_r; });
-            else
-                clear_tables(clr, tile, ntiles, [&](uint32_t i) { return i < clr.npart ? clr.start[i] : clr.n_r; });
-        }
+        if (clr.table && (kSelf ? big : *clr.big != 0)) clear(tile);
         if (!more) break;
         tile = next;
         __syncthreads();  // the tile's LDS is free again
@@ -628,7 +648,8 @@ void launch_scatter(const ScatterArgs& a, const PassCfg& cfg, const ClearTables&
     }
     allow_lds(k_part_scatter<BLOCK, IPT, kSeg, kNt, kCols, kSelf, kHash>, lds);
     // one workgroup per CU for tiles of more than 8 tuples per thread (kLoop)
-    const uint32_t grid = !kSeg && IPT > 8 && a.grid > kScatterLoopGrid ? kScatterLoopGrid : a.grid;
+    uint32_t grid = !kSeg && IPT > 8 && a.grid > kScatterLoopGrid ? kScatterLoopGrid : a.grid;
+    if (clr.table && grid < clr.share) grid = clr.share;
     rec.before("part_scatter");
     hipLaunchKernelGGL((k_part_scatter<BLOCK, IPT, kSeg, kNt, kCols, kSelf, kHash>), dim3(grid + side.blocks), dim3(BLOCK), lds,
                        rec.stream, a.p1, a.in, a.segs, a.tile_begin, a.tile_seg, a.nseg, cfg, a.start2, a.cur, a.out,

@@ -87,3 +87,11 @@ def test_auto_reserves_one_copy_for_one_scatter(exe, n_r, n_s):
     seq, nbytes = launches(exe, "join", n_r, n_s, algo=AUTO)
     assert sum(k == "k_part_scatter" for k, _ in seq) == 1
     assert nbytes["join"] < 8 * (n_r + n_s) + 20 * n_r + (8 << 20)
+
+
+@pytest.mark.parametrize("bits,lds_cap", [((4,), 0), ((8,), 256), ((6, 6), 256)])
+def test_few_tuples_probing_a_large_table_clear_it_with_the_whole_device(exe, bits, lds_cap):
+    """One tile of S: the scatter that clears the table's partitions has a workgroup per CU."""
+    seq, _ = launches(exe, "probe", 1 << 24, 1000, bits=bits, lds_cap=lds_cap)
+    scatters = [f for k, f in seq if k == "k_part_scatter"]
+    assert len(scatters) == 1 and "clears" in scatters[0] and int(scatters[0]["grid"]) >= 256
