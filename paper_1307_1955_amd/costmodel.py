@@ -164,6 +164,12 @@ def counts_final(passes: int, b1: int, b2: int, n: int) -> bool:
         (counted_pass2(passes, b1, b2) or b1 + b2 <= WIDE_COUNT_BITS) and n >= 400 << (b1 + b2))
 
 
+def tables_expected(n_r: int, P: int, cap: int) -> bool:
+    """Whether a launch of its own builds the HBM tables (csrc/hj_internal.h)."""
+    mean = n_r / P
+    return n_r > cap and mean + 3.0 * math.sqrt(mean) > cap
+
+
 def ovf_chunk(r_part: float) -> int:
     c = OVF_CHUNK
     if r_part > OVF_BIG_PART:
@@ -240,10 +246,13 @@ def launches(plan: dict, n_r: int, n_s: int, m: float) -> list[tuple[str, dict]]
     grid = P + math.ceil(n_s / JOIN_CHUNK)
     s_item = min(max(s_part, 1.0), JOIN_CHUNK)
     chunk = ovf_chunk(r_part)
-    # HBM tables are built by the first join launch
+    # HBM tables are built by the first join launch, or one before it
     build = {"ovf_n": ovf_r, "ovf_items": P * math.ceil(r_part / chunk) if hbm else 0, "per": min(r_part, chunk)}
     if not clears:
         out.append(("ovf_clear", {"bytes": 16.0 * ovf_r}))
+    if tables_expected(n_r, P, cap):
+        out.append(("ovf_build", build))
+        build = {}
     jf = {"items": items, "grid": grid, "r": min(r_part, cap), "s": s_item, "cap": cap, "hbm": int(hbm)}
     if not plan["one_pass"]:
         out.append(("join_count", dict(jf, bytes=4.0 * n, **build)))
@@ -258,6 +267,14 @@ def _part_lat(rounds: int, per_tile: float, c: dict) -> float:
     """Latency term of a partitioning launch: the first round of tiles, then a
     share q_part of each later round (rounds overlap)."""
     return per_tile * (1.0 + (rounds - 1) * c["q_part"])
+
+
+def _build_seconds(f: dict, c: dict) -> float:
+    """Building the HBM tables: inserts, or rounds of items of ovf_chunk() tuples."""
+    if not f.get("ovf_items"):
+        return 0.0
+    turns = math.ceil(f["ovf_items"] / (3.0 * CUS))
+    return max(f["ovf_n"] * c["t_ovf_insert"], turns * math.ceil(f["per"] / 512.0) * c["l_ovf_round"])
 
 
 def kernel_seconds(name: str, f: dict, c: dict) -> float:
@@ -289,15 +306,14 @@ def kernel_seconds(name: str, f: dict, c: dict) -> float:
             lat = c["l_join0"] + c["l_join_r"] * f["r"] + c["l_join_s"] * f["s"]
         lat *= c["f_count"] if name == "join_count" else c["f_1pass"] if name == "join_write_1pass" else 1.0
         rounds = math.ceil(max(f["items"], 1) / join_slots(f["cap"]))
-        build = 0.0
-        if f.get("ovf_items"):
-            turns = math.ceil(f["ovf_items"] / (3.0 * CUS))
-            build = max(f["ovf_n"] * c["t_ovf_insert"], turns * math.ceil(f["per"] / 512.0) * c["l_ovf_round"])
+        build = _build_seconds(f, c)
         # the first round, then its later ones beside the memory traffic
         t = lat + _smooth_max(f["bytes"] / c["bw_join"], (rounds - 1) * lat, c["p_join"])
         if name == "join_write_1pass":
             t = _smooth_max(t, f["items"] * math.ceil(f["s"] / (JOIN_CHUNK / 2)) * c["t_out"], 4.0)
         return d + build + t
+    if name == "ovf_build":
+        return d + _build_seconds(f, c)
     if name == "ovf_clear":
         return d + f["bytes"] / c["bw_fill"]
     if name == "shj_fill":

@@ -181,7 +181,11 @@ double model_seconds(const Plan& pl, uint64_t n_r_, uint64_t n_s_, double m) {
         t += d + 16 * ovf_r / k_bw_fill;  // clear the HBM tables
         nl += 1;
     }
-    if (hbm) {  // the first join launch builds them: inserts, or rounds of items of ovf_chunk() tuples
+    if (tables_expected(n_r_, (uint32_t)P, pl.lds_cap)) {  // a launch before the join builds them
+        t += d;
+        nl += 1;
+    }
+    if (hbm) {  // inserts, or rounds of items of ovf_chunk() tuples
         const double chunk = ovf_chunk((uint32_t)std::min(r_part, 4294967295.0));
         const double turns = std::ceil(P * std::ceil(r_part / chunk) / (3.0 * kCus));
         t += std::max(ovf_r * k_t_ovf_insert, turns * std::ceil(std::min(r_part, chunk) / 512) * k_l_ovf_round);

@@ -8,7 +8,7 @@
 // kFuseBits radix bits a second scatter, the partition pairs planned beside the
 // last one; small joins without the starts launch) -> count -> scan -> write
 // (or one-pass write); the first join launch builds the HBM tables of oversized
-// R partitions.
+// R partitions (where many are expected, a launch before it).
 // Everything is enqueued on one stream; no host synchronisation, no
 // host<->device copy and no allocation happen here.
 #include "engine.h"
@@ -508,10 +508,14 @@ hj::Tuple* phj_partition(const Plan& pl, const hj_rel& R, const hj_rel& S, const
 // PHJ join of the planned partition pairs (Algorithm 1 per pair): count -> scan
 // -> write (or one-pass write).
 // rt: partitioned R, st: partitioned S.
-void phj_join_pairs(const Plan& pl, const PhjWs& w, const hj::Tuple* rt, const hj::Tuple* st, const hj_out& out,
-                    uint64_t* d_count, hj::Recorder& rec) {
-    const hj::OvfBuild ovf{w.pairs, w.ovf_begin, w.ovf_part, w.ovf_begin + pl.P, w.words, rec.ctl.err};
+void phj_join_pairs(const Plan& pl, const PhjWs& w, uint64_t n_r, const hj::Tuple* rt, const hj::Tuple* st,
+                    const hj_out& out, uint64_t* d_count, hj::Recorder& rec) {
+    const bool before = hj::tables_expected(n_r, pl.P, pl.lds_cap);
+    const hj::OvfBuild ovf{w.pairs, w.ovf_begin, w.ovf_part, w.ovf_begin + pl.P, before ? nullptr : w.words, rec.ctl.err};
     if (!w.clears) hj::join_ovf_clear(ovf, (uint32_t)w.ovf_ub, w.ovf_table, rec);
+    if (before)
+        hj::join_ovf_build(ovf, (uint32_t)w.ovf_ub, rt, w.ovf_table, w.ovf_next, w.hot, pl.one_pass ? w.heavy : nullptr,
+                           rec);
     if (!pl.one_pass) {
         hj::join_count(w.item_rec, (uint32_t)w.items_ub, rt, st, pl.lds_cap, pl.B, pl.hash, ovf, w.ovf_table,
                        w.ovf_next, w.hot, w.wave_cnt, pl.nt_s, rec);
@@ -526,7 +530,7 @@ void run_phj(const Plan& pl, const hj_rel& R, const hj_rel& S, const hj_out& out
              uint64_t* d_count, hj::Recorder& rec) {
     const PhjWs w = phj_layout(pl, R.n, S.n, R.n, ws);
     const hj::Tuple* t = phj_partition(pl, R, S, w, R.n, nullptr, pl.one_pass ? d_count : nullptr, rec);
-    phj_join_pairs(pl, w, t, t + R.n, out, d_count, rec);
+    phj_join_pairs(pl, w, R.n, t, t + R.n, out, d_count, rec);
 }
 
 void run_join(const Plan& pl, const hj_rel& R, const hj_rel& S, const hj_out& out, void* ws,
@@ -573,7 +577,7 @@ void run_probe(const Plan& pl, const hj_table& t, const hj_rel& S, const hj_out&
         const PhjWs w = phj_layout(pl, 0, S.n, t.n_r, ws);
         const hj_rel none{nullptr, nullptr, 0};
         const hj::Tuple* s = phj_partition(pl, none, S, w, t.n_r, tw.pairs, pl.one_pass ? d_count : nullptr, rec);
-        phj_join_pairs(pl, w, hj::one_scatter(pl.passes, pl.b1, pl.b2) ? tw.A : tw.B, s, out, d_count, rec);
+        phj_join_pairs(pl, w, t.n_r, hj::one_scatter(pl.passes, pl.b1, pl.b2) ? tw.A : tw.B, s, out, d_count, rec);
     }
 }
 

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <cmath>
+
 namespace hj {
 
 // Partitioned tuples are 64-bit words: the key in the low 32 bits, the rid in
@@ -354,7 +356,7 @@ constexpr uint32_t kJoinChunk = 2 * kJoinSub;  // S tuples per work item (probed
 constexpr uint32_t kOvfChunk = 2048;
 constexpr uint32_t kOvfChunkBig = 16384;
 constexpr uint32_t kOvfBigPart = 1u << 16;
-constexpr uint32_t kOvfGrid = 2048;  // workgroups of the HBM-table clear launch (8 per CU)
+constexpr uint32_t kOvfGrid = 2048;  // workgroups of the HBM-table clear and build launches (8 per CU)
 __host__ __device__ inline uint32_t ovf_chunk(uint32_t r_len) {
     uint32_t c = kOvfChunk;
     if (r_len > kOvfBigPart)
@@ -379,9 +381,20 @@ constexpr uint32_t kItemGroup = 16;  // consecutive join items dealt to one XCD
 // Dynamic LDS bytes of the join kernels for tables of up to lds_cap tuples of a
 // partition on `bits` radix bits (0: a direct join).
 size_t join_lds_bytes(uint32_t lds_cap, uint32_t bits, bool write);
+// Whether the tables are built by a launch of their own before the join: when
+// partitions three standard deviations above the mean do not fit LDS, many have
+// tables and the build is worth a launch; else only a skewed R has any, and the
+// join launch that probes them first builds them.  Measured: 16M x 16M at 8 bits
+// (every partition a table) 2237 us with the build inside the join and 1764
+// before it; 1M x 16M with a tenth of R on one key 237 against 243.
+inline bool tables_expected(uint64_t n_r, uint32_t P, uint32_t lds_cap) {
+    if (n_r <= lds_cap) return false;
+    const double mean = (double)n_r / P;
+    return mean + 3.0 * std::sqrt(mean) > (double)lds_cap;
+}
 // The HBM tables of R's oversized partitions (from the join plan): build items
 // by partition, their number, and the words (zero before) [1], [2] that count
-// items taken and built.
+// items taken and built (nullptr: built by join_ovf_build).
 struct OvfBuild {
     const PartPair* pairs;
     const uint32_t* begin;  // [P + 1]
@@ -392,8 +405,12 @@ struct OvfBuild {
 };
 // Clears the HBM tables where the last scatter did not (ClearTables).
 void join_ovf_clear(const OvfBuild& b, uint32_t grid, uint64_t* ovf_table, Recorder& rec);
+// Builds them (tables_expected).
+void join_ovf_build(const OvfBuild& b, uint32_t grid, const Tuple* rt, uint64_t* ovf_table, uint32_t* ovf_next,
+                    HotKeys* hot, HeavyQueue* heavy, Recorder& rec);
 // rt, st: partitioned R and S.  The first of a plan's join launches (the count,
-// or the one-pass write) builds the HBM tables before it probes them.
+// or the one-pass write) builds the HBM tables before it probes them, when they
+// are not yet built (OvfBuild::words).
 // hot: where the build records its hot keys (zeroed before); heavy: the
 // one-pass queue (nullptr for count -> scan -> write), whose `wait` it sets.
 // item_rec comes from the join plan; grid: join_grid; bits, hash: how R and S are

@@ -78,22 +78,70 @@ struct ItemLoc {
     uint32_t s_begin, s_n;
 };
 
+// Inserts one build item (ovf_chunk rows of a partition) into its HBM table.
+// Every thread of the workgroup calls it.  runs, seen: LDS of a run per wave and
+// of WavePush::kSeen bytes for this wave.
+template <uint32_t kBlock>
+__device__ __forceinline__ void build_item(const OvfBuild& B, uint32_t item, const Tuple* rt, uint64_t* ovf_table,
+                                           uint32_t* ovf_next, HotKeys* hot, HeavyQueue* heavy, WavePush::Run* runs,
+                                           uint8_t* seen) {
+    const uint32_t i = uniform(B.part[item]);
+    const uint32_t c = item - uniform(B.begin[i]);
+    const PartPair pp{uniform(B.pairs[i].r_off), uniform(B.pairs[i].r_len), 0u, uniform(B.pairs[i].s_len)};
+    uint64_t* region = ovf_table + 2ull * pp.r_off;
+    uint32_t* next = ovf_next + pp.r_off;
+    const RegionStep step{2u * pp.r_len};
+    const uint32_t chunk = ovf_chunk(pp.r_len);
+    const uint32_t end = min((c + 1) * chunk, pp.r_len);
+    // a partition the one-pass write may queue tuples of: the write's helpers
+    // wait until its work items are done
+    if (heavy && c == 0 && threadIdx.x == 0 && pp.r_len > kQueueRows) {
+        atomicAdd(&heavy->items_expected, items_of(pp));
+        __hip_atomic_store(&heavy->wait, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    WavePush push;
+    push.hot_keys = hot;
+    for (uint32_t j0 = c * chunk; j0 < end; j0 += kBlock) {  // uniform trip count
+        const uint32_t j = j0 + threadIdx.x;
+        int32_t k = 0;
+        if (j < end) k = key_of(rt[pp.r_off + j]);
+        const uint64_t s = push.claim<2>(region, j < end, k, j, region_slot(k, step.H), step, seen);
+        push.add(region, next, s, k, j);
+    }
+    push.flush_block<kBlock / kWave>(region, next, runs);
+}
+
+// The HBM tables in a launch of their own (tables_expected): workgroups of four
+// waves, which fill a CU, where the join's LDS leaves it three quarters.  What
+// bounds it is the chains of dependent accesses in flight.
+constexpr uint32_t kBuildBlock = 256;
+__global__ void __launch_bounds__(kBuildBlock) k_ovf_build(OvfBuild B, const Tuple* rt, uint64_t* ovf_table,
+                                                          uint32_t* ovf_next, HotKeys* hot, HeavyQueue* heavy) {
+    constexpr uint32_t kWaves = kBuildBlock / kWave;
+    __shared__ WavePush::Run runs[kWaves];
+    __shared__ uint8_t seen[kWaves * WavePush::kSeen];
+    const uint32_t nitems = table_items(B);
+    for (uint32_t item = blockIdx.x; item < nitems; item += gridDim.x)
+        build_item<kBuildBlock>(B, item, rt, ovf_table, ovf_next, hot, heavy, runs,
+                                seen + threadIdx.x / kWave * WavePush::kSeen);
+}
+
 // The HBM tables of the oversized partitions, built inside the join launch that
-// probes them first: a workgroup claims build items (ovf_chunk rows of a
-// partition) until none is left and, with `wait`, returns only when every item
-// is built.  A workgroup waits when all items are claimed, so each is in the
-// hands of a running workgroup that waits for nothing before it is done.
-// Workgroups whose own item needs a table build and wait; of the others the
-// first `nitems` build before they turn to their items (every claim is an atomic
-// on one word: claims by all workgroups, after their items, took the one-pass
-// write of 64K x 16M with a tenth of R on one key from 121 us to 226).
-// A build launch of its own cost every join 6 us, mostly for nothing to build.
-// What bounds a build is its chain of dependent accesses, about 3 us per 512
-// rows; the joins of other partitions run beside it.
+// probes them first (where few partitions have one, else by k_ovf_build): a
+// workgroup claims build items until none is left and, with `wait`, returns
+// only when every item is built.  A workgroup waits when all items are claimed,
+// so each is in the hands of a running workgroup that waits for nothing before
+// it is done.  Workgroups whose own item needs a table build and wait; of the
+// others the first `nitems` build before they turn to their items (every claim
+// is an atomic on one word: claims by all workgroups, after their items, took
+// the one-pass write of 64K x 16M with a tenth of R on one key from 121 us to
+// 226).  A build launch of its own cost every join 6 us, mostly for nothing to
+// build.  What bounds a build is its chain of dependent accesses, about 3 us
+// per 512 rows; the joins of other partitions run beside it.
 // lds: kJoinWaves runs, a word and kJoinWaves * WavePush::kSeen bytes.
 __device__ __forceinline__ void build_tables(const OvfBuild& B, const Tuple* rt, uint64_t* ovf_table,
-                                                      uint32_t* ovf_next, HotKeys* hot, HeavyQueue* heavy,
-                                                      uint32_t nitems, bool wait, uint32_t* lds) {
+                                             uint32_t* ovf_next, HotKeys* hot, HeavyQueue* heavy, uint32_t nitems,
+                                             bool wait, uint32_t* lds) {
     WavePush::Run* runs = reinterpret_cast<WavePush::Run*>(lds);
     uint32_t* s_item = reinterpret_cast<uint32_t*>(runs + kJoinWaves);
     uint8_t* seen = reinterpret_cast<uint8_t*>(s_item + 1) + threadIdx.x / kWave * WavePush::kSeen;
@@ -102,30 +150,7 @@ __device__ __forceinline__ void build_tables(const OvfBuild& B, const Tuple* rt,
         __syncthreads();
         const uint32_t item = uniform(*s_item);
         if (item >= nitems) break;
-        const uint32_t i = uniform(B.part[item]);
-        const uint32_t c = item - uniform(B.begin[i]);
-        const PartPair pp{uniform(B.pairs[i].r_off), uniform(B.pairs[i].r_len), 0u, uniform(B.pairs[i].s_len)};
-        uint64_t* region = ovf_table + 2ull * pp.r_off;
-        uint32_t* next = ovf_next + pp.r_off;
-        const RegionStep step{2u * pp.r_len};
-        const uint32_t chunk = ovf_chunk(pp.r_len);
-        const uint32_t end = min((c + 1) * chunk, pp.r_len);
-        // a partition the one-pass write may queue tuples of: the write's helpers
-        // wait until its work items are done
-        if (heavy && c == 0 && threadIdx.x == 0 && pp.r_len > kQueueRows) {
-            atomicAdd(&heavy->items_expected, items_of(pp));
-            __hip_atomic_store(&heavy->wait, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        WavePush push;
-        push.hot_keys = hot;
-        for (uint32_t j0 = c * chunk; j0 < end; j0 += kJoinBlock) {  // uniform trip count
-            const uint32_t j = j0 + threadIdx.x;
-            int32_t k = 0;
-            if (j < end) k = key_of(rt[pp.r_off + j]);
-            const uint64_t s = push.claim<2>(region, j < end, k, j, region_slot(k, step.H), step, seen);
-            push.add(region, next, s, k, j);
-        }
-        push.flush_block<kJoinWaves>(region, next, runs);
+        build_item<kJoinBlock>(B, item, rt, ovf_table, ovf_next, hot, heavy, runs, seen);
         await_memory();
         __syncthreads();
         if (threadIdx.x == 0) {  // (every wave's stores have reached this XCD's L2)
@@ -570,7 +595,7 @@ __global__ void __launch_bounds__(kJoinBlock) __attribute__((amdgpu_waves_per_eu
     const uint32_t novf = table_items(B);  // uniform
     const Tuple* __restrict__ stp = st + L.s_begin;
     const bool mine = novf && L.live && L.r_len > lds_cap;  // uniform
-    if (mine || blockIdx.x < novf) {
+    if (B.words && (mine || blockIdx.x < novf)) {
         build_tables(B, rt, ovf_table, ovf_next, hot, nullptr, novf, mine, lds);
         __syncthreads();
     }
@@ -728,7 +753,7 @@ k_join_write(const ItemRec* __restrict__ item_rec, uint32_t bits, WriteArgs A, O
     if (!helper) {
         L = locate_item(item_rec);
     }
-    if (kOnePass && novf) {
+    if (kOnePass && novf && B.words) {
         const bool wait = helper || (L.live && L.r_len > A.lds_cap);  // uniform
         if (wait || blockIdx.x < novf) {
             build_tables(B, A.rt, A.ovf_table, A.ovf_next, A.hot, A.heavy, novf, wait, lds);
@@ -888,6 +913,15 @@ void join_ovf_clear(const OvfBuild& b, uint32_t grid, uint64_t* ovf_table, Recor
     grid = grid < kOvfGrid ? grid : kOvfGrid;  // grid-stride: few chunks in the common case
     rec.before("ovf_clear");
     hipLaunchKernelGGL(k_ovf_clear, dim3(grid), dim3(256), 0, rec.stream, b, ovf_table);
+    rec.after();
+}
+
+void join_ovf_build(const OvfBuild& b, uint32_t grid, const Tuple* rt, uint64_t* ovf_table, uint32_t* ovf_next,
+                    HotKeys* hot, HeavyQueue* heavy, Recorder& rec) {
+    if (grid == 0) return;
+    grid = grid < kOvfGrid ? grid : kOvfGrid;
+    rec.before("ovf_build");
+    hipLaunchKernelGGL(k_ovf_build, dim3(grid), dim3(kBuildBlock), 0, rec.stream, b, rt, ovf_table, ovf_next, hot, heavy);
     rec.after();
 }
 

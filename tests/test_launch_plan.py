@@ -95,3 +95,21 @@ def test_few_tuples_probing_a_large_table_clear_it_with_the_whole_device(exe, bi
     seq, _ = launches(exe, "probe", 1 << 24, 1000, bits=bits, lds_cap=lds_cap)
     scatters = [f for k, f in seq if k == "k_part_scatter"]
     assert len(scatters) == 1 and "clears" in scatters[0] and int(scatters[0]["grid"]) >= 256
+
+
+# (|R|, bits, lds_cap, whether a launch before the join builds the HBM tables)
+BUILDS = [(1 << 26, (6, 6), 0, True), (1 << 24, (6,), 0, True), (1 << 13, (5,), 256, True), (7500, (5,), 256, True),
+          (1 << 25, (6, 6), 0, True), (1 << 24, (6, 6), 0, False), (1 << 20, (8,), 0, False), (6000, (5,), 256, False),
+          (200, (1,), 256, False)]
+
+
+@pytest.mark.parametrize("one_pass", [True, False], ids=["1pass", "2pass"])
+@pytest.mark.parametrize("case", range(len(BUILDS)))
+def test_expected_tables_are_built_before_the_join(exe, case, one_pass):
+    """Mean partitions near or past lds_cap: most have a table, built by a launch that fills the device;
+    else the first join launch builds the few that a skewed R has."""
+    n_r, bits, cap, before = BUILDS[case]
+    for mode in ("join", "probe"):
+        seq = [k for k, _ in launches(exe, mode, n_r, 100000, bits=bits, lds_cap=cap, one_pass=one_pass)[0]]
+        assert ("k_ovf_build" in seq) == before
+        assert not before or seq.index("k_ovf_build") + 1 == seq.index("k_join_write" if one_pass else "k_join_count")
