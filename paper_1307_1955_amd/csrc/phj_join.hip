@@ -23,6 +23,7 @@
 // reserves each round's pairs on a running total (Section 3.3's dynamic
 // output allocation replaced by counting or by block reservation).
 #include <algorithm>
+#include <type_traits>
 
 #include "hj_device.h"
 #include "hj_heavy.h"
@@ -177,6 +178,14 @@ __device__ __forceinline__ void build_tables(const OvfBuild& B, const Tuple* rt,
 }
 
 constexpr uint32_t kSU = kSubJ / kWave;  // S tuples per lane of a probe round
+// Small work items (up to kJoinBlock R and kFewU kJoinBlock S tuples) have code of
+// their own: one round of the build instead of RPT, and their S tuples spread
+// over the waves, kFewU groups of 64 each, where kSU groups in the first wave
+// left seven idle.  Items of 256 x 256 tuples (1M x 1M, 2^12 partitions): count
+// 28.0 to 18.3 us, write 38.0 to 15.4.  Larger items keep full waves: every step
+// of a chain reads for all kSU groups of a wave, whether they hold a tuple or not
+// (1024 x 1024 spread over the waves: count 31 to 36 us, write 43 to 52).
+constexpr uint32_t kFewU = 2;
 
 static_assert(kRptLarge * kJoinBlock == kMaxLdsCap, "largest build covers kMaxLdsCap");
 
@@ -245,11 +254,14 @@ struct LdsTable {
     uint32_t keep;  // the radix-hash bits above the partition's
 };
 
-__device__ __forceinline__ LdsTable lds_table(uint32_t* lds, uint32_t cap, uint32_t bits) {
-    const TableShape t = table_shape(cap, bits);
+// small: a table of up to kJoinBlock rows, with 1024 buckets to clear (or as many
+// as leave the links their bits) whatever the capacity.
+__device__ __forceinline__ LdsTable lds_table(uint32_t* lds, uint32_t cap, uint32_t bits, bool small = false) {
+    TableShape t = table_shape(cap, bits);
     LdsTable v;
     v.heads = lds;
     v.rec = lds + (1u << t.log2H);
+    if (small) t.log2H = min(t.log2H, t.link_bits > bits + 10 ? t.link_bits - bits : 10u);
     v.rid = v.rec + cap + 2 * kWave;
     v.cap = cap;
     v.log2H = t.log2H;
@@ -274,7 +286,7 @@ __device__ __forceinline__ uint32_t mixed(const LdsTable& v, int32_t key) {
 // a lane past n exchanges on a spare row.
 template <uint32_t RPT, uint32_t kHash, bool kRids>
 __device__ __forceinline__ void build_lds(const int32_t* k, const int32_t* rid, uint32_t n, const LdsTable& v) {
-    constexpr uint32_t kGroup = RPT % 4 == 0 ? 4 : 3;
+    constexpr uint32_t kGroup = RPT == 1 ? 1 : RPT % 4 == 0 ? 4 : 3;
     static_assert(RPT % kGroup == 0, "whole groups");
     uint4* heads = reinterpret_cast<uint4*>(v.heads);
     for (uint32_t x = threadIdx.x; x < (1u << v.log2H) / 4; x += kJoinBlock)
@@ -329,13 +341,13 @@ __device__ __forceinline__ ItemLoc locate_item(const ItemRec* __restrict__ item_
 }
 
 // S keys and rids of this lane for the wave's range of the item from wb on,
-// of the item's s_n >= 1 tuples.  Lanes past the end load the last tuple again:
+// kU groups of 64 of the item's s_n >= 1 tuples.  Lanes past the end load the last tuple again:
 // behind a branch each load would be awaited on its own (kNt: non-temporal loads, for large joins; see kNtMinTuples).
-template <bool kNt>
+template <uint32_t kU, bool kNt>
 __device__ __forceinline__ void load_s(const Tuple* __restrict__ st, uint32_t wb, uint32_t s_n, int32_t* q,
                                        int32_t* qr) {
 #pragma unroll
-    for (uint32_t u = 0; u < kSU; ++u) {
+    for (uint32_t u = 0; u < kU; ++u) {
         const uint32_t j = wb + u * kWave + lane_id();
         const Tuple* a = st + min(j, s_n - 1);
         const uint64_t t = kNt ? __builtin_nontemporal_load(a) : *a;
@@ -344,10 +356,11 @@ __device__ __forceinline__ void load_s(const Tuple* __restrict__ st, uint32_t wb
     }
 }
 // The same from two columns (direct joins).
+template <uint32_t kU>
 __device__ __forceinline__ void load_s(const int32_t* __restrict__ skp, const int32_t* __restrict__ srp, uint32_t wb,
                                        uint32_t s_n, int32_t* q, int32_t* qr) {
 #pragma unroll
-    for (uint32_t u = 0; u < kSU; ++u) {
+    for (uint32_t u = 0; u < kU; ++u) {
         const uint32_t j = wb + u * kWave + lane_id();
         const uint32_t i = min(j, s_n - 1);
         q[u] = skp[i];
@@ -355,20 +368,20 @@ __device__ __forceinline__ void load_s(const int32_t* __restrict__ skp, const in
     }
 }
 
-// p1-p4 for the lane's kSU S keys against the LDS table, without branches per
+// p1-p4 for the lane's kU S keys against the LDS table, without branches per
 // key: the chain heads of all keys are read first, then the chains are walked
 // in lockstep (each step reads the current record of every key; an ended chain
-// stays at row cap), so each step keeps kSU LDS reads in flight and a wave runs
+// stays at row cap), so each step keeps kU LDS reads in flight and a wave runs
 // only as many steps as its longest chain.
 // cf[u] = matches | first << 16 (16-bit halves: rows < 2^16), first = row of
 // the first match met (cap when there is none).  m[u] becomes the record's part
 // of the key.
-template <uint32_t kHash>
+template <uint32_t kU, uint32_t kHash>
 __device__ __forceinline__ void probe_lds(const LdsTable& v, const int32_t* q, uint32_t wb, uint32_t we, uint32_t* m,
                                           uint32_t* cf) {
-    uint32_t h[kSU];
+    uint32_t h[kU];
 #pragma unroll
-    for (uint32_t u = 0; u < kSU; ++u) {
+    for (uint32_t u = 0; u < kU; ++u) {
         const bool ok = wb + u * kWave + lane_id() < we;
         m[u] = mixed<kHash>(v, q[u]);
         const uint32_t head = v.heads[m[u] >> (32 - v.log2H)];
@@ -379,14 +392,14 @@ __device__ __forceinline__ void probe_lds(const LdsTable& v, const int32_t* q, u
     while (true) {
         bool live = false;
 #pragma unroll
-        for (uint32_t u = 0; u < kSU; ++u) live |= h[u] != v.cap;
+        for (uint32_t u = 0; u < kU; ++u) live |= h[u] != v.cap;
         if (__ballot(live) == 0) break;
-        uint32_t rc[kSU];
+        uint32_t rc[kU];
 #pragma unroll
-        for (uint32_t u = 0; u < kSU; ++u) rc[u] = v.rec[h[u]];
+        for (uint32_t u = 0; u < kU; ++u) rc[u] = v.rec[h[u]];
         __builtin_amdgcn_sched_barrier(0);  // keep the step's reads together, in flight at once
 #pragma unroll
-        for (uint32_t u = 0; u < kSU; ++u) {
+        for (uint32_t u = 0; u < kU; ++u) {
             const bool hit = (rc[u] ^ m[u]) <= v.link_mask && h[u] != v.cap;
             const uint32_t first = (cf[u] & 0xFFFFu) == 0 ? h[u] << 16 : cf[u];
             cf[u] = hit ? (first & 0xFFFF0000u) | ((cf[u] & 0xFFFFu) + 1u) : cf[u];
@@ -478,10 +491,11 @@ __device__ __forceinline__ uint64_t block_reserve(T mine, unsigned long long* to
     return pos0;
 }
 
+template <uint32_t kU>
 __device__ __forceinline__ uint32_t lane_pairs_lds(const uint32_t* cf) {
     uint32_t m = 0;
 #pragma unroll
-    for (uint32_t u = 0; u < kSU; ++u) m += cf[u] & 0xFFFFu;
+    for (uint32_t u = 0; u < kU; ++u) m += cf[u] & 0xFFFFu;
     return m;
 }
 
@@ -489,6 +503,7 @@ __device__ __forceinline__ uint32_t lane_pairs_lds(const uint32_t* cf) {
 // by match counts); returns the slot after the wave's last pair.  LDS table.
 // A round of a wave has fewer than 2^32 pairs (kSubJ keys x kMaxLdsCap
 // matches), so slots are 32-bit offsets from the wave's uniform base.
+template <uint32_t kU>
 __device__ __forceinline__ uint64_t write_round_lds(const LdsTable& v, const uint32_t* m, const int32_t* qr,
                                                     const uint32_t* cf, uint64_t pos0, uint64_t capacity,
                                                     int32_t* __restrict__ out_r, int32_t* __restrict__ out_s) {
@@ -497,12 +512,12 @@ __device__ __forceinline__ uint64_t write_round_lds(const LdsTable& v, const uin
     const uint32_t room = left > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)left;
     int32_t* __restrict__ o_r = out_r + pos0;
     int32_t* __restrict__ o_s = out_s + pos0;
-    int32_t rid0[kSU];  // (row cap + 64 .. hold no rid, but are readable: no branch)
+    int32_t rid0[kU];  // (row cap + 64 .. hold no rid, but are readable: no branch)
 #pragma unroll
-    for (uint32_t u = 0; u < kSU; ++u) rid0[u] = (int32_t)v.rid[cf[u] >> 16];
+    for (uint32_t u = 0; u < kU; ++u) rid0[u] = (int32_t)v.rid[cf[u] >> 16];
     uint32_t done = 0;  // pairs of the wave written so far
 #pragma unroll
-    for (uint32_t u = 0; u < kSU; ++u) {
+    for (uint32_t u = 0; u < kU; ++u) {
         const uint32_t c = cf[u] & 0xFFFFu;
         uint32_t excl, wtotal;
         wave_offsets32(c, &excl, &wtotal);
@@ -568,7 +583,7 @@ __device__ __forceinline__ uint64_t join_count_hbm(const ItemLoc L, uint32_t w, 
     load_hot(hot, sh->hk, sh->hr, &sh->nhk);  // read after the round's barrier
     for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
         const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-        load_s<false>(stp, wb, L.s_n, q, qr);
+        load_s<kSU, false>(stp, wb, L.s_n, q, qr);
         if (threadIdx.x == 0) hs->n = 0;
         __syncthreads();
         uint32_t c[kSU], at[kSU];
@@ -580,6 +595,13 @@ __device__ __forceinline__ uint64_t join_count_hbm(const ItemLoc L, uint32_t w, 
         __syncthreads();  // the set is reused by the next round
     }
     return cnt;
+}
+
+// S tuples per wave of a small item: whole groups of 64.
+__device__ __forceinline__ uint32_t small_share(uint32_t s_n) { return (s_n + kJoinBlock - 1) / kJoinBlock * kWave; }
+
+__device__ __forceinline__ bool small_item(const ItemLoc& L) {
+    return L.r_len <= kJoinBlock && L.s_n <= kFewU * kJoinBlock;
 }
 
 template <uint32_t RPT, bool kNt, uint32_t kHash>
@@ -601,19 +623,24 @@ __global__ void __launch_bounds__(kJoinBlock) __attribute__((amdgpu_waves_per_eu
     }
     uint64_t cnt = 0;
     if (L.live && L.r_len <= lds_cap) {
-        int32_t q[kSU], qr[kSU];
-        int32_t k[RPT], rid[RPT];
-        load_r<RPT>(rt + L.r_off, L.r_len, k, rid);
-        load_s<kNt>(stp, w * kSubJ, L.s_n, q, qr);
-        const LdsTable v = lds_table(lds, lds_cap, bits);
-        build_lds<RPT, kHash, false>(k, rid, L.r_len, v);
-        for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
-            const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-            if (sb) load_s<kNt>(stp, wb, L.s_n, q, qr);
-            uint32_t m[kSU], cf[kSU];
-            probe_lds<kHash>(v, q, wb, we, m, cf);
-            cnt += lane_pairs_lds(cf);
-        }
+        auto run = [&](auto rounds, auto groups) {
+            constexpr uint32_t kR = decltype(rounds)::value, kU = decltype(groups)::value;
+            int32_t q[kU], qr[kU], k[kR], rid[kR];
+            const uint32_t n = kR == 1 ? small_share(L.s_n) : kSubJ;  // per wave
+            load_r<kR>(rt + L.r_off, L.r_len, k, rid);
+            load_s<kU, kNt>(stp, w * n, L.s_n, q, qr);
+            const LdsTable v = lds_table(lds, lds_cap, bits, kR == 1);
+            build_lds<kR, kHash, false>(k, rid, L.r_len, v);
+            for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
+                const uint32_t wb = sb + w * n, we = min(wb + n, L.s_n);
+                if (sb) load_s<kU, kNt>(stp, wb, L.s_n, q, qr);
+                uint32_t m[kU], cf[kU];
+                probe_lds<kU, kHash>(v, q, wb, we, m, cf);
+                cnt += lane_pairs_lds<kU>(cf);
+            }
+        };
+        if (small_item(L)) run(std::integral_constant<uint32_t, 1>(), std::integral_constant<uint32_t, kFewU>());
+        else run(std::integral_constant<uint32_t, RPT>(), std::integral_constant<uint32_t, kSU>());
         cnt = wave_sum(cnt);
     }
     if (mine)
@@ -645,7 +672,7 @@ __device__ __forceinline__ void join_write_hbm(
     load_hot(hot, sh->hk, sh->hr, &sh->nhk);  // read after the round's barrier
     for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
         const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-        load_s<false>(stp, wb, L.s_n, q, qr);
+        load_s<kSU, false>(stp, wb, L.s_n, q, qr);
         if (threadIdx.x == 0) hs->n = hs->queued = 0;
         __syncthreads();
         uint32_t c[kSU], at[kSU];
@@ -763,20 +790,26 @@ k_join_write(const ItemRec* __restrict__ item_rec, uint32_t bits, WriteArgs A, O
     if (!helper) {
         if (L.live && L.r_len <= A.lds_cap) {
             const Tuple* __restrict__ stp = A.st + L.s_begin;
-            int32_t q[kSU], qr[kSU], k[RPT], rid[RPT];
             uint64_t base = kOnePass ? 0ull : A.wave_base[(uint64_t)L.item * kJoinWaves + w];
-            load_r<RPT>(A.rt + L.r_off, L.r_len, k, rid);
-            load_s<kNt>(stp, w * kSubJ, L.s_n, q, qr);
-            const LdsTable v = lds_table(lds, A.lds_cap, bits);
-            build_lds<RPT, kHash, true>(k, rid, L.r_len, v);
-            for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
-                const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, L.s_n);
-                if (sb) load_s<kNt>(stp, wb, L.s_n, q, qr);
-                uint32_t m[kSU], cf[kSU];
-                probe_lds<kHash>(v, q, wb, we, m, cf);
-                const uint64_t pos0 = kOnePass ? block_reserve(lane_pairs_lds(cf), A.total, wtot, sb != 0) : base;
-                base = write_round_lds(v, m, qr, cf, pos0, A.capacity, A.out_r, A.out_s);
-            }
+            auto run = [&](auto rounds, auto groups) {
+                constexpr uint32_t kR = decltype(rounds)::value, kU = decltype(groups)::value;
+                int32_t q[kU], qr[kU], k[kR], rid[kR];
+                const uint32_t n = kR == 1 ? small_share(L.s_n) : kSubJ;  // per wave
+                load_r<kR>(A.rt + L.r_off, L.r_len, k, rid);
+                load_s<kU, kNt>(stp, w * n, L.s_n, q, qr);
+                const LdsTable v = lds_table(lds, A.lds_cap, bits, kR == 1);
+                build_lds<kR, kHash, true>(k, rid, L.r_len, v);
+                for (uint32_t sb = 0; sb < L.s_n; sb += kJoinSub) {
+                    const uint32_t wb = sb + w * n, we = min(wb + n, L.s_n);
+                    if (sb) load_s<kU, kNt>(stp, wb, L.s_n, q, qr);
+                    uint32_t m[kU], cf[kU];
+                    probe_lds<kU, kHash>(v, q, wb, we, m, cf);
+                    const uint64_t pos0 = kOnePass ? block_reserve(lane_pairs_lds<kU>(cf), A.total, wtot, sb != 0) : base;
+                    base = write_round_lds<kU>(v, m, qr, cf, pos0, A.capacity, A.out_r, A.out_s);
+                }
+            };
+            if (small_item(L)) run(std::integral_constant<uint32_t, 1>(), std::integral_constant<uint32_t, kFewU>());
+            else run(std::integral_constant<uint32_t, RPT>(), std::integral_constant<uint32_t, kSU>());
         }
     }
     if (novf) {
@@ -812,16 +845,16 @@ k_direct_join(const DirectJob* __restrict__ jobs, const uint32_t* __restrict__ i
     int32_t k[RPT], rid[RPT];
     load_r<RPT>(J.rk, J.rr, r_len, k, rid);
     int32_t q[kSU], qr[kSU];
-    load_s(skp, srp, w * kSubJ, s_n, q, qr);
+    load_s<kSU>(skp, srp, w * kSubJ, s_n, q, qr);
     const LdsTable v = lds_table(lds, lds_cap, 0u);
     build_lds<RPT, 0, true>(k, rid, r_len, v);
     for (uint32_t sb = 0; sb < s_n; sb += kJoinSub) {
         const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, s_n);
-        if (sb) load_s(skp, srp, wb, s_n, q, qr);
+        if (sb) load_s<kSU>(skp, srp, wb, s_n, q, qr);
         uint32_t m[kSU], cf[kSU];
-        probe_lds<0>(v, q, wb, we, m, cf);
-        const uint64_t pos0 = block_reserve(lane_pairs_lds(cf), (unsigned long long*)J.count, wtot, sb != 0);
-        write_round_lds(v, m, qr, cf, pos0, J.capacity, J.out_r, J.out_s);
+        probe_lds<kSU, 0>(v, q, wb, we, m, cf);
+        const uint64_t pos0 = block_reserve(lane_pairs_lds<kSU>(cf), (unsigned long long*)J.count, wtot, sb != 0);
+        write_round_lds<kSU>(v, m, qr, cf, pos0, J.capacity, J.out_r, J.out_s);
     }
 }
 
