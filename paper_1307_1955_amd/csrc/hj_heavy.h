@@ -135,13 +135,15 @@ __device__ __forceinline__ void heavy_counts(Col rk, Len r_len, HeavySet* hs) {
 
 // Writes the matches of every registered tuple into its slots hs->pos[e] ..
 // hs->pos[e] + cnt - 1, in no particular order: one scan of R per distinct
-// key, kV (<= 32) keys per thread per step; each wave takes slots for its hits
-// of an element with one LDS atomic on the key's fill counter (no barrier in
-// the scan), and consecutive hit lanes write consecutive slots.  Slots at or
-// past `capacity` are not written.  All threads of the block call it, after
-// the positions are set.  kRids: the step's rids are loaded with its keys
-// (more registers, no dependent load per hit).
-template <uint32_t kBlock, uint32_t kV, bool kRids = false, typename Col, typename Len>
+// key, kV (<= 32) keys per thread per step with their rids (no dependent load
+// per hit); each wave takes slots for all its hits of a step with one LDS
+// atomic on the key's fill counter (no barrier in the scan), and consecutive
+// hit lanes write consecutive slots.  Slots at or past `capacity` are not
+// written.  All threads of the block call it, after the positions are set.
+// What bounds it is the latency of a step, of loads and of stores: 1M rows of
+// one key in a partition, one S tuple: a write launch of 2447 us in steps with an
+// LDS atomic and a rid load for each of the kV keys, 883 us so.
+template <uint32_t kBlock, uint32_t kV, typename Col, typename Len>
 __device__ __forceinline__ void heavy_writes(Col rk, Col rr, Len r_len, HeavySet* hs, uint64_t capacity,
                                              int32_t* __restrict__ out_r, int32_t* __restrict__ out_s) {
     constexpr Len kStep = (Len)kV * kBlock;
@@ -158,35 +160,36 @@ __device__ __forceinline__ void heavy_writes(Col rk, Col rr, Len r_len, HeavySet
             // element u of the thread: row j0 + u * kBlock + threadIdx.x; rows
             // past the end read the last row (all loads issue together) and
             // do not count
-            int32_t v[kV], rid[kRids ? kV : 1];
+            int32_t v[kV], rid[kV];
 #pragma unroll
             for (uint32_t u = 0; u < kV; ++u) {
                 const Len j = min(j0 + (Len)u * kBlock + threadIdx.x, r_len - 1);
                 v[u] = rk[j];
-                if (kRids) rid[u] = rr[j];
+                rid[u] = rr[j];
             }
-            uint32_t bits = 0;
+            uint32_t bits = 0, hits = 0;
 #pragma unroll
-            for (uint32_t u = 0; u < kV; ++u)
-                bits |= (j0 + (Len)u * kBlock + threadIdx.x < r_len && v[u] == k) ? 1u << u : 0u;
             for (uint32_t u = 0; u < kV; ++u) {
-                const uint64_t m = __ballot((bits >> u) & 1u);
-                if (m == 0) continue;  // uniform over the wave
-                const int lead = __ffsll((unsigned long long)m) - 1;
-                uint32_t base = 0;
-                if ((int)lane_id() == lead) base = atomicAdd(&fill[e], (uint32_t)__popcll(m));
-                base = __shfl(base, lead);
-                if ((bits >> u) & 1u) {
-                    const uint32_t rank = base + (uint32_t)__popcll(m & lanemask_lt());
-                    const int32_t r = kRids ? rid[kRids ? u : 0] : rr[j0 + (Len)u * kBlock + threadIdx.x];
-                    for (uint32_t e2 = e; e2 < ne; ++e2) {
-                        if (hs->rep[e2] != e) continue;
-                        const uint64_t at = hs->pos[e2] + rank;
-                        if (at < capacity) {
-                            out_r[at] = r;
-                            out_s[at] = hs->srid[e2];
-                        }
+                bits |= (j0 + (Len)u * kBlock + threadIdx.x < r_len && v[u] == k) ? 1u << u : 0u;
+                hits += (uint32_t)__popcll(__ballot((bits >> u) & 1u));
+            }
+            if (hits == 0) continue;  // uniform over the wave
+            uint32_t base = 0;
+            if (lane_id() == 0) base = atomicAdd(&fill[e], hits);
+            base = uniform_word(base);
+            for (uint32_t e2 = e; e2 < ne; ++e2) {
+                if (uniform_word(hs->rep[e2]) != e) continue;
+                uint64_t at = hs->pos[e2] + base;
+                const int32_t srid = hs->srid[e2];
+#pragma unroll
+                for (uint32_t u = 0; u < kV; ++u) {
+                    const uint64_t m = __ballot((bits >> u) & 1u);
+                    const uint64_t to = at + (uint32_t)__popcll(m & lanemask_lt());
+                    if (((bits >> u) & 1u) && to < capacity) {
+                        out_r[to] = rid[u];
+                        out_s[to] = srid;
                     }
+                    at += (uint32_t)__popcll(m);
                 }
             }
         }
