@@ -511,11 +511,12 @@ hj::Tuple* phj_partition(const Plan& pl, const hj_rel& R, const hj_rel& S, const
 void phj_join_pairs(const Plan& pl, const PhjWs& w, uint64_t n_r, const hj::Tuple* rt, const hj::Tuple* st,
                     const hj_out& out, uint64_t* d_count, hj::Recorder& rec) {
     const bool before = hj::tables_expected(n_r, pl.P, pl.lds_cap);
+    // (no partition of fewer rows queues tuples: no helper workgroups then)
+    hj::HeavyQueue* heavy = pl.one_pass && n_r > hj::kQueueRows ? w.heavy : nullptr;
     const hj::OvfBuild ovf{w.pairs, w.ovf_begin, w.ovf_part, w.ovf_begin + pl.P, before ? nullptr : w.words, rec.ctl.err};
     if (!w.clears) hj::join_ovf_clear(ovf, (uint32_t)w.ovf_ub, w.ovf_table, rec);
     if (before)
-        hj::join_ovf_build(ovf, (uint32_t)w.ovf_ub, rt, w.ovf_table, w.ovf_next, w.hot, pl.one_pass ? w.heavy : nullptr,
-                           rec);
+        hj::join_ovf_build(ovf, (uint32_t)w.ovf_ub, rt, w.ovf_table, w.ovf_next, w.hot, heavy, rec);
     if (!pl.one_pass) {
         hj::join_count(w.item_rec, (uint32_t)w.items_ub, rt, st, pl.lds_cap, pl.B, pl.hash, ovf, w.ovf_table,
                        w.ovf_next, w.hot, w.wave_cnt, pl.nt_s, rec);
@@ -523,7 +524,7 @@ void phj_join_pairs(const Plan& pl, const PhjWs& w, uint64_t n_r, const hj::Tupl
     }
     hj::join_write(w.item_rec, (uint32_t)w.items_ub, rt, st, pl.lds_cap, pl.B, pl.hash, ovf, w.ovf_table, w.ovf_next, w.hot,
                    pl.one_pass ? nullptr : w.wave_cnt, d_count, out.rid_r, out.rid_s, out.capacity,
-                   pl.one_pass ? w.heavy : nullptr, pl.nt_s, rec);
+                   heavy, pl.nt_s, rec);
 }
 
 void run_phj(const Plan& pl, const hj_rel& R, const hj_rel& S, const hj_out& out, void* ws,
