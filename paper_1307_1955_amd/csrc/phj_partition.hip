@@ -22,6 +22,8 @@
 // counted by the one histogram up to 15 bits, above by a histogram of pass 2.
 // The paper's partition "buckets" with dynamically allocated storage
 // (Section 3.1, Section 3.3) become contiguous partitions at counted offsets.
+#include <algorithm>
+
 #include "hj_device.h"
 #include "hj_internal.h"
 #include "hj_side.h"
@@ -132,6 +134,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8)))
     for (uint64_t i = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; i < A.nzero; i += (uint64_t)gridDim.x * BLOCK)
         A.zero[i] = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0 && A.err_clear) *A.err_clear = 0;
+    const uint32_t grid = A.self ? A.ntiles : A.h.grid();
+    if (blockIdx.x >= grid) return;  // (many words to clear for few tiles)
     for (uint32_t i = threadIdx.x; i < P; i += BLOCK) cnt[i] = 0;
     const uint32_t nx = A.self ? 1u : A.h.nx();
     const uint32_t x = A.self ? 0u : blockIdx.x & (nx - 1), q = blockIdx.x >> A.h.log_nx;
@@ -167,10 +171,19 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8)))
         if (A.fine_bits) {
             uint32_t* __restrict__ r1 = A.rows1 + (uint64_t)row * P1;
             const uint32_t F = 1u << A.fine_bits;
-            for (uint32_t i = threadIdx.x; i < P1; i += BLOCK) {
-                uint32_t v = 0;
-                for (uint32_t j = 0; j < F; ++j) v += cnt[(i << A.fine_bits) | ((j + i) & (F - 1))];  // (apart in banks)
-                r1[i] = v;
+            if (F >= kWave) {  // a wave per partition (a thread each took 360 us at 2 partitions of 8192 counters)
+                for (uint32_t i = threadIdx.x / kWave; i < P1; i += BLOCK / kWave) {
+                    uint32_t v = 0;
+                    for (uint32_t j = lane_id(); j < F; j += kWave) v += cnt[(i << A.fine_bits) | j];
+                    v = wave_sum(v);
+                    if (lane_id() == 0) r1[i] = v;
+                }
+            } else {
+                for (uint32_t i = threadIdx.x; i < P1; i += BLOCK) {
+                    uint32_t v = 0;
+                    for (uint32_t j = 0; j < F; ++j) v += cnt[(i << A.fine_bits) | ((j + i) & (F - 1))];  // (apart in banks)
+                    r1[i] = v;
+                }
             }
             __syncthreads();
         }
@@ -179,7 +192,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8)))
             r[i] = cnt[i];
             cnt[i] = 0;
         }
-        row = gridDim.x + x;  // S's, after R's
+        row = grid + x;  // S's, after R's
     }
 }
 
@@ -593,7 +606,8 @@ template <uint32_t BLOCK, uint32_t IPT, uint32_t kHash>
 void launch_hist(const Pass1& p1, const PassCfg& cfg, Recorder& rec) {
     static_assert(BLOCK * IPT >= 1024 && BLOCK * IPT <= kMaxScatterTile && BLOCK / kWave <= kScanScratch, "tile shape");
     const size_t lds = sizeof(uint32_t) * (((size_t)1 << (cfg.bits + p1.fine_bits)) + kWave);
-    const uint32_t grid = p1.self ? p1.ntiles : p1.h.grid();
+    // (workgroups past the tiles' clear words only: 4096 rows in 2^18 partitions, one tile, 2 MB to clear)
+    const uint32_t grid = std::max(p1.self ? p1.ntiles : p1.h.grid(), (uint32_t)std::min<uint64_t>(256, p1.nzero / 4096));
     const auto fn = cfg.nt ? k_part_hist<BLOCK, IPT, true, kHash> : k_part_hist<BLOCK, IPT, false, kHash>;
     allow_lds(fn, lds);
     rec.before("part_hist");

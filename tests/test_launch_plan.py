@@ -113,3 +113,11 @@ def test_expected_tables_are_built_before_the_join(exe, case, one_pass):
         seq = [k for k, _ in launches(exe, mode, n_r, 100000, bits=bits, lds_cap=cap, one_pass=one_pass)[0]]
         assert ("k_ovf_build" in seq) == before
         assert not before or seq.index("k_ovf_build") + 1 == seq.index("k_join_write" if one_pass else "k_join_count")
+
+
+def test_histogram_of_few_tuples_clears_with_more_workgroups(exe):
+    """4096 rows into 2^18 partitions: one tile, and 2 MB of counts to clear."""
+    seq, _ = launches(exe, "build", 4096, 1, bits=(9, 9))
+    assert seq[0][0] == "k_part_hist" and int(seq[0][1]["grid"]) >= 64
+    seq, _ = launches(exe, "join", 1 << 20, 1 << 20, bits=(6, 6))
+    assert int(seq[0][1]["grid"]) == 512
