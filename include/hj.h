@@ -106,9 +106,13 @@ typedef struct hj_out {
            splits on the high bits[0] of them, pass 2 on the low bits[1] (up
            to 12 bits in all both passes are made as one scatter).
    hash    an hj_hash value.
-   tile    tuples per partitioning tile: a power of two in 1024..8192, or 0
-           = chosen from the sizes (8192 when |R| + |S| >= 2^25, or >= 2^24
-           with one pass of 8 or more bits; else 4096).
+   tile    tuples per partitioning tile at least: a power of two in 1024..8192,
+           or 0 = chosen from the sizes (8192 when |R| + |S| >= 2^25, or >= 2^24
+           with one pass of 8 or more bits; else 4096).  A pass with tuples
+           enough takes larger tiles: twice the tile, up to 4096, while that
+           leaves 256 tiles; from tiles of 4096 on 8192 at 10, 11 or 13 bits
+           and 16384 at 12 bits, when there are 256 such.  hj_resolve_params
+           gives the tile before this.
    lds_cap largest R partition (tuples) joined from an LDS-resident table:
            0 = chosen from |R| and B; else a multiple of 64 in 256..8192.
            Larger partitions take the HBM-table path.

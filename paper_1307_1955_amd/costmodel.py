@@ -40,8 +40,8 @@ OVF_BIG_PART = 1 << 16
 OVF_GRID = 2048            # workgroups of the HBM-table clear launch
 SHJ_TILE = 2048            # S tuples per SHJ probe workgroup
 SCAN_CHUNK = 2048          # entries per scan workgroup
-COUNTED_MAX_BITS = 13      # two passes of 4..13 bits in all: pass 1 counts the final partitions,
-WIDE_COUNT_BITS = 15       #   from 400 tuples per partition on up to here
+COUNTED_MAX_BITS = 13      # counted_pass2
+WIDE_COUNT_BITS = 15       # the histogram counts the final partitions, from 400 tuples per partition on, up to here
 FUSE_BITS = 12             # radix bits up to which one scatter makes the final partitions
 SELF_BITS, SELF_WORDS = 8, 16384  # starts summed by the scatter's workgroups (csrc/hj_internal.h self_starts)
 
@@ -90,6 +90,8 @@ def shj_slots(n_r: int) -> int:
 
 def scatter_tile(tile: int, bits: int, n: int) -> int:
     """Tuples per scatter workgroup (csrc/hj_internal.h scatter_tile)."""
+    while tile < 4096 and n >= 512 * tile:
+        tile *= 2
     want = 16384 if bits == 12 else 8192 if bits >= 10 else tile
     return tile if tile < 4096 or want <= tile or n < 256 * want else want
 
@@ -150,7 +152,7 @@ def _table_factor(table_bytes: float, gamma: float, base: float = 1 << 20) -> fl
 
 
 def counted_pass2(passes: int, b1: int, b2: int) -> bool:
-    """Two passes whose pass 2 reserves its runs on counts taken in pass 1."""
+    """Two passes of 4..13 bits in all (csrc/hj_internal.h)."""
     return passes == 2 and 4 <= b1 + b2 <= COUNTED_MAX_BITS
 
 
@@ -160,8 +162,7 @@ def one_scatter(passes: int, b1: int, b2: int) -> bool:
 
 def counts_final(passes: int, b1: int, b2: int, n: int) -> bool:
     """Whether the first histogram counts the final partitions."""
-    return one_scatter(passes, b1, b2) or (
-        (counted_pass2(passes, b1, b2) or b1 + b2 <= WIDE_COUNT_BITS) and n >= 400 << (b1 + b2))
+    return one_scatter(passes, b1, b2) or (b1 + b2 <= WIDE_COUNT_BITS and n >= 400 << (b1 + b2))
 
 
 def tables_expected(n_r: int, P: int, cap: int) -> bool:
@@ -218,7 +219,7 @@ def launches(plan: dict, n_r: int, n_s: int, m: float) -> list[tuple[str, dict]]
     final = counts_final(plan["passes"], b1, b2, n)
     tile1 = scatter_tile(tile, B if one else b1, n)
     tiles1 = math.ceil(n_r / tile1) + math.ceil(n_s / tile1)
-    self_starts = one and B <= SELF_BITS and (tiles1 << B) <= SELF_WORDS
+    self_starts = one and B <= SELF_BITS and (tiles1 << B) <= min(SELF_WORDS, 32 * _part_block(tile1))
     cbits = B if final else b1  # what the histogram counts
     grid = tiles1 if self_starts else hist_grid(tiles1, cbits)
     out.append(("part_hist", {"n": n, "grid": grid, "bins": 1 << cbits}))

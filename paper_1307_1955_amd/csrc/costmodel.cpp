@@ -144,7 +144,7 @@ double model_seconds(const Plan& pl, uint64_t n_r_, uint64_t n_s_, double m) {
     const bool one = one_scatter(pl.passes, b1, b2), final = counts_final(pl.passes, b1, b2, nn);
     const uint32_t tile1 = scatter_tile(tile, one ? b1 + b2 : b1, nn);
     const uint64_t tiles1 = (n_r_ + tile1 - 1) / tile1 + (n_s_ + tile1 - 1) / tile1;
-    const bool self = one && self_starts(tiles1, b1 + b2);
+    const bool self = one && self_starts(tiles1, b1 + b2, tile1);
     const uint32_t cbits = final ? b1 + b2 : b1;  // what the histogram counts
     const double hist_grid = self ? (double)tiles1 : (double)hist_rows(tiles1, cursor_replicas(tiles1), cbits).grid();
     const double r_part = n_r / P, s_part = n_s / P;

@@ -228,7 +228,7 @@ PhjWs phj_layout(const Plan& pl, uint64_t n_r, uint64_t n_s, uint64_t n_r_tab, v
     w.tile1 = hj::scatter_tile(pl.tile, one ? pl.B : pl.b1, n);
     w.tiles1 = cdiv(n_r, w.tile1) + cdiv(n_s, w.tile1);
     const uint32_t bits1 = one ? pl.B : pl.b1, cbits = hist2 ? pl.b1 : pl.B;
-    w.self = one && hj::self_starts(w.tiles1, pl.B);
+    w.self = one && hj::self_starts(w.tiles1, pl.B, w.tile1);
     w.h = hj::hist_rows(w.tiles1, hj::cursor_replicas(w.tiles1), cbits);
     w.err = c.take<uint64_t>(1);
     w.A = c.take<hj::Tuple>(n);

@@ -180,9 +180,8 @@ struct PassCfg {
 // loads gained nothing and stay plain).
 constexpr uint64_t kNtMinTuples = 1ull << 24;
 constexpr uint64_t kNtMinBuild = 1ull << 23;
-// Two passes whose final partitions number 2^4..2^kCountedMaxBits are
-// "counted": the histogram of the input counts the final partitions and no
-// later pass has a histogram of its own.
+// Two passes of 4..kCountedMaxBits radix bits in all: plans whose final partitions
+// one histogram can count in any case of size (counts_final says when it does).
 constexpr uint32_t kCountedMaxBits = 13;
 inline bool counted_pass2(uint32_t passes, uint32_t b1, uint32_t b2) {
     return passes == 2 && b1 + b2 >= 4 && b1 + b2 <= kCountedMaxBits;
@@ -199,11 +198,11 @@ inline bool one_scatter(uint32_t passes, uint32_t b1, uint32_t b2) { return pass
 // counters of a workgroup in LDS, 128 KiB); else pass 2 has its own.  Plans of
 // two scatters do so while the workgroups' rows fit the first copy (8 bytes a
 // tuple), where they lie until it is written: up to 520 rows of 4 bytes for each
-// final partition and half as many for pass 1.
+// final partition and half as many for pass 1.  (With fewer rows for fewer tuples
+// 64K x 64K at 7+6 bits took 135 us, 130 with the second histogram.)
 constexpr uint32_t kWideCountBits = 15;
 inline bool counts_final(uint32_t passes, uint32_t b1, uint32_t b2, uint64_t n) {
-    return one_scatter(passes, b1, b2) ||
-           ((counted_pass2(passes, b1, b2) || b1 + b2 <= kWideCountBits) && n >= 400ull << (b1 + b2));
+    return one_scatter(passes, b1, b2) || (b1 + b2 <= kWideCountBits && n >= 400ull << (b1 + b2));
 }
 // Whether the last scatter clears the HBM tables of oversized partitions (it
 // needs the final partitions' sizes before it starts), else a launch of its own.
@@ -212,12 +211,15 @@ inline bool scatter_clears(uint32_t passes, uint32_t b1, uint32_t b2, uint64_t n
     return one_scatter(passes, b1, b2) || (counts_final(passes, b1, b2, n) && counted_clears_tables(b2));
 }
 // Tuples per workgroup of a pass into 2^bits partitions: the plan's tile, or
-// more at a high fan-out, where a 4096-tuple tile's runs would be too short, as
-// long as every CU still has a workgroup.  Measured, 2^25 tuples: 2^10
-// partitions 117 / 105 / 122 us with 4096 / 8192 / 16384 tuples, 2^11 149 / 123
-// / 132 us, 2^12 186 / 190 / 151 us.  Tiles below 4096 are the caller's wish.
+// more, as long as every CU still has a workgroup: at a high fan-out, where a
+// 4096-tuple tile's runs would be too short, and instead of tiles below 4096,
+// each of which reserves its runs as a large one does.  Measured, 2^25 tuples:
+// 2^10 partitions 117 / 105 / 122 us with 4096 / 8192 / 16384 tuples, 2^11 149 /
+// 123 / 132 us, 2^12 186 / 190 / 151 us; 2^6 partitions and
+// 268 MB of HBM tables cleared beside, 200 us with 1024 and 131 with 4096.
 constexpr uint32_t kMaxScatterTile = 16384;
 inline uint32_t scatter_tile(uint32_t tile, uint32_t bits, uint64_t n) {
+    while (tile < 4096 && n >= 256ull * 2 * tile) tile *= 2;
     const uint32_t want = bits == 12 ? kMaxScatterTile : bits >= 10 ? 8192u : tile;
     return tile < 4096 || want <= tile || n < 256ull * want ? tile : want;
 }
@@ -259,11 +261,14 @@ inline HistRows hist_rows(uint64_t tiles, uint32_t nx, uint32_t count_bits) {
 }
 // Small joins: the histogram writes one row per tile and every workgroup of the
 // scatter sums the rows itself, which saves the launch that makes the starts.
-// The rows (kSelfWords words at most) are read by every scatter workgroup.
+// The rows (kSelfWords words at most) are read by every scatter workgroup, up to
+// 32 words a thread (256 rows of 64 counters by 256 threads: a build of 262144
+// rows 24.4 us, 15.0 with the launch).
 constexpr uint32_t kSelfBits = 8;
 constexpr uint32_t kSelfWords = 16384;
-inline bool self_starts(uint64_t tiles, uint32_t bits) {
-    return bits <= kSelfBits && (tiles << bits) <= kSelfWords;
+inline bool self_starts(uint64_t tiles, uint32_t bits, uint32_t tile) {
+    const uint64_t most = 32ull * scatter_block(tile);
+    return bits <= kSelfBits && (tiles << bits) <= (most < kSelfWords ? most : kSelfWords);
 }
 
 // The input of a join's first pass and what its histogram leaves for later

@@ -1,5 +1,5 @@
-"""GPU parity of the histograms that count the final partitions of two scatters: sums per pass-1
-partition by one thread each (fewer than 64 of them) or by a wave, few rows for few tuples."""
+"""GPU parity of the histograms that count the final partitions of two scatters: the sums of a pass-1
+partition's counters by a thread (fewer than 64 of them) or by a wave; and tiles raised to 4096."""
 import numpy as np
 import pytest
 
@@ -16,9 +16,10 @@ import paper_1307_1955_amd.hj as hj  # noqa: E402
 
 DEV = torch.device("cuda:0")
 CASES = [(1 << 20, 2500000, (1, 12)), (1 << 20, 2500000, (7, 6)), (1 << 20, 2500000, (8, 5)), (1 << 21, 5 << 20, (2, 12)),
-         # 13 bits of few tuples: fewer rows, in the words that are free
+         # too few tuples: a second histogram
          (1, 1, (7, 6)), (5000, 300, (7, 6)), (70001, 60001, (1, 12)), (70001, 60001, (12, 1)), (64 * 1024, 64 * 1024 - 1, (6, 7)),
-         (33000, 34000, (7, 6))]
+         # twice the requested tile of 1024 from 2^19 tuples on, 4096 from 2^20, and one scatter of them
+         (1 << 18, (1 << 18) - 1, (3, 4)), (1 << 18, 1 << 18, (3, 4)), (1 << 19, 1 << 19, (3, 4)), (1 << 19, (1 << 19) - 1, (6, 6))]
 
 
 @pytest.mark.parametrize("tile", [0, 1024])

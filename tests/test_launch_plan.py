@@ -121,3 +121,18 @@ def test_histogram_of_few_tuples_clears_with_more_workgroups(exe):
     assert seq[0][0] == "k_part_hist" and int(seq[0][1]["grid"]) >= 64
     seq, _ = launches(exe, "join", 1 << 20, 1 << 20, bits=(6, 6))
     assert int(seq[0][1]["grid"]) == 512
+
+
+# (tile, |R| + |S|, bits, tuples per scatter workgroup): requested tiles are the least, as include/hj.h has it
+TILES = [(1024, (1 << 19) - 2, (6,), 1024), (1024, 1 << 19, (6,), 2048), (1024, 1 << 20, (6,), 4096), (2048, 1 << 22, (6,), 4096),
+         (1024, 1 << 20, (6, 6), 4096), (4096, 1 << 22, (6,), 4096), (8192, 1 << 18, (6,), 8192), (4096, 1 << 21, (10,), 8192),
+         (4096, (1 << 21) - 2, (10,), 4096)]
+
+
+@pytest.mark.parametrize("case", range(len(TILES)))
+def test_scatter_tiles(exe, case):
+    tile, n, bits, want = TILES[case]
+    seq, _ = launches(exe, "join", n // 2, n // 2, bits=bits, tile=tile)
+    f = [f for k, f in seq if k == "k_part_scatter"][0]
+    tiles = 2 * -(-(n // 2) // want)
+    assert tiles <= int(f["grid"]) < tiles + 20  # (and the join plan's workgroups)
