@@ -134,6 +134,16 @@ def join_slots(cap: int) -> int:
     return CUS * max(1, min(LDS_PER_CU // (join_lds_bytes(cap) + 512), by_waves))
 
 
+def direct_blocks(cap: int) -> int:
+    """Workgroups of a direct join that a CU holds, without rids in LDS where that
+    holds more (csrc/phj_join.hip direct_blocks)."""
+    heads = 64
+    while 2 * heads <= cap:
+        heads *= 2
+    by_lds = LDS_PER_CU // (4 * (2 * heads + cap + 128) + 512)
+    return max(1, min(by_lds, (4 if cap > 4608 else 6) * 4 // 8))
+
+
 def _nonempty(mean: float) -> float:
     return 1.0 - math.exp(-mean) if mean < 30 else 1.0
 
@@ -202,7 +212,7 @@ def launches(plan: dict, n_r: int, n_s: int, m: float) -> list[tuple[str, dict]]
         return out
     cap = plan["lds_cap"]
     if plan["passes"] == 0:
-        slots = 256 if cap > 4608 else 640
+        slots = CUS * direct_blocks(cap)
         chunk = JOIN_CHUNK // 2 if n_s <= slots * (JOIN_CHUNK // 2) else JOIN_CHUNK
         items = math.ceil(n_s / chunk)
         if items > 1:

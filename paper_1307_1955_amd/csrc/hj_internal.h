@@ -452,15 +452,11 @@ struct DirectJob {
     uint32_t n_r, n_s, item0, chunk;
 };
 // S tuples per work item of a single direct join: one probe round while every
-// item still runs at once (1 a CU with the largest tables, else 3: up to 640,
-// 4.4K x 3.5M took 27.4 us in 760 of them, 26.7 before), else kJoinChunk.  An item is a chain of
+// item still runs at once (direct_blocks a CU), else kJoinChunk.  An item is a chain of
 // dependent steps and a second round adds a load, a probe and a reservation to
 // it; on idle CUs building R's table again costs nothing (2.2K x 26.7K:
 // 18.3 to 13.7 us, 4K x 2M 23.3 to 19.0).  Batches keep kJoinChunk: their items fill the device.
-inline uint32_t direct_chunk(uint64_t n_s, uint32_t lds_cap) {
-    const uint64_t slots = join_rpt(lds_cap) > kRptMid ? 256 : 640;
-    return n_s <= slots * kJoinSub ? kJoinSub : kJoinChunk;
-}
+uint32_t direct_chunk(uint64_t n_s, uint32_t lds_cap);
 // A single direct join, its job a kernel argument.  One work item zeroes the
 // job's count and the call's error word (rec.err_clear) itself; more need a
 // launch before them (1K x 3K, two launches and one: 13.9 and 11.0 us).

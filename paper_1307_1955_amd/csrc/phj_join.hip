@@ -441,15 +441,29 @@ __device__ __forceinline__ void probe_hbm(const uint64_t* __restrict__ region, c
     }
 }
 
+// Rids of a table's rows: in LDS, or in R's column of n >= 1 rows (direct joins whose
+// LDS would hold fewer workgroups with them).  Rows without a rid are readable too.
+struct LdsRids {
+    const uint32_t* rid;
+    __device__ __forceinline__ int32_t operator()(uint32_t row) const { return (int32_t)rid[row]; }
+};
+struct ColumnRids {
+    const int32_t* __restrict__ rid;
+    uint32_t n;
+    __device__ __forceinline__ int32_t operator()(uint32_t row) const { return rid[min(row, n - 1)]; }
+};
+
 // Writes the matches after the first of an S tuple (m: the record's part of its
 // key, `first` the first match's row) to o_r/o_s[p ...], slots below `room` only.
-__device__ __forceinline__ void write_more(const LdsTable& v, uint32_t m, int32_t rs, uint32_t first, uint32_t p,
-                                           uint32_t room, int32_t* __restrict__ o_r, int32_t* __restrict__ o_s) {
+template <typename Rids>
+__device__ __forceinline__ void write_more(const LdsTable& v, Rids rids, uint32_t m, int32_t rs, uint32_t first,
+                                           uint32_t p, uint32_t room, int32_t* __restrict__ o_r,
+                                           int32_t* __restrict__ o_s) {
     for (uint32_t x = v.rec[first] & v.link_mask; x != v.cap;) {
         const uint32_t r = v.rec[x];
         if ((r ^ m) <= v.link_mask) {
             if (p < room) {
-                o_r[p] = (int32_t)v.rid[x];
+                o_r[p] = rids(x);
                 o_s[p] = rs;
             }
             ++p;
@@ -503,8 +517,8 @@ __device__ __forceinline__ uint32_t lane_pairs_lds(const uint32_t* cf) {
 // by match counts); returns the slot after the wave's last pair.  LDS table.
 // A round of a wave has fewer than 2^32 pairs (kSubJ keys x kMaxLdsCap
 // matches), so slots are 32-bit offsets from the wave's uniform base.
-template <uint32_t kU>
-__device__ __forceinline__ uint64_t write_round_lds(const LdsTable& v, const uint32_t* m, const int32_t* qr,
+template <uint32_t kU, typename Rids>
+__device__ __forceinline__ uint64_t write_round_lds(const LdsTable& v, Rids rids, const uint32_t* m, const int32_t* qr,
                                                     const uint32_t* cf, uint64_t pos0, uint64_t capacity,
                                                     int32_t* __restrict__ out_r, int32_t* __restrict__ out_s) {
     pos0 = uniform64(pos0);
@@ -512,9 +526,9 @@ __device__ __forceinline__ uint64_t write_round_lds(const LdsTable& v, const uin
     const uint32_t room = left > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)left;
     int32_t* __restrict__ o_r = out_r + pos0;
     int32_t* __restrict__ o_s = out_s + pos0;
-    int32_t rid0[kU];  // (row cap + 64 .. hold no rid, but are readable: no branch)
+    int32_t rid0[kU];
 #pragma unroll
-    for (uint32_t u = 0; u < kU; ++u) rid0[u] = (int32_t)v.rid[cf[u] >> 16];
+    for (uint32_t u = 0; u < kU; ++u) rid0[u] = rids(cf[u] >> 16);
     uint32_t done = 0;  // pairs of the wave written so far
 #pragma unroll
     for (uint32_t u = 0; u < kU; ++u) {
@@ -527,7 +541,7 @@ __device__ __forceinline__ uint64_t write_round_lds(const LdsTable& v, const uin
             o_s[p] = qr[u];
         }
         if (wtotal > kWave || __ballot(c > 1))  // uniform: some key has several matches
-            if (c > 1) write_more(v, m[u], qr[u], cf[u] >> 16, p + 1, room, o_r, o_s);
+            if (c > 1) write_more(v, rids, m[u], qr[u], cf[u] >> 16, p + 1, room, o_r, o_s);
         done += wtotal;
     }
     return pos0 + done;
@@ -805,7 +819,7 @@ k_join_write(const ItemRec* __restrict__ item_rec, uint32_t bits, WriteArgs A, O
                     uint32_t m[kU], cf[kU];
                     probe_lds<kU, kHash>(v, q, wb, we, m, cf);
                     const uint64_t pos0 = kOnePass ? block_reserve(lane_pairs_lds<kU>(cf), A.total, wtot, sb != 0) : base;
-                    base = write_round_lds<kU>(v, m, qr, cf, pos0, A.capacity, A.out_r, A.out_s);
+                    base = write_round_lds<kU>(v, LdsRids{v.rid}, m, qr, cf, pos0, A.capacity, A.out_r, A.out_s);
                 }
             };
             if (small_item(L)) run(std::integral_constant<uint32_t, 1>(), std::integral_constant<uint32_t, kFewU>());
@@ -823,8 +837,8 @@ k_join_write(const ItemRec* __restrict__ item_rec, uint32_t bits, WriteArgs A, O
 // the job's R and writes the chunk's pairs to the job's output with one-pass
 // reservation.
 // kOne: the only job is `one`; a grid of one workgroup clears its count and
-// err_clear.
-template <uint32_t RPT, bool kOne>
+// err_clear.  kRids: rids in LDS (direct_rids_in_lds).
+template <uint32_t RPT, bool kOne, bool kRids>
 __global__ void __launch_bounds__(kJoinBlock) __attribute__((amdgpu_waves_per_eu(RPT > kRptMid ? 4 : 6)))
 k_direct_join(const DirectJob* __restrict__ jobs, const uint32_t* __restrict__ item_job, DirectJob one,
               uint64_t* err_clear, uint32_t lds_cap) {
@@ -847,14 +861,15 @@ k_direct_join(const DirectJob* __restrict__ jobs, const uint32_t* __restrict__ i
     int32_t q[kSU], qr[kSU];
     load_s<kSU>(skp, srp, w * kSubJ, s_n, q, qr);
     const LdsTable v = lds_table(lds, lds_cap, 0u);
-    build_lds<RPT, 0, true>(k, rid, r_len, v);
+    build_lds<RPT, 0, kRids>(k, rid, r_len, v);
     for (uint32_t sb = 0; sb < s_n; sb += kJoinSub) {
         const uint32_t wb = sb + w * kSubJ, we = min(wb + kSubJ, s_n);
         if (sb) load_s<kSU>(skp, srp, wb, s_n, q, qr);
         uint32_t m[kSU], cf[kSU];
         probe_lds<kSU, 0>(v, q, wb, we, m, cf);
         const uint64_t pos0 = block_reserve(lane_pairs_lds<kSU>(cf), (unsigned long long*)J.count, wtot, sb != 0);
-        write_round_lds<kSU>(v, m, qr, cf, pos0, J.capacity, J.out_r, J.out_s);
+        if (kRids) write_round_lds<kSU>(v, LdsRids{v.rid}, m, qr, cf, pos0, J.capacity, J.out_r, J.out_s);
+        else write_round_lds<kSU>(v, ColumnRids{J.rr, r_len}, m, qr, cf, pos0, J.capacity, J.out_r, J.out_s);
     }
 }
 
@@ -890,25 +905,61 @@ static void allow_lds(const void* fn, size_t lds) {
     if (lds > 65536) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
-template <uint32_t RPT, bool kOne>
+namespace {
+
+// Workgroups of a direct join that a CU holds: by LDS, and by the waves the
+// register budget allows.
+uint32_t direct_blocks(uint32_t lds_cap, bool rids) {
+    const uint32_t by_lds = (uint32_t)(160u * 1024u / (join_lds_bytes(lds_cap, 0, rids) + 512u));
+    const uint32_t by_waves = (join_rpt(lds_cap) > kRptMid ? 4u : 6u) * 4u / kJoinWaves;
+    return std::max(1u, std::min(by_lds, by_waves));
+}
+
+// Rids in LDS unless the device holds more of the items at once without them, whose
+// matches then read R's column: with the two buckets per row that a direct table
+// needs (its links have no partition's bits to use), rids leave a CU one workgroup
+// instead of two from 6016 rows on, two instead of three at 4096 to 4608.  6500 x
+// 16M: 123 us with rids in LDS, 87.5 without; 4608 x 2M (455 items) 18.0 and 18.7.
+bool direct_rids_in_lds(uint32_t lds_cap, uint32_t nitems) {
+    if (nitems <= 256) return true;
+    const uint32_t with = direct_blocks(lds_cap, true);
+    return nitems <= 256 * with || with == direct_blocks(lds_cap, false);
+}
+
+template <uint32_t RPT, bool kOne, bool kRids>
 void direct_join_t(const DirectJob* jobs, const uint32_t* item_job, const DirectJob& one, uint32_t nitems,
                    uint32_t lds_cap, Recorder& rec) {
-    const size_t lds = join_lds_bytes(lds_cap, 0, true);
-    allow_lds((const void*)k_direct_join<RPT, kOne>, lds);
+    const size_t lds = join_lds_bytes(lds_cap, 0, kRids);
+    allow_lds((const void*)k_direct_join<RPT, kOne, kRids>, lds);
     rec.before("direct_join");
-    hipLaunchKernelGGL((k_direct_join<RPT, kOne>), dim3(nitems), dim3(kJoinBlock), lds, rec.stream, jobs, item_job, one,
-                       rec.err_clear, lds_cap);
+    hipLaunchKernelGGL((k_direct_join<RPT, kOne, kRids>), dim3(nitems), dim3(kJoinBlock), lds, rec.stream, jobs, item_job,
+                       one, rec.err_clear, lds_cap);
     rec.after();
 }
 
 template <bool kOne>
 void direct_join_rpt(const DirectJob* jobs, const uint32_t* item_job, const DirectJob& one, uint32_t nitems,
                      uint32_t lds_cap, Recorder& rec) {
+    const bool rids = direct_rids_in_lds(lds_cap, nitems);
     switch (join_rpt(lds_cap)) {
-        case kRptSmall: direct_join_t<kRptSmall, kOne>(jobs, item_job, one, nitems, lds_cap, rec); break;
-        case kRptMid: direct_join_t<kRptMid, kOne>(jobs, item_job, one, nitems, lds_cap, rec); break;
-        default: direct_join_t<kRptLarge, kOne>(jobs, item_job, one, nitems, lds_cap, rec); break;
+        case kRptSmall: direct_join_t<kRptSmall, kOne, true>(jobs, item_job, one, nitems, lds_cap, rec); break;
+        case kRptMid:
+            if (rids) direct_join_t<kRptMid, kOne, true>(jobs, item_job, one, nitems, lds_cap, rec);
+            else direct_join_t<kRptMid, kOne, false>(jobs, item_job, one, nitems, lds_cap, rec);
+            break;
+        default:
+            if (rids) direct_join_t<kRptLarge, kOne, true>(jobs, item_job, one, nitems, lds_cap, rec);
+            else direct_join_t<kRptLarge, kOne, false>(jobs, item_job, one, nitems, lds_cap, rec);
+            break;
     }
+}
+
+}  // namespace
+
+uint32_t direct_chunk(uint64_t n_s, uint32_t lds_cap) {
+    if (n_s <= 256ull * kJoinSub) return kJoinSub;
+    const uint64_t slots = 256ull * std::max(direct_blocks(lds_cap, true), direct_blocks(lds_cap, false));
+    return n_s <= slots * kJoinSub ? kJoinSub : kJoinChunk;
 }
 
 void direct_join(const DirectJob* jobs, const uint32_t* item_job, uint32_t nitems, uint32_t lds_cap,
