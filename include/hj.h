@@ -59,7 +59,7 @@ typedef enum hj_status {
 /* HJ_AUTO: the library evaluates its cost model (hj_model_seconds) for SHJ, for
    PHJ without partitioning (|R| <= 8192), and for PHJ in one or two radix
    passes around 4096 R tuples per partition (at p->tile, or the tile chosen from
-   the sizes), and runs the plan with the least modelled time;
+   the sizes; up to 2^20 R tuples only with partitions that fit lds_cap), and runs the plan with the least modelled time;
    hash, lds_cap and flags are kept.  hj_resolve_params shows the choice. */
 typedef enum hj_algo { HJ_SHJ = 0, HJ_PHJ = 1, HJ_AUTO = 2 } hj_algo;
 

@@ -212,7 +212,13 @@ double model_seconds(const Plan& pl, uint64_t n_r_, uint64_t n_s_, double m) {
 // loses by shorter runs (pass 1 reads the inputs cold; 16M x 16M ran 9% slower
 // with 4096-tuple tiles, which the model priced faster).  Hash, lds_cap and
 // flags are the caller's.  The output size is taken as |S|
-// (one match per probe tuple), the same for every candidate.
+// (one match per probe tuple), the same for every candidate.  Partitions that
+// all need HBM tables (a small lds_cap) are weighed only past kOneTableRows:
+// below, one table over all of R is cached as well and needs no partitioning
+// (measured with lds_cap 256: 8.8K x 15M 195 us against 266 and more, 300K x 4.8M
+// 134 against 161, 1M x 4M 160 against 181; past 1M rows either wins), which the model's per-access
+// constants do not see.
+constexpr uint64_t kOneTableRows = 1ull << 20;
 void auto_params(uint64_t n_r, uint64_t n_s, hj_params* p) {
     const hj_params base = *p;
     const double m = (double)n_s;
@@ -226,6 +232,7 @@ void auto_params(uint64_t n_r, uint64_t n_s, hj_params* p) {
         Plan pl;
         const hj_status st = check_params(&q, n_r, n_s, &pl);
         if (st != HJ_OK) return;
+        if (pl.phj && pl.passes && n_r <= kOneTableRows && (n_r >> pl.B) > pl.lds_cap) return;
         const double t = model_seconds(pl, n_r, n_s, m);
         if (t < best_t) {
             best_t = t;

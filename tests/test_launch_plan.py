@@ -136,3 +136,11 @@ def test_scatter_tiles(exe, case):
     f = [f for k, f in seq if k == "k_part_scatter"][0]
     tiles = 2 * -(-(n // 2) // want)
     assert tiles <= int(f["grid"]) < tiles + 20  # (and the join plan's workgroups)
+
+
+@pytest.mark.parametrize("n_r,n_s", [(8800, 15590469), (13212, 15941266), (300000, 4800000)])
+def test_auto_keeps_one_table_for_a_small_lds_cap(exe, n_r, n_s):
+    """Partitions that would all need HBM tables are not worth a partitioning of a small R."""
+    for one_pass in (True, False):
+        seq, _ = launches(exe, "join", n_r, n_s, algo=AUTO, lds_cap=256, one_pass=one_pass)
+        assert "k_shj_build" in [k for k, _ in seq]
