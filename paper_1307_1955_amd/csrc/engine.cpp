@@ -67,8 +67,11 @@ struct Carver {
 
 // LDS per CU on gfx950, and what a join workgroup is planned with: 12 bytes per
 // tuple and 1.5 KB (static LDS plus allocation rounding; measured: a 54,080-byte
-// table set no longer fits three workgroups per CU, 53,312 bytes does).  The
-// tables themselves (join_lds_bytes) take at most that.
+// table set no longer fits three workgroups per CU, 53,312 bytes does).  Tables
+// with one bucket per row (join_lds_bytes) take at most that; with two, which
+// they have where three workgroups still share a CU, up to a third of a CU's LDS
+// each: three workgroups are as many as the write kernels' registers allow, so
+// the capacities that the plan tells apart by more than three share the figure.
 constexpr size_t kLdsPerCu = 160 * 1024;
 
 uint32_t join_blocks_per_cu(uint32_t cap) { return (uint32_t)(kLdsPerCu / (12ull * cap + 1536)); }

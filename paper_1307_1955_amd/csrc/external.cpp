@@ -40,7 +40,7 @@ namespace {
 
 using Clock = std::chrono::steady_clock;
 
-constexpr uint32_t kExtTile = 8192;           // partitioning tile of the chunks
+constexpr uint32_t kExtTile = hj::kColumnsTile;  // partitioning tile of the chunks
 constexpr uint64_t kMaxChunk = 1ull << 28;    // tuples per chunk (and per device slot)
 constexpr uint32_t kMaxFanoutBits = 13;       // one radix pass
 constexpr size_t kMinExternalWs = 64ull << 20;

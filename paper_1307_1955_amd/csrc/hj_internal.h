@@ -226,8 +226,9 @@ inline uint32_t scatter_tile(uint32_t tile, uint32_t bits, uint64_t n) {
 // Threads of a partitioning workgroup that takes `tile` tuples.
 inline uint32_t scatter_block(uint32_t tile) { return tile >= 8192 ? 1024u : tile >= 4096 ? 512u : kMinPartBlock; }
 // Replicas of a pass-1 partition's cursor: one for each of the 8 XCDs (tile t
-// reserves in replica t mod 8, and workgroups go to the XCDs round-robin), so that the tuples that one XCD writes to a partition
-// are contiguous and lines are written by one L2.  Measured on MI355X, 2^25
+// reserves in replica t mod 8, and workgroups go to the XCDs round-robin), so that
+// the tuples that one XCD writes to a partition are contiguous and lines are
+// written by one L2.  Measured on MI355X, 2^25
 // tuples, 8192-tuple tiles: 92 against 113 us at 2^6 partitions with one
 // cursor for all, 105 against 146 us at 2^10.  Small joins keep one.
 inline uint32_t cursor_replicas(uint64_t tiles) { return tiles >= 64 ? 8u : 1u; }
@@ -336,7 +337,8 @@ inline uint32_t clear_share(uint64_t n_r) { return (uint32_t)(n_r < 4096ull * 25
 // (hj_side.h: the pass-2 segment table or the join plan).
 struct SideJob;
 // First pass: the input's tuples to `out`, or to two columns (key_out, rid_out)
-// when out is nullptr.
+// when out is nullptr (tiles of kColumnsTile, MurmurHash 2.0).
+constexpr uint32_t kColumnsTile = 8192;
 // cur1: the starts launch's cursors (self_starts: unused).
 void part_scatter(const Pass1& p1, const PassCfg& cfg, uint32_t* cur1, Tuple* out, int32_t* key_out,
                   int32_t* rid_out, const ClearTables& clr, const SideJob& side, Recorder& rec);

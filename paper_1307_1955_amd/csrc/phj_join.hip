@@ -619,11 +619,10 @@ __device__ __forceinline__ bool small_item(const ItemLoc& L) {
 }
 
 template <uint32_t RPT, bool kNt, uint32_t kHash>
-__global__ void __launch_bounds__(kJoinBlock) __attribute__((amdgpu_waves_per_eu(6))) k_join_count(const ItemRec* __restrict__ item_rec,
-                                                          const Tuple* __restrict__ rt,
-                                                          const Tuple* __restrict__ st, uint32_t lds_cap,
-                                                          uint32_t bits, uint64_t* ovf_table, uint32_t* ovf_next,
-                                                          HotKeys* hot, uint64_t* __restrict__ wave_cnt, OvfBuild B) {
+__global__ void __launch_bounds__(kJoinBlock) __attribute__((amdgpu_waves_per_eu(6)))
+k_join_count(const ItemRec* __restrict__ item_rec, const Tuple* __restrict__ rt, const Tuple* __restrict__ st,
+             uint32_t lds_cap, uint32_t bits, uint64_t* ovf_table, uint32_t* ovf_next, HotKeys* hot,
+             uint64_t* __restrict__ wave_cnt, OvfBuild B) {
     extern __shared__ uint32_t lds[];
     const uint32_t w = threadIdx.x / kWave;
     const uint32_t lane = lane_id();

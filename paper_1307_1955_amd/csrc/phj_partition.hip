@@ -372,14 +372,12 @@ __device__ __forceinline__ void sum_rows(const uint32_t* __restrict__ rows, uint
 // Registers: at most 64 up to 8 tuples per thread, so that LDS alone limits
 // the workgroups of a CU (two of 8192 tuples).
 template <uint32_t BLOCK, uint32_t IPT, bool kSeg, bool kNt, bool kCols, bool kSelf, uint32_t kHash>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(IPT <= 8 ? 8 : 4))) k_part_scatter(Pass1 A, const Tuple* __restrict__ in,
-                                                        const PartSeg* __restrict__ segs,
-                                                        const uint32_t* __restrict__ tile_begin,
-                                                        const uint32_t* __restrict__ tile_seg, uint32_t nseg,
-                                                        PassCfg cfg, const uint32_t* __restrict__ start2,
-                                                        uint32_t* __restrict__ cur1, Tuple* __restrict__ out,
-                                                        int32_t* __restrict__ key_out, int32_t* __restrict__ rid_out,
-                                                        ClearTables clr, SideJob side, uint32_t lds_words) {
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(IPT <= 8 ? 8 : 4)))
+k_part_scatter(Pass1 A, const Tuple* __restrict__ in, const PartSeg* __restrict__ segs,
+               const uint32_t* __restrict__ tile_begin, const uint32_t* __restrict__ tile_seg, uint32_t nseg, PassCfg cfg,
+               const uint32_t* __restrict__ start2, uint32_t* __restrict__ cur1, Tuple* __restrict__ out,
+               int32_t* __restrict__ key_out, int32_t* __restrict__ rid_out, ClearTables clr, SideJob side,
+               uint32_t lds_words) {
     extern __shared__ uint64_t lds64[];
     uint32_t* lds = reinterpret_cast<uint32_t*>(lds64);
     if (blockIdx.x >= gridDim.x - side.blocks) {  // extra workgroups: the side job
@@ -671,25 +669,37 @@ void launch_scatter(const ScatterArgs& a, const PassCfg& cfg, const ClearTables&
     rec.after();
 }
 
-template <bool kSeg, bool kNt, bool kCols, bool kSelf, uint32_t kHash>
+template <bool kSeg, bool kNt, bool kSelf, uint32_t kHash>
 void scatter_tiles(const ScatterArgs& a, const PassCfg& cfg, const ClearTables& clr, const SideJob& side,
                    Recorder& rec) {
     switch (cfg.tile) {  // workgroup size by tile: scatter_block()
-        case 1024: launch_scatter<256, 4, kSeg, kNt, kCols, kSelf, kHash>(a, cfg, clr, side, rec); break;
-        case 2048: launch_scatter<256, 8, kSeg, kNt, kCols, kSelf, kHash>(a, cfg, clr, side, rec); break;
-        case 4096: launch_scatter<512, 8, kSeg, kNt, kCols, kSelf, kHash>(a, cfg, clr, side, rec); break;
-        case 8192: launch_scatter<1024, 8, kSeg, kNt, kCols, kSelf, kHash>(a, cfg, clr, side, rec); break;
+        case 1024: launch_scatter<256, 4, kSeg, kNt, false, kSelf, kHash>(a, cfg, clr, side, rec); break;
+        case 2048: launch_scatter<256, 8, kSeg, kNt, false, kSelf, kHash>(a, cfg, clr, side, rec); break;
+        case 4096: launch_scatter<512, 8, kSeg, kNt, false, kSelf, kHash>(a, cfg, clr, side, rec); break;
+        case 8192: launch_scatter<1024, 8, kSeg, kNt, false, kSelf, kHash>(a, cfg, clr, side, rec); break;
         default:  // (self_starts joins have no tiles of more than 8192 tuples)
-            if constexpr (!kSelf) launch_scatter<1024, 16, kSeg, kNt, kCols, kSelf, kHash>(a, cfg, clr, side, rec);
+            if constexpr (!kSelf) launch_scatter<1024, 16, kSeg, kNt, false, kSelf, kHash>(a, cfg, clr, side, rec);
             break;
     }
 }
 
-template <bool kSeg, bool kNt, bool kCols, bool kSelf = false>
+template <bool kSeg, bool kNt, bool kSelf = false>
 void scatter_hash(const ScatterArgs& a, const PassCfg& cfg, const ClearTables& clr, const SideJob& side,
                   Recorder& rec) {
-    if (cfg.hash_kind) scatter_tiles<kSeg, kNt, kCols, kSelf, 1>(a, cfg, clr, side, rec);
-    else scatter_tiles<kSeg, kNt, kCols, kSelf, 0>(a, cfg, clr, side, rec);
+    if (cfg.hash_kind) scatter_tiles<kSeg, kNt, kSelf, 1>(a, cfg, clr, side, rec);
+    else scatter_tiles<kSeg, kNt, kSelf, 0>(a, cfg, clr, side, rec);
+}
+
+// Two columns out: one tile and MurmurHash 2.0 only (the out-of-core partition pass).
+template <bool kNt>
+void scatter_columns(const ScatterArgs& a, const PassCfg& cfg, const ClearTables& clr, const SideJob& side,
+                     Recorder& rec) {
+    if (cfg.tile != kColumnsTile || !cfg.hash_kind) {
+        if (rec.err == hipSuccess) rec.err = hipErrorInvalidConfiguration;
+        return;
+    }
+    static_assert(kColumnsTile == 1024 * 8, "tile of the column kernels");
+    launch_scatter<1024, 8, false, kNt, true, false, 1>(a, cfg, clr, side, rec);
 }
 
 // (grid > 0 or side workgroups, and a tile the kernels are built for)
@@ -756,11 +766,16 @@ void part_scatter(const Pass1& p1, const PassCfg& cfg, uint32_t* cur1, Tuple* ou
                   int32_t* rid_out, const ClearTables& clr, const SideJob& side, Recorder& rec) {
     const ScatterArgs a{p1, nullptr, nullptr, nullptr, nullptr, 0, p1.ntiles, nullptr, cur1, out, key_out, rid_out};
     if (!scatter_ok(a, cfg, side, rec)) return;
-    if (out && p1.self) scatter_hash<false, false, false, true>(a, cfg, clr, side, rec);
-    else if (out && cfg.nt) scatter_hash<false, true, false>(a, cfg, clr, side, rec);
-    else if (out) scatter_hash<false, false, false>(a, cfg, clr, side, rec);
-    else if (cfg.nt) scatter_hash<false, true, true>(a, cfg, clr, side, rec);
-    else scatter_hash<false, false, true>(a, cfg, clr, side, rec);
+    if (!out) {
+        if (cfg.nt) scatter_columns<true>(a, cfg, clr, side, rec);
+        else scatter_columns<false>(a, cfg, clr, side, rec);
+    } else if (p1.self) {
+        scatter_hash<false, false, true>(a, cfg, clr, side, rec);
+    } else if (cfg.nt) {
+        scatter_hash<false, true>(a, cfg, clr, side, rec);
+    } else {
+        scatter_hash<false, false>(a, cfg, clr, side, rec);
+    }
 }
 
 void part_scatter2(const Tuple* in, const PartSeg* segs, const uint32_t* tile_begin, const uint32_t* tile_seg,
@@ -768,8 +783,8 @@ void part_scatter2(const Tuple* in, const PartSeg* segs, const uint32_t* tile_be
                    Tuple* out, const ClearTables& clr, const SideJob& side, Recorder& rec) {
     const ScatterArgs a{Pass1{}, in, segs, tile_begin, tile_seg, nseg, grid, start2, cnt2, out, nullptr, nullptr};
     if (!scatter_ok(a, cfg, side, rec)) return;
-    if (cfg.nt) scatter_hash<true, true, false>(a, cfg, clr, side, rec);
-    else scatter_hash<true, false, false>(a, cfg, clr, side, rec);
+    if (cfg.nt) scatter_hash<true, true>(a, cfg, clr, side, rec);
+    else scatter_hash<true, false>(a, cfg, clr, side, rec);
 }
 
 }  // namespace hj

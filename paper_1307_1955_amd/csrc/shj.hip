@@ -2,8 +2,8 @@
 //
 // The paper's table -- bucket headers, a key list per bucket, a rid list per
 // key (Section 3.1) -- needs dynamic allocation inside the kernel (Section
-// 3.3).  Here it is an array of 2^L 64-bit slots, L = ceil(log2(2 |R|)), plus
-// one uint32 `next` per R row:
+// 3.3).  Here it is an array of 2 |R| 64-bit slots (rounded up to whole 128-byte
+// lines), plus one uint32 `next` per R row:
 //   * a slot is one distinct key and the head of its row chain (the key node
 //     and its rid list); linear probing over slots plays the bucket's key list;
 //   * next[row] links the rows of a duplicated key (the rid list), so
