@@ -418,9 +418,10 @@ k_part_scatter(Pass1 A, const Tuple* __restrict__ in, const PartSeg* __restrict_
     const uint32_t G = gridDim.x - side.blocks;
     uint32_t tile = kSeg ? live_remap(blockIdx.x, ntiles)  // an XCD's tiles are contiguous: it writes whole segments
                          : blockIdx.x;
+    constexpr bool kMore = IPT <= 8;  // (tiles of 16384 tuples: one per CU at least, as many as clear_share)
     // share c of the HBM tables' clearing (rare; uniform)
     auto clear = [&](uint32_t c) {
-        const uint32_t n = max(ntiles, clr.share);
+        const uint32_t n = kMore ? max(ntiles, clr.share) : ntiles;
         if (kSelf && !clr.r_pairs) {  // R's tiles know R's partitions, and share the clearing among them
             clear_tables(clr, c, A.nt_r, [&](uint32_t i) { return i < P ? tot[i] : clr.n_r; }, [](uint32_t) { return true; });
             return;
@@ -430,7 +431,7 @@ k_part_scatter(Pass1 A, const Tuple* __restrict__ in, const PartSeg* __restrict_
         else clear_tables(clr, c, n, begin, [&](uint32_t i) { return clr.start[clr.npart + i + 1] != clr.start[clr.npart + i]; });
     };
     if (tile >= ntiles) {  // a workgroup that only clears
-        if (!clr.table || tile >= clr.share) return;
+        if (!kMore || !clr.table || tile >= clr.share) return;
         if (!kSelf) {
             if (*clr.big != 0) clear(tile);
             return;
@@ -661,7 +662,7 @@ void launch_scatter(const ScatterArgs& a, const PassCfg& cfg, const ClearTables&
     allow_lds(k_part_scatter<BLOCK, IPT, kSeg, kNt, kCols, kSelf, kHash>, lds);
     // one workgroup per CU for tiles of more than 8 tuples per thread (kLoop)
     uint32_t grid = !kSeg && IPT > 8 && a.grid > kScatterLoopGrid ? kScatterLoopGrid : a.grid;
-    if (clr.table && grid < clr.share) grid = clr.share;
+    if (IPT <= 8 && clr.table && grid < clr.share) grid = clr.share;
     rec.before("part_scatter");
     hipLaunchKernelGGL((k_part_scatter<BLOCK, IPT, kSeg, kNt, kCols, kSelf, kHash>), dim3(grid + side.blocks), dim3(BLOCK), lds,
                        rec.stream, a.p1, a.in, a.segs, a.tile_begin, a.tile_seg, a.nseg, cfg, a.start2, a.cur, a.out,
