@@ -47,10 +47,11 @@ __device__ __forceinline__ uint32_t uniform(uint32_t x) { return uniform_word(x)
 // Build items of the HBM tables, or 0 when a chained scan of the call gave up
 // (which the call reports): partitions made from wrong starts may share table
 // slots, and a look-up in a table without an empty slot would not end.
+// (Both words are read at once: one after the other, every workgroup of a join with
+// tables waited for both.)
 __device__ __forceinline__ uint32_t table_items(const OvfBuild& B) {
     const uint32_t n = *B.total;
-    if (n == 0) return 0;
-    return uniform((uint32_t)(status_load(B.err) & kErrLookback)) ? 0u : n;
+    return *B.err & kErrLookback ? 0u : n;
 }
 
 __global__ void __launch_bounds__(256) k_ovf_clear(OvfBuild B, uint64_t* __restrict__ ovf_table) {

@@ -117,18 +117,19 @@ __device__ __forceinline__ bool slot_in(uint32_t s, uint32_t len) {
     return s < IPT ? threadIdx.x + s / 4 * BLOCK < len / 4 : threadIdx.x < len % 4;
 }
 
-// kFine counters: those of the final partitions (bits + fine_bits bits), which
+// kFine: counters of the final partitions (bits + fine_bits bits), which
 // go to `rows` and, summed per pass-1 partition, to rows1.  What bounds it: the
 // key read (2^25 tuples at 2^12 counters: 29 us, 4.6 TB/s).  Persistent
 // workgroups write one row for all their tiles: a row per tile would be 64 MB
 // there, and counters in memory added to with atomics cost 26 us per 8M of them.
-template <uint32_t BLOCK, uint32_t IPT, bool kNt, uint32_t kHash>
+template <uint32_t BLOCK, uint32_t IPT, bool kNt, uint32_t kHash, bool kFine>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) k_part_hist(Pass1 A, PassCfg cfg) {
     extern __shared__ uint32_t cnt[];  // [P], then [64] for slots without an element
     constexpr uint32_t T = BLOCK * IPT;
     const uint32_t P1 = 1u << cfg.bits;
-    const uint32_t P = P1 << A.fine_bits;
-    const uint32_t shift = cfg.shift - A.fine_bits;  // pass 1 takes the bits above the fine ones
+    const uint32_t fine = kFine ? A.fine_bits : 0u, bits = cfg.bits + fine;
+    const uint32_t P = P1 << fine;
+    const uint32_t shift = cfg.shift - fine;  // pass 1 takes the bits above the fine ones
     const uint64_t lt = lanemask_lt();
     // the words later launches expect to be zero
     for (uint64_t i = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; i < A.nzero; i += (uint64_t)gridDim.x * BLOCK)
@@ -153,12 +154,12 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8)))
             const uint32_t off = (x + j * nx - t0) * T, len = min(T, n - off);
             int32_t keys[IPT + 1];
             load_tile<BLOCK, IPT, kNt>(col + off, len, A.rows, keys, keys[IPT]);
-            if (cfg.bits + A.fine_bits <= kBallotMaxBits) {  // uniform
+            if (bits <= kBallotMaxBits) {  // uniform
 #pragma unroll
                 for (uint32_t k = 0; k <= IPT; ++k) {
                     const bool ok = slot_in<BLOCK, IPT>(k, len);
                     const uint32_t p = part_of<kHash>(keys[k], shift, P);
-                    const uint64_t m = match_mask(p, cfg.bits + A.fine_bits, ok);
+                    const uint64_t m = match_mask(p, bits, ok);
                     if (ok && (m & lt) == 0) atomicAdd(&cnt[p], (uint32_t)__popcll(m));
                 }
             } else {
@@ -168,20 +169,20 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8)))
             }
         }
         __syncthreads();
-        if (A.fine_bits) {
+        if (kFine) {
             uint32_t* __restrict__ r1 = A.rows1 + (uint64_t)row * P1;
-            const uint32_t F = 1u << A.fine_bits;
+            const uint32_t F = 1u << fine;
             if (F >= kWave) {  // a wave per partition (a thread each took 360 us at 2 partitions of 8192 counters)
                 for (uint32_t i = threadIdx.x / kWave; i < P1; i += BLOCK / kWave) {
                     uint32_t v = 0;
-                    for (uint32_t j = lane_id(); j < F; j += kWave) v += cnt[(i << A.fine_bits) | j];
+                    for (uint32_t j = lane_id(); j < F; j += kWave) v += cnt[(i << fine) | j];
                     v = wave_sum(v);
                     if (lane_id() == 0) r1[i] = v;
                 }
             } else {
                 for (uint32_t i = threadIdx.x; i < P1; i += BLOCK) {
                     uint32_t v = 0;
-                    for (uint32_t j = 0; j < F; ++j) v += cnt[(i << A.fine_bits) | ((j + i) & (F - 1))];  // (apart in banks)
+                    for (uint32_t j = 0; j < F; ++j) v += cnt[(i << fine) | ((j + i) & (F - 1))];  // (apart in banks)
                     r1[i] = v;
                 }
             }
@@ -426,9 +427,18 @@ k_part_scatter(Pass1 A, const Tuple* __restrict__ in, const PartSeg* __restrict_
             clear_tables(clr, c, A.nt_r, [&](uint32_t i) { return i < P ? tot[i] : clr.n_r; }, [](uint32_t) { return true; });
             return;
         }
-        auto begin = [&](uint32_t i) { return i >= clr.npart ? clr.n_r : clr.r_pairs ? clr.r_pairs[i].r_off : clr.start[i]; };
-        if (kSelf) clear_tables(clr, c, n, begin, [&](uint32_t i) { return (i + 1 < P ? tot[i + 1] : A.n_s) != tot[i]; });
-        else clear_tables(clr, c, n, begin, [&](uint32_t i) { return clr.start[clr.npart + i + 1] != clr.start[clr.npart + i]; });
+        if constexpr (!kMore) {  // (one copy of the code: three would cost the kernel registers)
+            clear_tables(clr, c, n,
+                         [&](uint32_t i) { return i >= clr.npart ? clr.n_r : clr.r_pairs ? clr.r_pairs[i].r_off : clr.start[i]; },
+                         [&](uint32_t i) { return clr.start[clr.npart + i + 1] != clr.start[clr.npart + i]; });
+            return;
+        }
+        auto cleared = [&](auto begin) {
+            if (kSelf) clear_tables(clr, c, n, begin, [&](uint32_t i) { return (i + 1 < P ? tot[i + 1] : A.n_s) != tot[i]; });
+            else clear_tables(clr, c, n, begin, [&](uint32_t i) { return clr.start[clr.npart + i + 1] != clr.start[clr.npart + i]; });
+        };
+        if (clr.r_pairs) cleared([&](uint32_t i) { return i < clr.npart ? clr.r_pairs[i].r_off : clr.n_r; });
+        else cleared([&](uint32_t i) { return i < clr.npart ? clr.start[i] : clr.n_r; });
     };
     if (tile >= ntiles) {  // a workgroup that only clears
         if (!kMore || !clr.table || tile >= clr.share) return;
@@ -607,7 +617,8 @@ void launch_hist(const Pass1& p1, const PassCfg& cfg, Recorder& rec) {
     const size_t lds = sizeof(uint32_t) * (((size_t)1 << (cfg.bits + p1.fine_bits)) + kWave);
     // (workgroups past the tiles' clear words only: 4096 rows in 2^18 partitions, one tile, 2 MB to clear)
     const uint32_t grid = std::max(p1.self ? p1.ntiles : p1.h.grid(), (uint32_t)std::min<uint64_t>(256, p1.nzero / 4096));
-    const auto fn = cfg.nt ? k_part_hist<BLOCK, IPT, true, kHash> : k_part_hist<BLOCK, IPT, false, kHash>;
+    const auto fn = p1.fine_bits ? (cfg.nt ? k_part_hist<BLOCK, IPT, true, kHash, true> : k_part_hist<BLOCK, IPT, false, kHash, true>)
+                                 : (cfg.nt ? k_part_hist<BLOCK, IPT, true, kHash, false> : k_part_hist<BLOCK, IPT, false, kHash, false>);
     allow_lds(fn, lds);
     rec.before("part_hist");
     hipLaunchKernelGGL(fn, dim3(grid), dim3(BLOCK), lds, rec.stream, p1, cfg);
