@@ -59,8 +59,9 @@ typedef enum hj_status {
 /* HJ_AUTO: the library evaluates its cost model (hj_model_seconds) for SHJ, for
    PHJ without partitioning (|R| <= 8192), and for PHJ in one or two radix
    passes around 4096 R tuples per partition (at p->tile, or the tile chosen from
-   the sizes; up to 2^20 R tuples only with partitions that fit lds_cap), and runs the plan with the least modelled time;
-   hash, lds_cap and flags are kept.  hj_resolve_params shows the choice. */
+   the sizes; up to 2^20 R tuples only with partitions that fit lds_cap), and
+   runs the plan with the least modelled time; hash, lds_cap and flags are kept.
+   hj_resolve_params shows the choice. */
 typedef enum hj_algo { HJ_SHJ = 0, HJ_PHJ = 1, HJ_AUTO = 2 } hj_algo;
 
 /* Hash applied to a key before its radix bits are taken (Section 3.1 partitions
@@ -185,7 +186,7 @@ hj_status hj_join_timed(const hj_params* p, const hj_rel* R, const hj_rel* S, co
    the first call on that GPU until the process ends.  Arguments, result and
    asynchrony as hj_join; nothing is allocated.  Returns HJ_ERR_WORKSPACE,
    before touching the device, when hj_workspace_bytes(p, R->n, S->n) exceeds
-   the array (e.g. HJ_AUTO up to about |R| = |S| = 1.7M tuples, SHJ up to about
+   the array (e.g. HJ_AUTO up to about |R| = |S| = 1.9M tuples, SHJ up to about
    3M + 3M).  All calls on one GPU share its array: calls that overlap on one
    GPU (two streams, two threads) race; serialise them.  The call's device
    error word (hj_workspace_status) sits in the array and is not reachable by

@@ -366,8 +366,8 @@ __device__ __forceinline__ void sum_rows(const uint32_t* __restrict__ rows, uint
 // 2), else of the input's columns.  kCols: two columns out instead of tuples.
 // What bounds it: HBM traffic at few partitions (128M x 256M, 2^7 partitions:
 // 1.22 ms, 5.3 TB/s of its 16 bytes per tuple), at 2^12 the lines that leave the
-// L2 before a partition's next run fills them (16M x 16M: 442 MB written for 268,
-// 285 read, 4.7 TB/s in 156 us with 16384-tuple tiles, where two
+// L2 before a partition's next run fills them (16M x 16M: 425-442 MB written for
+// 268, 283 read, 4.6 TB/s in 155 us with 16384-tuple tiles, where two
 // scatters of 2^6 took 107 us each before the tuples were one word, the cursors
 // per XCD and the tile's loads and LDS accesses free of branches).  kSelf: partition starts from the rows (self_starts).
 // Registers: at most 64 up to 8 tuples per thread, so that LDS alone limits
