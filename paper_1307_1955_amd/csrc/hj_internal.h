@@ -180,8 +180,8 @@ struct PassCfg {
 // loads gained nothing and stay plain).
 constexpr uint64_t kNtMinTuples = 1ull << 24;
 constexpr uint64_t kNtMinBuild = 1ull << 23;
-// Two passes of 4..kCountedMaxBits radix bits in all: plans whose final partitions
-// one histogram can count in any case of size (counts_final says when it does).
+// Two passes of 4..kCountedMaxBits radix bits in all.  (A statement about plans
+// only, kept for those who ask it: which histogram counts what is counts_final.)
 constexpr uint32_t kCountedMaxBits = 13;
 inline bool counted_pass2(uint32_t passes, uint32_t b1, uint32_t b2) {
     return passes == 2 && b1 + b2 >= 4 && b1 + b2 <= kCountedMaxBits;

@@ -192,8 +192,12 @@ static_assert(kRptLarge * kJoinBlock == kMaxLdsCap, "largest build covers kMaxLd
 
 // Strided columns of the heavy-key scans (hj_heavy.h) over partitioned tuples.
 typedef Column<2> TupleColumn;
-__device__ __forceinline__ TupleColumn key_column(const Tuple* t) { return TupleColumn{reinterpret_cast<const int32_t*>(t)}; }
-__device__ __forceinline__ TupleColumn rid_column(const Tuple* t) { return TupleColumn{reinterpret_cast<const int32_t*>(t) + 1}; }
+__device__ __forceinline__ TupleColumn key_column(const Tuple* t) {
+    return TupleColumn{reinterpret_cast<const int32_t*>(t)};
+}
+__device__ __forceinline__ TupleColumn rid_column(const Tuple* t) {
+    return TupleColumn{reinterpret_cast<const int32_t*>(t) + 1};
+}
 
 // R_i's tuples of this thread, 1 <= n <= RPT * kJoinBlock (rows past n: the last).
 // Plain loads: every S chunk (work item) of a partition reads R_i again.
@@ -932,8 +936,8 @@ void direct_join_t(const DirectJob* jobs, const uint32_t* item_job, const Direct
     const size_t lds = join_lds_bytes(lds_cap, 0, kRids);
     allow_lds((const void*)k_direct_join<RPT, kOne, kRids>, lds);
     rec.before("direct_join");
-    hipLaunchKernelGGL((k_direct_join<RPT, kOne, kRids>), dim3(nitems), dim3(kJoinBlock), lds, rec.stream, jobs, item_job,
-                       one, rec.err_clear, lds_cap);
+    hipLaunchKernelGGL((k_direct_join<RPT, kOne, kRids>), dim3(nitems), dim3(kJoinBlock), lds, rec.stream, jobs,
+                       item_job, one, rec.err_clear, lds_cap);
     rec.after();
 }
 
@@ -1005,7 +1009,8 @@ void join_ovf_build(const OvfBuild& b, uint32_t grid, const Tuple* rt, uint64_t*
     if (grid == 0) return;
     grid = grid < kOvfGrid ? grid : kOvfGrid;
     rec.before("ovf_build");
-    hipLaunchKernelGGL(k_ovf_build, dim3(grid), dim3(kBuildBlock), 0, rec.stream, b, rt, ovf_table, ovf_next, hot, heavy);
+    hipLaunchKernelGGL(k_ovf_build, dim3(grid), dim3(kBuildBlock), 0, rec.stream, b, rt, ovf_table, ovf_next, hot,
+                       heavy);
     rec.after();
 }
 

@@ -369,7 +369,8 @@ __device__ __forceinline__ void sum_rows(const uint32_t* __restrict__ rows, uint
 // L2 before a partition's next run fills them (16M x 16M: 425-442 MB written for
 // 268, 283 read, 4.6 TB/s in 155 us with 16384-tuple tiles, where two
 // scatters of 2^6 took 107 us each before the tuples were one word, the cursors
-// per XCD and the tile's loads and LDS accesses free of branches).  kSelf: partition starts from the rows (self_starts).
+// per XCD and the tile's loads and LDS accesses free of branches).  kSelf:
+// partition starts from the rows (self_starts).
 // Registers: at most 64 up to 8 tuples per thread, so that LDS alone limits
 // the workgroups of a CU (two of 8192 tuples).
 template <uint32_t BLOCK, uint32_t IPT, bool kSeg, bool kNt, bool kCols, bool kSelf, uint32_t kHash>
@@ -424,18 +425,25 @@ k_part_scatter(Pass1 A, const Tuple* __restrict__ in, const PartSeg* __restrict_
     auto clear = [&](uint32_t c) {
         const uint32_t n = kMore ? max(ntiles, clr.share) : ntiles;
         if (kSelf && !clr.r_pairs) {  // R's tiles know R's partitions, and share the clearing among them
-            clear_tables(clr, c, A.nt_r, [&](uint32_t i) { return i < P ? tot[i] : clr.n_r; }, [](uint32_t) { return true; });
+            clear_tables(clr, c, A.nt_r, [&](uint32_t i) { return i < P ? tot[i] : clr.n_r; },
+                         [](uint32_t) { return true; });
             return;
         }
         if constexpr (!kMore) {  // (one copy of the code: three would cost the kernel registers)
             clear_tables(clr, c, n,
-                         [&](uint32_t i) { return i >= clr.npart ? clr.n_r : clr.r_pairs ? clr.r_pairs[i].r_off : clr.start[i]; },
+                         [&](uint32_t i) {
+                             return i >= clr.npart ? clr.n_r : clr.r_pairs ? clr.r_pairs[i].r_off : clr.start[i];
+                         },
                          [&](uint32_t i) { return clr.start[clr.npart + i + 1] != clr.start[clr.npart + i]; });
             return;
         }
         auto cleared = [&](auto begin) {
-            if (kSelf) clear_tables(clr, c, n, begin, [&](uint32_t i) { return (i + 1 < P ? tot[i + 1] : A.n_s) != tot[i]; });
-            else clear_tables(clr, c, n, begin, [&](uint32_t i) { return clr.start[clr.npart + i + 1] != clr.start[clr.npart + i]; });
+            if (kSelf)
+                clear_tables(clr, c, n, begin, [&](uint32_t i) { return (i + 1 < P ? tot[i + 1] : A.n_s) != tot[i]; });
+            else
+                clear_tables(clr, c, n, begin, [&](uint32_t i) {
+                    return clr.start[clr.npart + i + 1] != clr.start[clr.npart + i];
+                });
         };
         if (clr.r_pairs) cleared([&](uint32_t i) { return i < clr.npart ? clr.r_pairs[i].r_off : clr.n_r; });
         else cleared([&](uint32_t i) { return i < clr.npart ? clr.start[i] : clr.n_r; });
@@ -501,7 +509,8 @@ k_part_scatter(Pass1 A, const Tuple* __restrict__ in, const PartSeg* __restrict_
         for (uint32_t i = threadIdx.x; i < (kSelf ? Pp + kWave + kScanScratch + 2 * Pp : Pp); i += BLOCK) cnt[i] = 0;
         __syncthreads();
         bool big = false;
-        if (kSelf) sum_rows<BLOCK>(A.rows, P, tile < A.nt_r ? 0u : A.nt_r, tile < A.nt_r ? A.nt_r : A.ntiles, tile, tot, bef);
+        if (kSelf)
+            sum_rows<BLOCK>(A.rows, P, tile < A.nt_r ? 0u : A.nt_r, tile < A.nt_r ? A.nt_r : A.ntiles, tile, tot, bef);
         uint32_t rank[kSlots];
         if (cfg.bits <= kBallotMaxBits) {  // uniform
 #pragma unroll
@@ -616,9 +625,11 @@ void launch_hist(const Pass1& p1, const PassCfg& cfg, Recorder& rec) {
     static_assert(BLOCK * IPT >= 1024 && BLOCK * IPT <= kMaxScatterTile && BLOCK / kWave <= kScanScratch, "tile shape");
     const size_t lds = sizeof(uint32_t) * (((size_t)1 << (cfg.bits + p1.fine_bits)) + kWave);
     // (workgroups past the tiles' clear words only: 4096 rows in 2^18 partitions, one tile, 2 MB to clear)
-    const uint32_t grid = std::max(p1.self ? p1.ntiles : p1.h.grid(), (uint32_t)std::min<uint64_t>(256, p1.nzero / 4096));
-    const auto fn = p1.fine_bits ? (cfg.nt ? k_part_hist<BLOCK, IPT, true, kHash, true> : k_part_hist<BLOCK, IPT, false, kHash, true>)
-                                 : (cfg.nt ? k_part_hist<BLOCK, IPT, true, kHash, false> : k_part_hist<BLOCK, IPT, false, kHash, false>);
+    const uint32_t grid =
+        std::max(p1.self ? p1.ntiles : p1.h.grid(), (uint32_t)std::min<uint64_t>(256, p1.nzero / 4096));
+    const auto fine = cfg.nt ? k_part_hist<BLOCK, IPT, true, kHash, true> : k_part_hist<BLOCK, IPT, false, kHash, true>;
+    const auto flat = cfg.nt ? k_part_hist<BLOCK, IPT, true, kHash, false> : k_part_hist<BLOCK, IPT, false, kHash, false>;
+    const auto fn = p1.fine_bits ? fine : flat;
     allow_lds(fn, lds);
     rec.before("part_hist");
     hipLaunchKernelGGL(fn, dim3(grid), dim3(BLOCK), lds, rec.stream, p1, cfg);

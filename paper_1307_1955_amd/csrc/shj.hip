@@ -241,7 +241,8 @@ __global__ void __launch_bounds__(kShjBlock) __attribute__((amdgpu_waves_per_eu(
     }
     heavy_writes<kShjBlock, kHeavyV>(Column<1>{r_key}, Column<1>{r_rid}, n_r, &hs, capacity, out_r, out_s);
     if (kOnePass)
-        help_heavy<kShjBlock, kHelpChunk>(heavy, Column<1>{r_key}, Column<1>{r_rid}, total, capacity, out_r, out_s, hs.wsum);
+        help_heavy<kShjBlock, kHelpChunk>(heavy, Column<1>{r_key}, Column<1>{r_rid}, total, capacity, out_r, out_s,
+                                          hs.wsum);
 }
 
 __global__ void __launch_bounds__(256) k_zero_one_pass(uint64_t* __restrict__ total, uint64_t* __restrict__ q,
