@@ -308,6 +308,7 @@ hj_status hj_join_external(const hj_params* p, const hj_rel* R, const hj_rel* S,
         if (e != hipSuccess) return hip_fail("workspace setup", e);
     }
     Ctx C{p, base, ws_bytes, err, H.st[0], H.cnt};
+    uint64_t werr = 0;
     C.out = out;
     const uint32_t k = (R->n && S->n) ? plan_fanout(p, R->n, S->n, ws_bytes) : 0;
     inf.fanout_bits = k;
@@ -350,9 +351,12 @@ hj_status hj_join_external(const hj_params* p, const hj_rel* R, const hj_rel* S,
         if (st != HJ_OK) return st;
         const Clock::time_point t2 = Clock::now();
         inf.partition_s = std::chrono::duration<double>(t2 - t1).count();
+        // boundaries from a scan that gave up may run backwards: nothing is linked
+        e = hipMemcpy(&werr, err, sizeof(uint64_t), hipMemcpyDeviceToHost);
+        if (e != hipSuccess) return hip_fail("error word read", e);
         // link: partition i = the partition-i runs of every chunk
         std::vector<Run> rr, sr;
-        for (uint32_t i = 0; i < P; ++i) {
+        for (uint32_t i = 0; i < P && !werr; ++i) {
             rr.clear();
             sr.clear();
             uint64_t nr = 0, ns = 0;
@@ -375,7 +379,6 @@ hj_status hj_join_external(const hj_params* p, const hj_rel* R, const hj_rel* S,
         }
         inf.join_s = std::chrono::duration<double>(Clock::now() - t2).count();
     }
-    uint64_t werr = 0;
     e = hipMemcpy(&werr, err, sizeof(uint64_t), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail("error word read", e);
     inf.pieces = C.pieces;
